@@ -68,8 +68,13 @@ DupLayout dup_layout(int64_t cap) {
   return D;
 }
 
-static clod_status host_views(int32_t V, const clod_view* vh, HostView* hv, uint32_t& tiles_total,
-                              int64_t& pixels_total, uint32_t& loss_blocks) {
+// Sums over a batch's views, and its largest view in tiles.
+struct HostTotals {
+  uint32_t tiles = 0, loss_blocks = 0, widest = 0, tallest = 0;
+  int64_t pixels = 0, rows = 0;
+};
+
+static clod_status host_views(int32_t V, const clod_view* vh, HostView* hv, HostTotals& t) {
   uint64_t tb = 0, pb = 0, lb = 0;
   for (int v = 0; v < V; ++v) {
     const clod_view& c = vh[v];
@@ -87,16 +92,21 @@ static clod_status host_views(int32_t V, const clod_view* vh, HostView* hv, uint
     tb += (uint64_t)h.tiles_x * h.tiles_y;
     pb += (uint64_t)c.width * c.height;
     lb += h.loss_blocks;
+    t.rows += h.tiles_y;
+    if ((uint32_t)h.tiles_x > t.widest) t.widest = (uint32_t)h.tiles_x;
+    if ((uint32_t)h.tiles_y > t.tallest) t.tallest = (uint32_t)h.tiles_y;
     if (tb >= 0xFFFFFFFFull || pb >= 0xFFFFFFFFull) return fail(CLOD_E_ARG, "batch too large (tiles or pixels exceed 2^32)");
   }
-  tiles_total = (uint32_t)tb;
-  pixels_total = (int64_t)pb;
-  loss_blocks = (uint32_t)lb;
+  t.tiles = (uint32_t)tb;
+  t.pixels = (int64_t)pb;
+  t.loss_blocks = (uint32_t)lb;
   return CLOD_OK;
 }
 
-static Layout make_layout(int64_t n, int32_t V, uint32_t tiles_total, int64_t pixels_total, bool any_budget) {
+static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_budget) {
   Layout L;
+  const uint32_t tiles_total = t.tiles;
+  const int64_t pixels_total = t.pixels;
   L.any_budget = any_budget;
   L.n = n;
   L.V = V;
@@ -104,6 +114,15 @@ static Layout make_layout(int64_t n, int32_t V, uint32_t tiles_total, int64_t pi
   L.tiles_total = tiles_total;
   L.pixels_total = pixels_total;
   L.scan_blocks = (int32_t)((L.VN + kScanChunk - 1) / kScanChunk);
+  L.rec_groups = (uint32_t)((L.VN + (int64_t)kRecChunk * kRecGroup - 1) / ((int64_t)kRecChunk * kRecGroup));
+  L.row_path = L.VN > 0 && t.rows <= (int64_t)kRowBinsMax && t.widest <= kColsMax && t.tallest <= kColsMax;
+  if (L.row_path) {
+    L.rows = (uint32_t)t.rows;
+    L.row_bins = kBlock;
+    while (L.row_bins < L.rows) L.row_bins *= 2;
+    L.cols = (t.widest + 63u) / 64u * 64u;
+    L.units_max = kHistWords / L.cols;
+  }
   size_t o = 0;
   L.hdr = o; o = align256(o + kHdrWords * 8);
   L.vinfo = o; o = align256(o + (size_t)V * sizeof(DevView));
@@ -123,11 +142,17 @@ static Layout make_layout(int64_t n, int32_t V, uint32_t tiles_total, int64_t pi
   L.flags = o; o = align256(o + (size_t)L.VN);
   L.alpha = o; o = align256(o + (size_t)L.VN * 4);
   L.rec = o; o = align256(o + (size_t)L.VN * kRecBytes);
-  L.scan_part = o; o = align256(o + ((size_t)L.scan_blocks + 1) * 4 * 2);   // records, emission
+  L.scan_part = o; o = align256(o + ((size_t)L.scan_blocks + 1) * 4);       // compaction, emission chunks
   L.ranges = o; o = align256(o + (size_t)tiles_total * 8);
   L.order = o; o = align256(o + (size_t)tiles_total * 4);
-  L.tord = o; o = align256(o + (size_t)kTileOrderWords * 4);
+  L.tord = o; o = align256(o + ((size_t)kTileOrderWords + (size_t)kOrderCopies * kTileBuckets) * 4);
   L.pair_part = o; o = align256(o + (size_t)tiles_total * 3 * 8);
+  L.sort_hist = o; o = align256(o + (L.VN > 0 ? (size_t)kHistWords * 4 : 0));
+  L.sort_stat = o; o = align256(o + (size_t)L.scan_blocks * sizeof(DepthStat));
+  L.sort_gcount = o; o = align256(o + (size_t)L.rec_groups * kLineWords * 4);
+  L.sort_gsum = o; o = align256(o + (L.VN > 0 ? (size_t)kDepthCounterWords * 4 : 0));
+  L.row_tab = o; o = align256(o + (L.row_path ? (4 * ((size_t)L.rows + 1) + L.units_max) * 4 : 0));
+  L.tcount = o; o = align256(o + (L.row_path ? (size_t)tiles_total * 4 : 0));
   L.gscreen = o; o = align256(o + (size_t)L.VN * kGscreen * 4);
   L.total = o;
   return L;
@@ -191,16 +216,16 @@ static clod_status prepare(const clod_batch* b, bool need_full_ws, Ctx& cx) {
     st = check_view(b->views_host[v], v);
     if (st != CLOD_OK) return st;
   }
-  uint32_t tiles_total;
-  int64_t pixels_total;
-  st = host_views(b->n_views, b->views_host, cx.hv, tiles_total, pixels_total, cx.loss_blocks);
+  HostTotals totals;
+  st = host_views(b->n_views, b->views_host, cx.hv, totals);
   if (st != CLOD_OK) return st;
+  cx.loss_blocks = totals.loss_blocks;
   const int64_t n = b->n;
   if (n < 0) return fail(CLOD_E_ARG, "batch->n must be >= 0");
   if (n * (int64_t)b->n_views >= 0xFFFFFFFFll) return fail(CLOD_E_ARG, "n * n_views must be < 2^32");
   bool any_budget = false;
   for (int v = 0; v < b->n_views; ++v) any_budget = any_budget || b->views_host[v].budget > 0;
-  cx.L = make_layout(n, b->n_views, tiles_total, pixels_total, any_budget);
+  cx.L = make_layout(n, b->n_views, totals, any_budget);
   for (int v = 0; v < b->n_views; ++v)
     cx.L.ssim_regions += (uint32_t)(((cx.hv[v].tiles_x + 1) / 2) * ((cx.hv[v].tiles_y + 1) / 2));
   // The per-view area and the projection work list precede the per-(view, Gaussian) planes.
@@ -290,22 +315,21 @@ static hipError_t project_stages(const clod_scene& sc, const clod_view* views_de
   if (e == hipSuccess)
     e = launch_project(sc, vinfo, L.V, prm, dmax_key, (uint32_t*)(w + L.cpart), (unsigned long long*)(w + L.counts),
                        counts_dev, eta_dev, (uint8_t*)(w + L.flags), (float*)(w + L.alpha), (float4*)(w + L.rec),
-                       (uint32_t*)(w + L.list), (uint32_t*)(w + L.lcount), out);
+                       (uint32_t*)(w + L.list), (uint32_t*)(w + L.lcount), (uint32_t*)(w + L.sort_gcount),
+                       L.rec_groups * kLineWords, out);
   return e;
 }
 
 static hipError_t bin_stages(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out) {
-  hipError_t e = launch_bin_sort(L, ws, D, dup, out);
-  if (e == hipSuccess) e = launch_ranges(L, ws, D, dup, sorted_buffer(L.tiles_total), out);
-  return e;
+  return launch_bin_sort(L, ws, D, dup, out);
 }
 
 static const uint32_t* sorted_vals(const clod_batch* b, const Layout& L, const DupLayout& D) {
-  return (const uint32_t*)((const char*)b->dup + (sorted_buffer(L.tiles_total) ? D.vals1 : D.vals0));
+  return (const uint32_t*)((const char*)b->dup + (sorted_buffer(L) ? D.vals1 : D.vals0));
 }
 
 static BlendBufs blend_bufs(const clod_batch* b, const Layout& L, const DupLayout& D) {
-  const bool odd = sorted_buffer(L.tiles_total) != 0;
+  const bool odd = sorted_buffer(L) != 0;
   char* dp = (char*)b->dup;
   const size_t k = odd ? D.keys0 : D.keys1, v = odd ? D.vals0 : D.vals1;   // adjacent: keys, then values
   return BlendBufs{sorted_vals(b, L, D), (unsigned long long*)(dp + k), v + (size_t)D.cap * 4 - k, D.cap};
@@ -324,12 +348,11 @@ const char* clod_last_error(void) { return g_err; }
 size_t clod_ws_bytes(int64_t n, int32_t n_views, const clod_view* views_host) {
   if (n < 0 || n_views < 1 || n_views > CLOD_MAX_VIEWS || !views_host) return 0;
   HostView hv[CLOD_MAX_VIEWS];
-  uint32_t tiles_total, lb;
-  int64_t pixels_total;
-  if (host_views(n_views, views_host, hv, tiles_total, pixels_total, lb) != CLOD_OK) return 0;
+  HostTotals totals;
+  if (host_views(n_views, views_host, hv, totals) != CLOD_OK) return 0;
   bool any_budget = false;
   for (int v = 0; v < n_views; ++v) any_budget = any_budget || views_host[v].budget > 0;
-  return make_layout(n, n_views, tiles_total, pixels_total, any_budget).total;
+  return make_layout(n, n_views, totals, any_budget).total;
 }
 
 size_t clod_dup_bytes(int64_t capacity) {
@@ -657,7 +680,7 @@ clod_status clod_inspect(const clod_batch* batch, int32_t section, const void** 
     DupLayout D;
     st = dup_check(batch, D);
     if (st != CLOD_OK) return st;
-    const bool odd = sorted_buffer(L.tiles_total) != 0;
+    const bool odd = sorted_buffer(L) != 0;
     const size_t off = section == CLOD_SEC_KEYS ? (odd ? D.keys1 : D.keys0) : (odd ? D.vals1 : D.vals0);
     *dev_ptr = (const char*)batch->dup + off;
     *count = D.cap;

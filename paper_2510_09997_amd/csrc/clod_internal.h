@@ -15,7 +15,7 @@ constexpr int kBlock = 256;                // threads per workgroup (4 wave64)
 // aligned 64-byte segment: (u, v, alpha'', radius), (conic A, B, C, 0), (r, g, b, 0), unused.
 constexpr int kRecQuads = 4;
 constexpr int kRecBytes = kRecQuads * 16;
-constexpr int kScanItems = 16;             // items per thread in the tiles-touched scan
+constexpr int kScanItems = 16;             // items per thread in the emission's chunks
 constexpr int kScanChunk = kBlock * kScanItems;
 // Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the number of long
 // tiles (lists of at least 2^(kLongBucket - 1) entries, the leading positions of the order).
@@ -30,6 +30,22 @@ constexpr int kTileOrderChunk = 1024;       // tiles per block in the ordering k
 constexpr int kSortItems = 8;              // keys per thread per radix tile
 constexpr int kSortTile = kBlock * kSortItems;   // 2048 keys per radix tile
 constexpr int kMaxSortBlocks = 1024;
+// Depth sort and row / column partitions (bin.hip): blocks per radix pass, blocks per group sum,
+// words of the wave count rows, digits of the first depth pass and of the widest partition.
+constexpr uint32_t kRadixBlocksMax = 1024;
+constexpr uint32_t kGroup = 32, kGroups = kRadixBlocksMax / kGroup;
+constexpr uint32_t kHistWords = 1u << 21;
+constexpr uint32_t kRecChunk = 16 * kBlock;  // flags per block of the compaction, chunks per group sum
+constexpr uint32_t kRecGroup = 64, kLineWords = 32;
+constexpr int kDepthBits0 = 9;
+constexpr uint32_t kDepthBins0 = 1u << kDepthBits0;
+constexpr uint32_t kRowBinsMax = 2048;     // tile rows of a batch in the row path
+constexpr uint32_t kColsMax = 256;         // tile columns (and rows) of a view in the row path
+constexpr uint32_t kUnit = 512;            // least row pairs per column unit
+constexpr uint32_t kOrderCopies = 32;      // copies of the length-class counters
+__host__ __device__ constexpr uint32_t radix_blocks(uint32_t bins) {
+  return kHistWords / (4u * bins) < kRadixBlocksMax ? kHistWords / (4u * bins) : kRadixBlocksMax;
+}
 constexpr int kMaxProjBlocks = 2048;      // per-block partial reductions of the per-Gaussian passes
 constexpr int kGscreen = 9;                // du, dv, dA, dB, dC, dalpha'', dr, dg, db (interleaved per record)
 
@@ -40,6 +56,7 @@ struct DevView {
   float s_v, limx, limy, tau_sv;
   int32_t width, height, tiles_x, tiles_y;
   uint32_t tile_base, pix_base, loss_block_base, rgn_base;   // rgn_base: first 32 x 32 SSIM region
+  uint32_t row_base;             // first tile row in the batch
   int32_t ftiles_x, ftiles_y;    // tiles of the frame (the view's own when it is not a viewport)
   int32_t vx, vy;                // viewport origin in the frame, pixels (multiples of 16)
   int32_t cam_lead;              // first view of this view's run of consecutive views with the same
@@ -56,8 +73,24 @@ struct SelState {
 };
 constexpr int kSelBlocks = 128;   // blocks per view of the select histograms
 
-// Workspace header words (uint64).
-enum : int { kHdrDup = 0, kHdrOverflow = 1, kHdrRend = 2, kHdrWords = 8 };
+// Workspace header words (uint64): pairs, overflow flag, rendered records; of the depth sort the
+// subtrahend of the keys and their bit length; row pairs per column unit and column units.
+enum : int { kHdrDup = 0, kHdrOverflow = 1, kHdrRend = 2, kHdrKeyBase = 3, kHdrKeyBits = 4, kHdrUnit = 5,
+             kHdrUnits = 6, kHdrWords = 8 };
+
+// Per chunk of the compaction: tile pairs and largest depth key.
+struct DepthStat {
+  unsigned long long pairs;
+  uint32_t kmax, reserved;
+};
+
+constexpr uint32_t kDepthCounterWords = kGroups * (kDepthBins0 + 3 * kRowBinsMax);
+
+// Per tile row of the batch (one more entry closes the ranges): first tile, first row pair, first
+// column unit; tile pairs of the row; and the row of every column unit.
+struct RowTables {
+  uint32_t *tile, *start, *ustart, *pairs, *urow;
+};
 
 struct Layout {
   int64_t n = 0;
@@ -68,9 +101,14 @@ struct Layout {
   int64_t pixels_total = 0;
   int32_t scan_blocks = 0;
   bool any_budget = false;    // some view selects by budget (allocates the select histograms)
+  // The row path of the binning: at most kRowBinsMax tile rows in the batch and views of at most
+  // kColsMax x kColsMax tiles (the LDS counters of a pass, and a rectangle packed in 32 bits).
+  bool row_path = false;
+  uint32_t rows = 0, row_bins = 0, cols = 0, units_max = 0;
+  uint32_t rec_groups = 0;    // groups of the compaction's chunks (scan_blocks of them)
   // byte offsets into ws
   size_t hdr, vinfo, dmax_key, counts, gdmax, loss_acc, kpart, cpart, gpart, ssim_acc, loss_part, sel_state, sel_hist, lcount, list, flags, alpha, rec,
-      scan_part, ranges, order, tord, pair_part, gscreen, total;
+      scan_part, ranges, order, tord, pair_part, sort_hist, sort_stat, sort_gcount, sort_gsum, row_tab, tcount, gscreen, total;
 };
 
 // Host-side per-view geometry (must agree with k_view_setup).
@@ -90,7 +128,7 @@ struct DupLayout {
 DupLayout dup_layout(int64_t cap);
 int sort_blocks(int64_t cap);
 int tile_passes(uint32_t tiles_total);     // radix passes of the tile-id sort
-int sorted_buffer(uint32_t tiles_total);   // ping-pong buffer (0/1) holding the sorted pairs
+int sorted_buffer(const Layout& L);        // ping-pong buffer (0/1) holding the sorted pairs
 
 // ----------------------------------------------------------------------------------------
 // Binary32 contract arithmetic (device).  The translation units are compiled with
@@ -348,6 +386,10 @@ struct Blk {
 };
 __device__ __forceinline__ Blk grid_blk() { return Blk{blockIdx.x, gridDim.x}; }
 
+__device__ __forceinline__ void zero_words(uint32_t* p, uint32_t count, Blk b) {
+  for (uint32_t i = b.id * kBlock + threadIdx.x; i < count; i += b.n * kBlock) p[i] = 0u;
+}
+
 // Contiguous chunk [lo, hi) of n items owned by block b (grids capped at kMaxProjBlocks).
 __device__ __forceinline__ void block_chunk(int64_t n, Blk b, int64_t& lo, int64_t& hi) {
   const int64_t per = (n + b.n - 1) / b.n;
@@ -473,7 +515,8 @@ __device__ __forceinline__ bool lod_kept(const DevView& Vw, float a2, int64_t i)
 // ----------------------------------------------------------------------------------------
 enum StageKind : int32_t {
   kStViewSetup = 1, kStFill, kStFrustumMax, kStFold, kStClassify, kStProject, kStSelectHist, kStSelectPick,
-  kStScanReduce, kStScanPartials, kStCompact, kStRadixUp, kStRadixScan, kStRadixDown, kStEmitReduce,
+  kStRecCount, kStRecCompact, kStDepthUp, kStDepthDown, kStRowUp, kStRowDown, kStColUp, kStColScan, kStColDown,
+  kStRadixUp, kStRadixScan, kStRadixDown, kStEmitReduce,
   kStEmitPartials, kStEmitOffsets, kStEmit, kStRanges, kStTileCount, kStTileScatter, kStBlend, kStReducePairs,
   kStLongMask
 };
@@ -490,6 +533,7 @@ struct FrustumArgs {
 struct FoldArgs {   // per-view folds of the per-block partials (frustum maximum or counts)
   const unsigned long long* kpart; const uint32_t* cpart; int32_t G, V; unsigned long long* dmax_key;
   unsigned long long* counts; int64_t* counts_dev; int64_t n; float* eta_dev;
+  uint32_t* clear; uint32_t clear_words;   // counters the depth sort starts with (or none)
 };
 struct ClassifyArgs {
   clod_scene sc; const DevView* views; int32_t V, write; clod_params prm; const unsigned long long* dmax_key;
@@ -504,15 +548,22 @@ struct SelectArgs {
   clod_scene sc; DevView* views; int32_t V; clod_params prm; const unsigned long long* dmax_key;
   SelState* state; uint32_t* hist; int32_t pass;
 };
-struct ScanReduceArgs {
-  const uint8_t* flags; int64_t count; uint32_t* partR; uint32_t* ranges; int64_t range_words;
+struct DepthArgs {   // the passes of the depth sort share it
+  const uint8_t* flags; int64_t VN; const float4* rec; unsigned long long* hdr; uint32_t* hist; uint32_t* gsum;
+  uint32_t* gnext;      // group sums of the pass after this one, cleared here
+  DepthStat* stat; uint32_t* part; uint32_t* gcount; const uint2* in; uint2* out; uint32_t* kout; uint32_t* vout; int64_t cap;
+  uint32_t* tord; uint32_t* ranges; int64_t range_words;
+  uint32_t chunks, groups, tord_words, row_bins; int32_t pass, pad;
 };
-struct ScanPartialsArgs {
-  uint32_t* partR; int32_t nparts; unsigned long long* hdr; int64_t cap; uint32_t* tord;
+struct RowArgs {
+  const DevView* views; int32_t V; uint32_t rows; int64_t n; unsigned long long* hdr; const uint32_t* rect;
+  const uint32_t* f; uint2* out; uint32_t* hist; uint32_t* gsum; RowTables tab; uint32_t bins, units_max, tiles_total;
+  float inv_n;
 };
-struct CompactArgs {
-  const uint8_t* flags; int64_t count; const uint32_t* partR; const float4* rec; const unsigned long long* hdr;
-  uint32_t* kout; uint32_t* vout;
+struct ColArgs {
+  unsigned long long* hdr; const uint2* in; uint32_t* hist; RowTables tab; uint32_t* tcount; uint2* ranges;
+  uint32_t* tord; uint32_t* tordc; uint32_t* order; uint32_t* kout; uint32_t* vout; uint32_t* clear;
+  uint32_t cols, tiles_total, clear_words, pad;
 };
 struct RadixArgs {   // one pass: upsweep, digit scan and downsweep share it
   const uint32_t* kin; const uint32_t* vin; uint32_t* kout; uint32_t* vout; uint32_t* hist;
@@ -537,6 +588,7 @@ struct RangesArgs {
 };
 struct TileOrderArgs {
   const uint2* ranges; uint32_t tiles; const unsigned long long* hdr; uint32_t* tord; uint32_t* order;
+  uint32_t* clear; uint32_t clear_words, pad;   // counters the next depth sort starts with
 };
 struct BlendArgs {
   const DevView* views; int32_t V; uint32_t tiles_total; int64_t VN; const float4* rec; const uint2* ranges;
@@ -565,8 +617,8 @@ struct Stage {
   uint32_t lds;     // dynamic LDS bytes of the per-stage launch
   union {
     ViewSetupArgs view_setup; FillArgs fill; FrustumArgs frustum; FoldArgs fold; ClassifyArgs classify;
-    ProjectArgs project; SelectArgs select; ScanReduceArgs scan_reduce; ScanPartialsArgs scan_partials;
-    CompactArgs compact; RadixArgs radix; EmitReduceArgs emit_reduce; EmitPartialsArgs emit_partials;
+    ProjectArgs project; SelectArgs select; DepthArgs depth; RowArgs row;
+    ColArgs col; RadixArgs radix; EmitReduceArgs emit_reduce; EmitPartialsArgs emit_partials;
     EmitOffsetsArgs emit_offsets; EmitArgs emit; RangesArgs ranges; TileOrderArgs tile_order; BlendArgs blend;
     ReducePairsArgs reduce_pairs; LongMaskArgs long_mask;
   } a;
@@ -581,6 +633,7 @@ struct Program {
 
 hipError_t launch_stage(const Stage& st, hipStream_t s);
 hipError_t launch_project_stage(const Stage& st, hipStream_t s);
+hipError_t launch_bin_stage(const Stage& st, hipStream_t s);
 hipError_t launch_sort_stage(const Stage& st, hipStream_t s);
 hipError_t launch_blend_stage(const Stage& st, hipStream_t s);
 
@@ -631,7 +684,7 @@ hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V,
 hipError_t launch_project(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
                           unsigned long long* dmax_key, uint32_t* cpart, unsigned long long* counts,
                           int64_t* counts_dev, float* eta_dev, uint8_t* flags, float* alpha, float4* rec, uint32_t* list,
-                          uint32_t* lcount, const Sink& out);
+                          uint32_t* lcount, uint32_t* clear, uint32_t clear_words, const Sink& out);
 hipError_t launch_lod_count(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
                             unsigned long long* dmax_key, uint32_t* cpart, unsigned long long* counts,
                             int64_t* counts_dev, float* eta_dev, uint32_t* list, uint32_t* lcount, const Sink& out);
@@ -657,8 +710,7 @@ hipError_t launch_lod_select(const clod_scene& sc, DevView* vinfo, int V, clod_p
                              const unsigned long long* dmax_key, SelState* state, uint32_t* hist, const Sink& out);
 
 hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out);
-hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, int parity,
-                         const Sink& out);
+hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out);
 
 // The pair buffers the forward blend reads: the sorted record indices, and the two arrays the
 // tile-id sort left free (they hold the very long tiles' block bit planes).

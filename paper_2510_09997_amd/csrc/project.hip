@@ -9,34 +9,42 @@
 
 namespace clod {
 
-// Derives per-view constants on the device (graph-replay safe: reads only views_dev).
-// With `hdr` non-NULL the workspace header is cleared as well (a new projection).
+// Derives per-view constants on the device (graph-replay safe: reads only views_dev).  With `hdr`
+// non-NULL the workspace header is cleared as well (a new projection).  One wave, a view per lane:
+// the running bases are wave scans (one thread walking the views took 12 us for five views and
+// 57 us for 64, on every render's critical path).
 __device__ __forceinline__ void view_setup_body(const ViewSetupArgs& a, Blk b) {
   const clod_view* __restrict__ views = a.views;
   const int V = a.V;
   const clod_params& prm = a.prm;
   DevView* __restrict__ out = a.out;
-  if (a.hdr && b.id == 0 && threadIdx.x < (unsigned)kHdrWords) a.hdr[threadIdx.x] = 0ull;
-  if (threadIdx.x != 0 || b.id != 0) return;
-  uint32_t tile_base = 0, pix_base = 0, loss_base = 0, rgn_base = 0;
+  if (b.id != 0 || threadIdx.x >= 64u) return;
+  const int lane = (int)threadIdx.x;
+  if (a.hdr && lane < kHdrWords)
+    a.hdr[lane] = lane == kHdrKeyBase ? (unsigned long long)__float_as_uint(prm.near_z) : 0ull;
+  uint32_t tile_base = 0, pix_base = 0, loss_base = 0, rgn_base = 0, row_base = 0;
+  int lead = 0;
   // Same camera: every field the positions, projections and colours depend on, bit for bit.
   auto same_camera = [](const clod_view& p, const clod_view& q) {
-    for (int j = 0; j < 9; ++j)
-      if (__float_as_uint(p.W[j]) != __float_as_uint(q.W[j])) return false;
+    uint32_t diff = 0;
+    for (int j = 0; j < 9; ++j) diff |= __float_as_uint(p.W[j]) ^ __float_as_uint(q.W[j]);
     for (int j = 0; j < 3; ++j)
-      if (__float_as_uint(p.t[j]) != __float_as_uint(q.t[j]) || __float_as_uint(p.c[j]) != __float_as_uint(q.c[j]))
-        return false;
-    return __float_as_uint(p.fx) == __float_as_uint(q.fx) && __float_as_uint(p.fy) == __float_as_uint(q.fy) &&
-           __float_as_uint(p.cx) == __float_as_uint(q.cx) && __float_as_uint(p.cy) == __float_as_uint(q.cy) &&
-           p.width == q.width && p.height == q.height && p.frame_width == q.frame_width &&
-           p.frame_height == q.frame_height && p.vx == q.vx && p.vy == q.vy;
+      diff |= (__float_as_uint(p.t[j]) ^ __float_as_uint(q.t[j])) | (__float_as_uint(p.c[j]) ^ __float_as_uint(q.c[j]));
+    diff |= (__float_as_uint(p.fx) ^ __float_as_uint(q.fx)) | (__float_as_uint(p.fy) ^ __float_as_uint(q.fy)) |
+            (__float_as_uint(p.cx) ^ __float_as_uint(q.cx)) | (__float_as_uint(p.cy) ^ __float_as_uint(q.cy));
+    diff |= (uint32_t)((p.width ^ q.width) | (p.height ^ q.height) | (p.frame_width ^ q.frame_width) |
+                       (p.frame_height ^ q.frame_height) | (p.vx ^ q.vx) | (p.vy ^ q.vy));
+    return diff == 0u;
   };
-  int lead = 0;
-  for (int v = 0; v < V; ++v) {
-    const clod_view& cv = views[v];
+  for (int v0 = 0; v0 < V; v0 += 64) {
+    const int v = v0 + lane;
+    const bool valid = v < V;
+    const clod_view& cv = views[valid ? v : V - 1];
+    const uint64_t starts = ballot64(valid && (v == 0 || !same_camera(cv, views[v - 1])));
+    const uint64_t upto = starts & (lanemask_lt() | (1ull << lane));
     DevView d;
-    if (v == 0 || !same_camera(cv, views[v - 1])) lead = v;
-    d.cam_lead = lead;
+    d.cam_lead = upto ? v0 + 63 - __builtin_clzll(upto) : lead;
+    lead = starts ? v0 + 63 - __builtin_clzll(starts) : lead;
     for (int j = 0; j < 9; ++j) d.W[j] = cv.W[j];
     for (int j = 0; j < 3; ++j) { d.t[j] = cv.t[j]; d.c[j] = cv.c[j]; }
     d.fx = cv.fx; d.fy = cv.fy; d.cx = cv.cx; d.cy = cv.cy;
@@ -55,17 +63,28 @@ __device__ __forceinline__ void view_setup_body(const ViewSetupArgs& a, Blk b) {
     d.height = cv.height;
     d.tiles_x = (cv.width + kTile - 1) / kTile;
     d.tiles_y = (cv.height + kTile - 1) / kTile;
-    d.tile_base = tile_base;
-    d.pix_base = pix_base;
-    d.loss_block_base = loss_base;
-    d.rgn_base = rgn_base;
     d.budget = cv.budget;
     d.mkey = 0ull;
-    tile_base += (uint32_t)(d.tiles_x * d.tiles_y);
-    rgn_base += (uint32_t)(((d.tiles_x + 1) / 2) * ((d.tiles_y + 1) / 2));
-    pix_base += (uint32_t)(cv.width * cv.height);
-    loss_base += (uint32_t)((3u * (uint32_t)(cv.width * cv.height) + kLossChunk - 1) / kLossChunk);
-    out[v] = d;
+    // Running bases: the sums over the views before this one.
+    auto before = [&](uint32_t mine, uint32_t& base) {
+      uint32_t inc = valid ? mine : 0u;
+      const uint32_t own = inc;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += up;
+      }
+      const uint32_t first = base + inc - own;
+      base += __shfl(inc, 63, 64);
+      return first;
+    };
+    const uint32_t px = (uint32_t)(cv.width * cv.height);
+    d.tile_base = before((uint32_t)(d.tiles_x * d.tiles_y), tile_base);
+    d.rgn_base = before((uint32_t)(((d.tiles_x + 1) / 2) * ((d.tiles_y + 1) / 2)), rgn_base);
+    d.pix_base = before(px, pix_base);
+    d.loss_block_base = before((3u * px + kLossChunk - 1) / kLossChunk, loss_base);
+    d.row_base = before((uint32_t)d.tiles_y, row_base);
+    if (valid) out[v] = d;
   }
 }
 __global__ void k_view_setup(ViewSetupArgs a) { view_setup_body(a, grid_blk()); }
@@ -139,6 +158,7 @@ __device__ __forceinline__ void fold_view(int v, const unsigned long long* __res
 
 // Block v folds view v.
 __device__ __forceinline__ void fold_body(const FoldArgs& a, Blk b) {
+  zero_words(a.clear, a.clear_words, b);
   fold_view((int)b.id, a.kpart, a.cpart, a.G, a.V, a.n, a.dmax_key, a.counts, a.counts_dev, a.eta_dev);
 }
 __global__ __launch_bounds__(kBlock) void k_reduce_partials(FoldArgs a) { fold_body(a, grid_blk()); }
@@ -681,12 +701,12 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, const Sin
 
 static Stage fold_stage(const unsigned long long* kpart, const uint32_t* cpart, int G, int V,
                         unsigned long long* dmax_key, unsigned long long* counts, int64_t* counts_dev, int64_t n,
-                        float* eta_dev) {
+                        float* eta_dev, uint32_t* clear, uint32_t clear_words) {
   Stage st{};
   st.kind = kStFold;
   st.items = (uint32_t)V;
   st.block = kBlock;
-  st.a.fold = FoldArgs{kpart, cpart, G, V, dmax_key, counts, counts_dev, n, eta_dev};
+  st.a.fold = FoldArgs{kpart, cpart, G, V, dmax_key, counts, counts_dev, n, eta_dev, clear, clear_words};
   return st;
 }
 
@@ -701,7 +721,7 @@ hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V,
   st.a.frustum = FrustumArgs{sc.mean, sc.n, vinfo, V, near_z, kpart};
   hipError_t e = out.put(st);
   if (e == hipSuccess)
-    e = out.put(fold_stage(kpart, nullptr, G, V, dmax_key, nullptr, nullptr, sc.n, nullptr));
+    e = out.put(fold_stage(kpart, nullptr, G, V, dmax_key, nullptr, nullptr, sc.n, nullptr, nullptr, 0));
   return e;
 }
 
@@ -709,7 +729,8 @@ template <bool kWrite>
 static hipError_t project_impl(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
                                unsigned long long* dmax_key, uint32_t* cpart, unsigned long long* counts,
                                int64_t* counts_dev, float* eta_dev, uint8_t* flags, float* alpha, float4* rec,
-                               uint32_t* list, uint32_t* lcount, const Sink& out) {
+                               uint32_t* list, uint32_t* lcount, uint32_t* clear, uint32_t clear_words,
+                               const Sink& out) {
   if (sc.n == 0) {
     hipError_t e = launch_fill_u32((uint32_t*)counts, 0u, 6 * (int64_t)V, out);
     if (e == hipSuccess && counts_dev) e = launch_fill_u32((uint32_t*)counts_dev, 0u, 6 * (int64_t)V, out);
@@ -736,15 +757,15 @@ static hipError_t project_impl(const clod_scene& sc, const DevView* vinfo, int V
   e = out.put(p);
   if (e != hipSuccess) return e;
   // Counts to the workspace and the caller, and the argmax index into the d_max key.
-  return out.put(fold_stage(nullptr, cpart, G, V, dmax_key, counts, counts_dev, sc.n, eta_dev));
+  return out.put(fold_stage(nullptr, cpart, G, V, dmax_key, counts, counts_dev, sc.n, eta_dev, clear, clear_words));
 }
 
 hipError_t launch_project(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
                           unsigned long long* dmax_key, uint32_t* cpart, unsigned long long* counts,
                           int64_t* counts_dev, float* eta_dev, uint8_t* flags, float* alpha, float4* rec,
-                          uint32_t* list, uint32_t* lcount, const Sink& out) {
+                          uint32_t* list, uint32_t* lcount, uint32_t* clear, uint32_t clear_words, const Sink& out) {
   return project_impl<true>(sc, vinfo, V, prm, dmax_key, cpart, counts, counts_dev, eta_dev, flags, alpha, rec, list,
-                            lcount, out);
+                            lcount, clear, clear_words, out);
 }
 
 hipError_t launch_lod_count(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
@@ -752,7 +773,7 @@ hipError_t launch_lod_count(const clod_scene& sc, const DevView* vinfo, int V, c
                             int64_t* counts_dev, float* eta_dev, uint32_t* list, uint32_t* lcount,
                             const Sink& out) {
   return project_impl<false>(sc, vinfo, V, prm, dmax_key, cpart, counts, counts_dev, eta_dev, nullptr, nullptr,
-                             nullptr, list, lcount, out);
+                             nullptr, list, lcount, nullptr, 0, out);
 }
 
 // One kernel per stage kind of this file (the template instance the arguments select).

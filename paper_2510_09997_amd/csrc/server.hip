@@ -27,6 +27,7 @@
 // barrier (the scoped model makes the other waves' writes visible through it).  Idle workers
 // poll one epoch word, bumped whenever a job or a stage opens, instead of the claim words.
 #include "project.hip"
+#include "bin.hip"
 #include "sort.hip"
 #include "blend.hip"
 
@@ -40,8 +41,10 @@ hipError_t launch_stage(const Stage& st, hipStream_t s) {
     case kStViewSetup: case kStFill: case kStFrustumMax: case kStFold: case kStClassify: case kStProject:
     case kStSelectHist: case kStSelectPick:
       return launch_project_stage(st, s);
-    case kStScanReduce: case kStScanPartials: case kStCompact: case kStRadixUp: case kStRadixScan:
-    case kStRadixDown: case kStEmitReduce: case kStEmitPartials: case kStEmitOffsets: case kStEmit:
+    case kStRecCount: case kStRecCompact: case kStDepthUp: case kStDepthDown: case kStRowUp: case kStRowDown:
+    case kStColUp: case kStColScan: case kStColDown:
+      return launch_bin_stage(st, s);
+    case kStRadixUp: case kStRadixScan: case kStRadixDown: case kStEmitReduce: case kStEmitPartials: case kStEmitOffsets: case kStEmit:
     case kStRanges: case kStTileCount: case kStTileScatter:
       return launch_sort_stage(st, s);
     case kStBlend: case kStReducePairs: case kStLongMask:
@@ -218,7 +221,10 @@ __device__ void srv_dispatch(SrvDev* D, SrvHost* H, uint64_t deadline) {
 // ---------------------------------------------------------------------------- workers
 union SrvLds {
   TileLds tile;
-  CompactLds compact;
+  RecLds rec;
+  RadixLds radix;
+  uint32_t row[row_lds_words(kRowBinsMax)];
+  ColLds col;
   UpsweepLds up;
   DownsweepLds down;
   OffsetsLds offsets;
@@ -265,9 +271,15 @@ __device__ bool srv_run(int32_t kind, const Stage& st, Blk b, SrvLds& U) {
     }
     case kStSelectHist: select_hist_body(uniform_copy(st.a.select), b); return true;
     case kStSelectPick: select_pick_body(uniform_copy(st.a.select), b); return true;
-    case kStScanReduce: scan_reduce_body(uniform_copy(st.a.scan_reduce), b); return true;
-    case kStScanPartials: scan_partials_body(uniform_copy(st.a.scan_partials), b); return true;
-    case kStCompact: compact_body(uniform_copy(st.a.compact), b, U.compact); return true;
+    case kStRecCount: rec_count_body(uniform_copy(st.a.depth), b); return true;
+    case kStRecCompact: rec_compact_body(uniform_copy(st.a.depth), b, U.rec); return true;
+    case kStDepthUp: depth_up_body(uniform_copy(st.a.depth), b, U.radix); return true;
+    case kStDepthDown: depth_down_body(uniform_copy(st.a.depth), b, U.radix); return true;
+    case kStRowUp: row_up_body(uniform_copy(st.a.row), b, U.row); return true;
+    case kStRowDown: row_down_body(uniform_copy(st.a.row), b, U.row); return true;
+    case kStColUp: col_up_body(uniform_copy(st.a.col), b); return true;
+    case kStColScan: col_scan_body(uniform_copy(st.a.col), b); return true;
+    case kStColDown: col_down_body(uniform_copy(st.a.col), b, U.col); return true;
     case kStRadixUp: radix_upsweep_body(uniform_copy(st.a.radix), b, U.up); return true;
     case kStRadixScan: radix_digit_scan_body(uniform_copy(st.a.radix), b); return true;
     case kStRadixDown: radix_downsweep_body(uniform_copy(st.a.radix), b, U.down); return true;

@@ -1,20 +1,20 @@
 // Tile binning (Sec. 3.1, splats sorted by depth per tile).  The order produced is the
 // stable order of the keys (tile << 32 | bits(depth)) emitted per rendered (view, Gaussian)
-// in index order, i.e. (tile, depth, index); it is built in two sorts that move far fewer
-// bytes than one sort of the 64-bit pair keys:
+// in index order, i.e. (tile, depth, index).  It starts with a depth sort of the rendered records
+// (bin.hip); then
 //
-//   1. compaction of the rendered records f = v*n + i in index order, keyed by bits(depth);
-//   2. stable LSD radix sort of these R records by their 32-bit depth key;
-//   3. emission, in that depth order, of one (tile id, f) pair per covered tile (a
-//      load-balanced expansion over equal output chunks: every store is coalesced);
-//   4. stable LSD radix sort of the D pairs by the tile id only.
+//   row path (bin.hip)     a partition of (record, tile row) pairs by row and of their tiles by
+//                          column, for batches of at most 2048 tile rows of views of at most 256 x
+//                          256 tiles (4096 x 4096 pixels);
+//   general path (here)    emission, in depth order, of one (tile id, f) pair per covered tile (a
+//                          load-balanced expansion over equal output chunks: every store is
+//                          coalesced), and a stable LSD radix sort of the D pairs by the tile id.
 //
-// Step 4 is stable and its input is in (depth, index) order within every tile, so the result
-// is ordered by (tile, depth, index), exactly the order of the single 64-bit sort.  Rendered
-// records each cover at least one tile, so R <= D and the record sort runs inside the pair
-// buffers.  Everything is device-driven: R and D live in the workspace header and every kernel
-// reads them, so no host synchronisation is needed between the stages and the whole sequence
-// can be captured in a graph.
+// Both are stable and start in (depth, index) order, so the result is ordered by (tile, depth,
+// index), exactly the order of a single 64-bit sort.  Rendered records each cover at least one
+// tile, so R <= D and the record sort runs inside the pair buffers.  Everything is device-driven:
+// R and D live in the workspace header and every kernel reads them, so no host synchronisation
+// is needed between the stages and the whole sequence can be captured in a graph.
 #include "clod_internal.h"
 
 namespace clod {
@@ -51,130 +51,8 @@ __device__ __forceinline__ int owner_of(const uint32_t* loff, uint32_t o) {
   return lo;
 }
 
-// ------------------------------------------------------------ step 1: counts and compaction
-// The rendered records are the (view, Gaussian) pairs whose flag byte has bit 2 set (the
-// projection sets it exactly where it writes a tile rectangle).  Thread t of a block owns the
-// 16 records [base + 16t, base + 16t + 16) and reads their flags in one 16-byte load; the
-// result is a 16-bit mask, bit k = record base + 16t + k is rendered.
-__device__ __forceinline__ uint32_t rendered_mask(const uint8_t* __restrict__ flags, int64_t count, int64_t j0) {
-  uint32_t w[4] = {0u, 0u, 0u, 0u};
-  if (j0 + 16 <= count) {
-    const uint4 q = *reinterpret_cast<const uint4*>(flags + j0);
-    w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-  } else {
-    for (int k = 0; k < 16 && j0 + k < count; ++k) w[k >> 2] |= (uint32_t)flags[j0 + k] << (8 * (k & 3));
-  }
-  uint32_t m = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t b = (w[q] >> 2) & 0x01010101u;   // bit 2 of each byte, at bits 0, 8, 16, 24
-    m |= ((b | (b >> 7) | (b >> 14) | (b >> 21)) & 0xFu) << (4 * q);
-  }
-  return m;
-}
-
-// Single block: exclusive scan of the per-chunk rendered counts; R and the overflow flag (R
-// above the capacity) to the header.  D is not known yet: k_emit_partials stores it.  Also
-// clears the counters of the tile ordering (tord).
-__device__ __forceinline__ void scan_partials_body(const ScanPartialsArgs& a, Blk) {
-  __shared__ uint32_t sm[4];
-  uint32_t* __restrict__ partR = a.partR;
-  const int nparts = a.nparts;
-  unsigned long long* __restrict__ hdr = a.hdr;
-  const int64_t cap = a.cap;
-  uint32_t* __restrict__ tord = a.tord;
-  if (threadIdx.x < kTileOrderWords) tord[threadIdx.x] = 0u;
-  uint32_t carry = 0;
-  // kScanItems consecutive partials per thread per round (one block scan per round).
-  for (int base = 0; base < nparts; base += kScanChunk) {
-    const int j0 = base + (int)threadIdx.x * kScanItems;
-    uint32_t r[kScanItems];
-    uint32_t sr = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      r[k] = j0 + k < nparts ? partR[j0 + k] : 0u;
-      sr += r[k];
-    }
-    uint32_t tot;
-    uint32_t ex = block_exclusive_scan(sr, sm, tot);
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      if (j0 + k < nparts) partR[j0 + k] = carry + ex;
-      ex += r[k];
-    }
-    carry += tot;
-  }
-  if (threadIdx.x == 0) {
-    hdr[kHdrDup] = 0ull;
-    hdr[kHdrOverflow] = (int64_t)carry > cap ? 1ull : 0ull;
-    hdr[kHdrRend] = carry;
-  }
-}
-__global__ __launch_bounds__(kBlock) void k_scan_partials(ScanPartialsArgs a) { scan_partials_body(a, grid_blk()); }
-
-// Per chunk of kScanChunk records: the number of rendered records.  Also clears the per-tile
-// ranges (2 * tiles words) for k_ranges, which writes only the non-empty tiles.
-__device__ __forceinline__ void scan_reduce_body(const ScanReduceArgs& a, Blk b) {
-  __shared__ uint32_t sm[4];
-  for (int64_t q = (int64_t)b.id * kBlock + threadIdx.x; q < a.range_words; q += (int64_t)b.n * kBlock)
-    a.ranges[q] = 0u;
-  const int64_t j0 = (int64_t)b.id * kScanChunk + (int64_t)threadIdx.x * kScanItems;
-  const uint32_t r = wave_sum((uint32_t)__popc(rendered_mask(a.flags, a.count, j0)));
-  if (lane_id() == 0) sm[threadIdx.x >> 6] = r;
-  __syncthreads();
-  if (threadIdx.x == 0) a.partR[b.id] = sm[0] + sm[1] + sm[2] + sm[3];
-}
-__global__ __launch_bounds__(kBlock) void k_scan_reduce(ScanReduceArgs a) { scan_reduce_body(a, grid_blk()); }
-
-// Rendered records of the chunk, in index order, to [partR[b], ...): key bits(depth), value f.
-// The depth gathers (one per rendered record, from the record's fourth quad) are issued right
-// after the flag load, so their latency overlaps the block scan; keys and indices are then
-// placed in LDS so the stores are coalesced.
-struct CompactLds {
-  uint32_t sk[kScanChunk], sf[kScanChunk];
-};
-__device__ __forceinline__ void compact_body(const CompactArgs& a, Blk b, CompactLds& S) {
-  __shared__ uint32_t sm[4];
-  uint32_t* sk = S.sk;
-  uint32_t* sf = S.sf;
-  const uint8_t* __restrict__ flags = a.flags;
-  const int64_t count = a.count;
-  const float4* __restrict__ rec = a.rec;
-  uint32_t* __restrict__ kout = a.kout;
-  uint32_t* __restrict__ vout = a.vout;
-  if (a.hdr[kHdrOverflow] != 0ull) return;
-  const int t = threadIdx.x;
-  const int64_t base = (int64_t)b.id * kScanChunk;
-  const int64_t j0 = base + (int64_t)t * kScanItems;
-  const uint32_t m = rendered_mask(flags, count, j0);
-  uint32_t dk[kScanItems];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k)
-    dk[k] = ((m >> k) & 1u) ? __float_as_uint(rec[kRecQuads * (j0 + k) + 3].x) : 0u;   // camera depth
-  uint32_t total;
-  uint32_t o = block_exclusive_scan((uint32_t)__popc(m), sm, total);
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    if ((m >> k) & 1u) {
-      sk[o] = dk[k];
-      sf[o] = (uint32_t)(j0 + k);
-      ++o;
-    }
-  }
-  __syncthreads();
-  const int64_t out0 = (int64_t)a.partR[b.id];
-  for (uint32_t q = (uint32_t)t; q < total; q += kBlock) {
-    kout[out0 + q] = sk[q];
-    vout[out0 + q] = sf[q];
-  }
-}
-__global__ __launch_bounds__(kBlock) void k_compact(CompactArgs a) {
-  __shared__ CompactLds S;
-  compact_body(a, grid_blk(), S);
-}
-
 // ---------------------------------------------------------------------------- radix sort
-// Reduce-then-scan LSD radix sort of (uint32 key, uint32 value) pairs with 8-bit digits; the
+// (General path and scene order.)  Reduce-then-scan LSD radix sort of (uint32 key, uint32 value) pairs with 8-bit digits; the
 // element count is header word `cw`.  Block b of G owns the contiguous chunk
 // [b*C, (b+1)*C) (C a multiple of the 2048-key tile), so the stable order across blocks is the
 // block order.
@@ -391,7 +269,7 @@ static hipError_t radix_passes(const unsigned long long* hdr, int cw, int G, int
   return hipSuccess;
 }
 
-// ---------------------------------------------------------------- step 3: ordered emission
+// ------------------------------------------------------------------------- ordered emission
 // Tiles touched by record f (the last word of its fourth quad).
 __device__ __forceinline__ uint32_t rec_tiles(const float4* __restrict__ rec, uint32_t f) {
   return __float_as_uint(rec[kRecQuads * (int64_t)f + 3].w);
@@ -643,48 +521,139 @@ int tile_passes(uint32_t tiles_total) {
   return (tb + 7) / 8;
 }
 
-int sorted_buffer(uint32_t tiles_total) { return (tile_passes(tiles_total) & 1) ? 0 : 1; }
+// The row path ends in buffer 1; the tile-id passes of the general path start in buffer 0.
+int sorted_buffer(const Layout& L) { return L.row_path || (tile_passes(L.tiles_total) & 1) ? 1 : 0; }
 
-hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out) {
-  char* w = (char*)ws;
-  char* dp = (char*)dup;
-  unsigned long long* hdr = (unsigned long long*)(w + L.hdr);
-  uint32_t* const k[2] = {(uint32_t*)(dp + D.keys0), (uint32_t*)(dp + D.keys1)};
-  uint32_t* const v[2] = {(uint32_t*)(dp + D.vals0), (uint32_t*)(dp + D.vals1)};
-  uint32_t* hist = (uint32_t*)(dp + D.hist);
-  const int nb = L.scan_blocks;
-  uint32_t* ranges = (uint32_t*)(w + L.ranges);
-  uint32_t* tord = (uint32_t*)(w + L.tord);
-  if (nb == 0) {
-    hipError_t e = launch_fill_u32((uint32_t*)hdr, 0u, 2 * kHdrWords, out);
-    if (e == hipSuccess) e = launch_fill_u32(ranges, 0u, 2 * (int64_t)L.tiles_total, out);
-    if (e == hipSuccess) e = launch_fill_u32(tord, 0u, kTileOrderWords, out);
-    return e;
-  }
-  uint32_t* partR = (uint32_t*)(w + L.scan_part);
-  uint32_t* partE = partR + (nb + 1);
-  const uint8_t* flags = (const uint8_t*)(w + L.flags);
-  const float4* rec = (const float4*)(w + L.rec);
-  const int G = sort_blocks(D.cap);
+// Group sums of the radix passes (section sort_gsum), each cleared by a kernel before its pass.  The
+// compaction's group counts (sort_gcount) are cleared at the end of a projection and of a
+// binning, so that a binning finds them clear.
+static void depth_counters(const Layout& L, char* w, uint32_t* (&gsum)[4]) {
+  gsum[0] = (uint32_t*)(w + L.sort_gsum);
+  for (int k = 1; k < 4; ++k) gsum[k] = gsum[0] + kGroups * (kDepthBins0 + (uint32_t)(k - 1) * kRowBinsMax);
+}
+// Blocks that the records of a batch can need in a pass (their number is known on the device only).
+static uint32_t record_blocks(const Layout& L, const DupLayout& D) {
+  const int64_t most = L.VN < D.cap ? L.VN : D.cap, b = (most + 4 * kWaveMin - 1) / (4 * kWaveMin);
+  return b < (int64_t)kRadixBlocksMax ? (uint32_t)b : kRadixBlocksMax;
+}
+
+static hipError_t depth_sort(const Layout& L, char* w, const DupLayout& D, char* dp, const Sink& out) {
+  uint32_t* gsum[4];
+  depth_counters(L, w, gsum);
   Stage st{};
   st.block = kBlock;
+  DepthArgs& a = st.a.depth;
+  a.flags = (const uint8_t*)(w + L.flags);
+  a.VN = L.VN;
+  a.rec = (const float4*)(w + L.rec);
+  a.hdr = (unsigned long long*)(w + L.hdr);
+  a.hist = (uint32_t*)(w + L.sort_hist);
+  a.stat = (DepthStat*)(w + L.sort_stat);
+  a.chunks = (uint32_t)L.scan_blocks;
+  a.gcount = (uint32_t*)(w + L.sort_gcount);
+  a.groups = L.rec_groups;
+  a.part = (uint32_t*)(w + L.scan_part);
+  a.cap = D.cap;
+  a.tord = (uint32_t*)(w + L.tord);
+  a.tord_words = kTileOrderWords + kOrderCopies * kTileBuckets;
+  a.ranges = (uint32_t*)(w + L.ranges);
+  a.range_words = L.row_path ? 0 : 2 * (int64_t)L.tiles_total;
+  a.row_bins = L.row_path ? L.row_bins : 0u;
+  uint2* const buf[2] = {(uint2*)(dp + D.keys0), (uint2*)(dp + D.keys1)};
   hipError_t e = hipSuccess;
+  auto put = [&](int32_t kind, uint32_t items) {
+    st.kind = kind;
+    st.items = items;
+    if (e == hipSuccess) e = out.put(st);
+  };
+  a.gnext = gsum[0];
+  a.out = buf[0];
+  put(kStRecCount, (uint32_t)L.scan_blocks);
+  put(kStRecCompact, (uint32_t)L.scan_blocks);
+  a.kout = (uint32_t*)(dp + D.keys0);
+  a.vout = (uint32_t*)(dp + D.vals0);
+  for (int p = 0; p < 3; ++p) {
+    a.pass = p;
+    a.gsum = gsum[p];
+    a.gnext = p < 2 || L.row_path ? gsum[p + 1] : nullptr;
+    a.in = buf[p & 1];
+    a.out = buf[(p + 1) & 1];   // the third pass, from buffer 0, writes kout and vout instead
+    if (p == 2) { a.kout = (uint32_t*)(dp + D.keys1); a.vout = (uint32_t*)(dp + D.vals1); }
+    const uint32_t items = (record_blocks(L, D) + 7u) / 8u * 8u;   // chunks are spread over the eight XCDs
+    put(kStDepthUp, items);
+    put(kStDepthDown, items);
+  }
+  return e;
+}
+
+static hipError_t row_partition(const Layout& L, char* w, const DupLayout& D, char* dp, const Sink& out) {
+  uint32_t* gsum[4];
+  depth_counters(L, w, gsum);
+  RowTables tab;
+  tab.tile = (uint32_t*)(w + L.row_tab);
+  tab.start = tab.tile + L.rows + 1;
+  tab.ustart = tab.start + L.rows + 1;
+  tab.pairs = tab.ustart + L.rows + 1;
+  tab.urow = tab.pairs + L.rows;
+  hipError_t e = hipSuccess;
+  Stage st{};
+  st.block = kBlock;
   auto put = [&](int32_t kind, int64_t items) {
     st.kind = kind;
     st.items = (uint32_t)items;
     if (e == hipSuccess) e = out.put(st);
   };
-  // 1. R and its overflow; compaction of the rendered records into buffer 0.
-  st.a.scan_reduce = ScanReduceArgs{flags, L.VN, partR, ranges, 2 * (int64_t)L.tiles_total};
-  put(kStScanReduce, nb);
-  st.a.scan_partials = ScanPartialsArgs{partR, nb, hdr, D.cap, tord};
-  put(kStScanPartials, 1);
-  st.a.compact = CompactArgs{flags, L.VN, (const uint32_t*)partR, rec, (const unsigned long long*)hdr, k[0], v[0]};
-  put(kStCompact, nb);
-  // 2. depth sort of the R records: 4 passes, back in buffer 0.
-  if (e == hipSuccess) e = radix_passes(hdr, kHdrRend, G, 0, 4, k, v, 0, hist, out);
-  // 3. emission in depth order into buffer 1.
-  // The emission output buffer 1 holds the sorted tile counts until k_emit overwrites it.
+  unsigned long long* hdr = (unsigned long long*)(w + L.hdr);
+  uint2* rp = (uint2*)(dp + D.keys0);
+  uint32_t* hist = (uint32_t*)(w + L.sort_hist);
+  st.a.row = RowArgs{(const DevView*)(w + L.vinfo), L.V, L.rows, L.n, hdr, (const uint32_t*)(dp + D.keys1),
+                     (const uint32_t*)(dp + D.vals1), rp, hist, gsum[3], tab, L.row_bins, L.units_max, L.tiles_total,
+                     1.0f / (float)L.n};
+  st.lds = row_lds_words(L.row_bins) * 4u;
+  const int64_t rb = (record_blocks(L, D) + 7u) / 8u * 8u;
+  put(kStRowUp, rb);
+  put(kStRowDown, rb);
+  st.lds = 0;
+  uint32_t* tord = (uint32_t*)(w + L.tord);
+  st.a.col = ColArgs{hdr, rp, hist, tab, (uint32_t*)(w + L.tcount), (uint2*)(w + L.ranges), tord, tord + kTileOrderWords,
+                     (uint32_t*)(w + L.order), (uint32_t*)(dp + D.keys1), (uint32_t*)(dp + D.vals1),
+                     (uint32_t*)(w + L.sort_gcount), L.cols, L.tiles_total, L.rec_groups * kLineWords, 0};
+  int64_t units = D.cap / kUnit + L.rows + 1;
+  if (units > (int64_t)L.units_max) units = L.units_max;
+  put(kStColUp, units);
+  put(kStColScan, (int64_t)L.rows * (L.cols / 64u));
+  put(kStColDown, units + (L.tiles_total + kTileOrderChunk - 1) / kTileOrderChunk);
+  return e;
+}
+
+hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out) {
+  char* w = (char*)ws;
+  char* dp = (char*)dup;
+  unsigned long long* hdr = (unsigned long long*)(w + L.hdr);
+  if (L.VN == 0) {
+    hipError_t e = launch_fill_u32((uint32_t*)hdr, 0u, 2 * kHdrWords, out);
+    if (e == hipSuccess) e = launch_fill_u32((uint32_t*)(w + L.ranges), 0u, 2 * (int64_t)L.tiles_total, out);
+    if (e == hipSuccess) e = launch_fill_u32((uint32_t*)(w + L.tord), 0u, kTileOrderWords, out);
+    return e == hipSuccess ? launch_ranges(L, ws, D, dup, out) : e;
+  }
+  hipError_t e = depth_sort(L, w, D, dp, out);
+  if (e != hipSuccess) return e;
+  if (L.row_path) return row_partition(L, w, D, dp, out);
+  // The depth sort left the records in buffer 1 (k[0], v[0]); the pairs start in buffer 0.
+  uint32_t* const k[2] = {(uint32_t*)(dp + D.keys1), (uint32_t*)(dp + D.keys0)};
+  uint32_t* const v[2] = {(uint32_t*)(dp + D.vals1), (uint32_t*)(dp + D.vals0)};
+  const int nb = L.scan_blocks;
+  uint32_t* partE = (uint32_t*)(w + L.scan_part);
+  const uint8_t* flags = (const uint8_t*)(w + L.flags);
+  const float4* rec = (const float4*)(w + L.rec);
+  Stage st{};
+  st.block = kBlock;
+  auto put = [&](int32_t kind, int64_t items) {
+    st.kind = kind;
+    st.items = (uint32_t)items;
+    if (e == hipSuccess) e = out.put(st);
+  };
+  // Emission in depth order into buffer 0, which holds the sorted tile counts until then.
   st.a.emit_reduce = EmitReduceArgs{(const uint32_t*)v[0], rec, flags, L.VN, (const unsigned long long*)hdr, partE, k[1]};
   put(kStEmitReduce, nb);
   st.a.emit_partials = EmitPartialsArgs{partE, hdr, nb, D.cap};
@@ -699,9 +668,11 @@ hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* 
   st.a.emit = EmitArgs{(const uint32_t*)v[0], (const uint32_t*)k[0], (const uint32_t*)owner, rec,
                        (const DevView*)(w + L.vinfo), L.n, (const unsigned long long*)hdr, k[1], v[1]};
   put(kStEmit, ge);
-  // 4. stable sort of the D pairs by tile id.
-  if (e == hipSuccess) e = radix_passes(hdr, kHdrDup, G, 0, tile_passes(L.tiles_total), k, v, 1, hist, out);
-  return e;
+  // Stable sort of the D pairs by tile id.
+  if (e == hipSuccess)
+    e = radix_passes(hdr, kHdrDup, sort_blocks(D.cap), 0, tile_passes(L.tiles_total), k, v, 1,
+                     (uint32_t*)(dp + D.hist), out);
+  return e == hipSuccess ? launch_ranges(L, ws, D, dup, out) : e;
 }
 
 // ---------------------------------------------------------------------------- ranges
@@ -770,6 +741,7 @@ __device__ __forceinline__ void tile_scatter_body(const TileOrderArgs& a, Blk bl
   const uint32_t tiles = a.tiles;
   uint32_t* __restrict__ tord = a.tord;
   uint32_t* __restrict__ order = a.order;
+  zero_words(a.clear, a.clear_words, blk);
   if (threadIdx.x < kTileBuckets) cnt[threadIdx.x] = 0;
   __syncthreads();
   const bool ovf = a.hdr[kHdrOverflow] != 0ull;
@@ -796,11 +768,11 @@ __device__ __forceinline__ void tile_scatter_body(const TileOrderArgs& a, Blk bl
 
 __global__ __launch_bounds__(kBlock) void k_tile_scatter(TileOrderArgs a) { tile_scatter_body(a, grid_blk()); }
 
-hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, int parity, const Sink& out) {
+hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out) {
   char* w = (char*)ws;
   char* dp = (char*)dup;
-  // The ranges and the ordering counters were cleared by launch_bin_sort.
-  const uint32_t* keys = (const uint32_t*)(dp + (parity ? D.keys1 : D.keys0));
+  // The ranges and the ordering counters were cleared by the depth sort.
+  const uint32_t* keys = (const uint32_t*)(dp + (sorted_buffer(L) ? D.keys1 : D.keys0));
   const unsigned long long* hdr = (const unsigned long long*)(w + L.hdr);
   int64_t g = (D.cap + 4 * kBlock - 1) / (4 * kBlock);
   if (g > 8192) g = 8192;
@@ -814,7 +786,7 @@ hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* du
   if (e == hipSuccess && L.tiles_total > 0) {
     st.items = (L.tiles_total + kTileOrderChunk - 1) / kTileOrderChunk;
     st.a.tile_order = TileOrderArgs{(const uint2*)(w + L.ranges), L.tiles_total, hdr, (uint32_t*)(w + L.tord),
-                                    (uint32_t*)(w + L.order)};
+                                    (uint32_t*)(w + L.order), (uint32_t*)(w + L.sort_gcount), L.rec_groups * kLineWords, 0};
     st.kind = kStTileCount;
     e = out.put(st);
     st.kind = kStTileScatter;
@@ -826,9 +798,6 @@ hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* du
 hipError_t launch_sort_stage(const Stage& st, hipStream_t s) {
   const dim3 g(st.items), blk(st.block);
   switch (st.kind) {
-    case kStScanReduce: hipLaunchKernelGGL(k_scan_reduce, g, blk, 0, s, st.a.scan_reduce); break;
-    case kStScanPartials: hipLaunchKernelGGL(k_scan_partials, g, blk, 0, s, st.a.scan_partials); break;
-    case kStCompact: hipLaunchKernelGGL(k_compact, g, blk, 0, s, st.a.compact); break;
     case kStRadixUp: hipLaunchKernelGGL(k_radix_upsweep, g, blk, 0, s, st.a.radix); break;
     case kStRadixScan: hipLaunchKernelGGL(k_radix_digit_scan, g, blk, 0, s, st.a.radix); break;
     case kStRadixDown: hipLaunchKernelGGL(k_radix_downsweep, g, blk, 0, s, st.a.radix); break;
