@@ -135,8 +135,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 8);
   L.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
   L.gpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
-  L.sel_state = o; o = align256(o + (size_t)V * sizeof(SelState));
-  L.sel_hist = o; o = align256(o + (L.any_budget ? (size_t)V * kSelBlocks * 256 * 4 : 0));
+  L.sel_hist = o; o = align256(o + (L.any_budget ? (size_t)V * kSelBytes : 0));
   L.lcount = o; o = align256(o + (size_t)kMaxProjBlocks * 4);   // work-list segment counts
   L.list = o; o = align256(o + (size_t)n * 4);                        // work list of the projection
   L.flags = o; o = align256(o + (size_t)L.VN);
@@ -245,7 +244,7 @@ static clod_status check_scene(const clod_scene* s) {
 
 // Count-only workspace: the sections the LoD counting kernels use, nothing per tile or pixel.
 struct CountLayout {
-  size_t vinfo, dmax_key, counts, kpart, cpart, sel_state, sel_hist, lcount, list, total;
+  size_t vinfo, dmax_key, counts, kpart, cpart, sel_hist, lcount, list, total;
 };
 
 static CountLayout count_layout(int64_t n, int32_t V, bool any_budget) {
@@ -256,8 +255,7 @@ static CountLayout count_layout(int64_t n, int32_t V, bool any_budget) {
   C.counts = o; o = align256(o + (size_t)V * 3 * 8);
   C.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 8);
   C.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
-  C.sel_state = o; o = align256(o + (size_t)V * sizeof(SelState));
-  C.sel_hist = o; o = align256(o + (any_budget ? (size_t)V * kSelBlocks * 256 * 4 : 0));
+  C.sel_hist = o; o = align256(o + (any_budget ? (size_t)V * kSelBytes : 0));
   C.lcount = o; o = align256(o + (size_t)kMaxProjBlocks * 4);
   C.list = o; o = align256(o + (size_t)n * 4);
   C.total = o;
@@ -308,10 +306,10 @@ static hipError_t project_stages(const clod_scene& sc, const clod_view* views_de
   unsigned long long* dmax_key = (unsigned long long*)(w + L.dmax_key);
   hipError_t e = launch_view_setup(views_dev, L.V, prm, vinfo, (unsigned long long*)(w + L.hdr), out);
   if (e == hipSuccess)
-    e = launch_frustum_max(sc, vinfo, L.V, prm.near_z, (unsigned long long*)(w + L.kpart), dmax_key, out);
+    e = launch_frustum_max(sc, vinfo, L.V, prm.near_z, (unsigned long long*)(w + L.kpart), dmax_key,
+                           (uint32_t*)(w + L.sel_hist), L.any_budget ? kSelWords * (uint32_t)L.V : 0u, out);
   if (e == hipSuccess && L.any_budget)
-    e = launch_lod_select(sc, vinfo, L.V, prm, dmax_key, (SelState*)(w + L.sel_state), (uint32_t*)(w + L.sel_hist),
-                          out);
+    e = launch_lod_select(sc, vinfo, L.V, prm, dmax_key, (uint32_t*)(w + L.sel_hist), (float*)(w + L.alpha), out);
   if (e == hipSuccess)
     e = launch_project(sc, vinfo, L.V, prm, dmax_key, (uint32_t*)(w + L.cpart), (unsigned long long*)(w + L.counts),
                        counts_dev, eta_dev, (uint8_t*)(w + L.flags), (float*)(w + L.alpha), (float4*)(w + L.rec),
@@ -467,11 +465,12 @@ clod_status clod_lod_count(const clod_scene* scene, const clod_batch* batch, int
   DevView* vinfo = (DevView*)(w + L.vinfo);
   HIP_TRY(launch_view_setup(batch->views_dev, L.V, batch->params, vinfo, nullptr, s), "view setup");
   HIP_TRY(launch_frustum_max(*scene, vinfo, L.V, batch->params.near_z, (unsigned long long*)(w + L.kpart),
-                             (unsigned long long*)(w + L.dmax_key), s),
+                             (unsigned long long*)(w + L.dmax_key), (uint32_t*)(w + L.sel_hist),
+                             L.any_budget ? kSelWords * (uint32_t)L.V : 0u, s),
           "frustum max");
   if (L.any_budget)
     HIP_TRY(launch_lod_select(*scene, vinfo, L.V, batch->params, (const unsigned long long*)(w + L.dmax_key),
-                              (SelState*)(w + L.sel_state), (uint32_t*)(w + L.sel_hist), s),
+                              (uint32_t*)(w + L.sel_hist), nullptr, s),
             "budget select");
   HIP_TRY(launch_lod_count(*scene, vinfo, L.V, batch->params, (unsigned long long*)(w + L.dmax_key),
                            (uint32_t*)(w + L.cpart), (unsigned long long*)(w + L.counts), counts_dev, nullptr,
@@ -511,11 +510,12 @@ clod_status clod_lod_count_noalloc(const clod_scene* scene, int32_t n_views, con
   DevView* vinfo = (DevView*)(w + Cl.vinfo);
   HIP_TRY(launch_view_setup(views_dev, n_views, *params, vinfo, nullptr, s), "view setup");
   HIP_TRY(launch_frustum_max(*scene, vinfo, n_views, params->near_z, (unsigned long long*)(w + Cl.kpart),
-                             (unsigned long long*)(w + Cl.dmax_key), s),
+                             (unsigned long long*)(w + Cl.dmax_key), (uint32_t*)(w + Cl.sel_hist),
+                             any_budget ? kSelWords * (uint32_t)n_views : 0u, s),
           "frustum max");
   if (any_budget)
     HIP_TRY(launch_lod_select(*scene, vinfo, n_views, *params, (const unsigned long long*)(w + Cl.dmax_key),
-                              (SelState*)(w + Cl.sel_state), (uint32_t*)(w + Cl.sel_hist), s),
+                              (uint32_t*)(w + Cl.sel_hist), nullptr, s),
             "budget select");
   HIP_TRY(launch_lod_count(*scene, vinfo, n_views, *params, (unsigned long long*)(w + Cl.dmax_key),
                            (uint32_t*)(w + Cl.cpart), (unsigned long long*)(w + Cl.counts), counts_dev, nullptr,

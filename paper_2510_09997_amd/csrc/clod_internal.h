@@ -66,12 +66,13 @@ struct DevView {
   unsigned long long mkey;       // K > 0: smallest kept selection key (set by the radix select)
 };
 
-// Radix select of the budgeted mask: per view, the threshold prefix found so far and the rank
-// (1-based, from the largest key) still to find among keys that share it.
-struct SelState {
-  unsigned long long prefix, rank;
-};
-constexpr int kSelBlocks = 128;   // blocks per view of the select histograms
+// Radix select of the budgeted mask: bins per level, chunks of a view, and per view three levels of
+// bins and the chunk counts (the workspace keeps kSelBytes for them).
+constexpr uint32_t kSelBins = 2048;
+constexpr int kSelBlocks = 512;
+constexpr uint32_t kSelWords = 3 * kSelBins + kSelBlocks;
+constexpr size_t kSelBytes = 128 * 256 * 4;
+static_assert(kSelWords * 4 <= kSelBytes, "select bins");
 
 // Workspace header words (uint64): pairs, overflow flag, rendered records; of the depth sort the
 // subtrahend of the keys and their bit length; row pairs per column unit and column units.
@@ -107,7 +108,7 @@ struct Layout {
   uint32_t rows = 0, row_bins = 0, cols = 0, units_max = 0;
   uint32_t rec_groups = 0;    // groups of the compaction's chunks (scan_blocks of them)
   // byte offsets into ws
-  size_t hdr, vinfo, dmax_key, counts, gdmax, loss_acc, kpart, cpart, gpart, ssim_acc, loss_part, sel_state, sel_hist, lcount, list, flags, alpha, rec,
+  size_t hdr, vinfo, dmax_key, counts, gdmax, loss_acc, kpart, cpart, gpart, ssim_acc, loss_part, sel_hist, lcount, list, flags, alpha, rec,
       scan_part, ranges, order, tord, pair_part, sort_hist, sort_stat, sort_gcount, sort_gsum, row_tab, tcount, gscreen, total;
 };
 
@@ -545,8 +546,8 @@ struct ProjectArgs {
   int32_t write, packed;   // records written; colours from the packed coefficients
 };
 struct SelectArgs {
-  clod_scene sc; DevView* views; int32_t V; clod_params prm; const unsigned long long* dmax_key;
-  SelState* state; uint32_t* hist; int32_t pass;
+  clod_scene sc; const DevView* views; DevView* views_out; int32_t V; clod_params prm;
+  const unsigned long long* dmax_key; uint32_t* hist; float* alpha /* or none */; int32_t level, pad;
 };
 struct DepthArgs {   // the passes of the depth sort share it
   const uint8_t* flags; int64_t VN; const float4* rec; unsigned long long* hdr; uint32_t* hist; uint32_t* gsum;
@@ -678,7 +679,8 @@ hipError_t launch_view_setup(const clod_view* views_dev, int V, clod_params prm,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, const Sink& out);
 int proj_blocks(int64_t n);
 hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V, float near_z,
-                              unsigned long long* kpart, unsigned long long* dmax_key, const Sink& out);
+                              unsigned long long* kpart, unsigned long long* dmax_key,
+                              uint32_t* clear, uint32_t clear_words, const Sink& out);
 // counts (workspace) and counts_dev (caller's int64 [V][3], nullable) receive the per-view
 // {frustum, mask, rendered} counts.
 hipError_t launch_project(const clod_scene& sc, const DevView* vinfo, int V, clod_params prm,
@@ -707,7 +709,7 @@ struct AdamSegs {
 };
 hipError_t launch_adam(const AdamSegs& segs, float b1, float b2, float eps, float bc1, float bc2, hipStream_t s);
 hipError_t launch_lod_select(const clod_scene& sc, DevView* vinfo, int V, clod_params prm,
-                             const unsigned long long* dmax_key, SelState* state, uint32_t* hist, const Sink& out);
+                             const unsigned long long* dmax_key, uint32_t* hist, float* alpha, const Sink& out);
 
 hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out);
 hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out);

@@ -569,105 +569,180 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   project_body<DEG, true, true>(a, grid_blk(), sdyn);
 }
 
-// Budgeted LoD (a view with budget K, 0 < K < n): the K-th largest selection key, by an MSD
-// radix select over the eight bytes of the 64-bit key.  Pass p histograms byte p (from the top)
-// of the keys that share the prefix found so far (k_select_hist, one histogram per block and
-// view; alpha'' is recomputed from the scene exactly as the projection computes it), then
-// k_select_pick finds the byte value holding the wanted rank and narrows the prefix.  After
-// eight passes the prefix is the threshold key.  K >= n keeps everything (threshold 0).
+// Budgeted LoD (a view with budget K, 0 < K < n): the K-th largest selection key.  alpha'' (as
+// bits) is found by an MSD radix select in three levels of 11, 11 and 10 bits; among equal
+// alpha'' the lowest indices are kept, so the last stage finds the index at the remaining rank.
+//   k_select_hist   levels 0 to 2: counts of the level's digit over the keys that share the digits
+//                   found so far (LDS counts, added to the view's bins)
+//   k_select_hist   level 3: keys equal to the threshold per chunk of the view's Gaussians
+//   k_select_pick   the chunk and then the index at the rank; the threshold key to the view
+// Every block finds the digits of the levels before its own itself from the view's bins, so no
+// launch sits between the levels.  Level 0 computes alpha'' exactly as the projection does and,
+// where there is a plane for it (not in the counting entry points), stores it for the other
+// levels to read instead of computing it again.  Five launches; the eight 8-bit levels over the
+// whole 64-bit key that these replaced took sixteen and computed alpha'' eight times (3M
+// Gaussians in four viewports: 540 us, now 134 us).  K >= n keeps everything (threshold 0).
+__device__ __forceinline__ int64_t select_chunk(int64_t n) {   // Gaussians per chunk
+  const int64_t c = (n + kSelBlocks - 1) / kSelBlocks;
+  return (c + kBlock - 1) / kBlock * kBlock;
+}
+// The digits of the first `levels` levels (as the leading bits of a key) and the rank, from the
+// largest, among the keys that share them.
+__device__ __forceinline__ void select_derive(const uint32_t* __restrict__ hist, int levels, int64_t budget,
+                                              uint32_t& prefix, uint32_t& rank, uint32_t* sm) {
+  __shared__ uint32_t found[2];
+  constexpr int kPer = kSelBins / kBlock;
+  prefix = 0u;
+  rank = (uint32_t)budget;   // 0 < budget < n < 2^32
+  for (int l = 0; l < levels; ++l) {
+    // Thread t takes the digits kSelBins - 1 - (8 t + k), so a scan over them counts from the top.
+    const uint32_t* h = hist + l * kSelBins + (kSelBins - kPer * (1 + (int)threadIdx.x));
+    uint32_t c[kPer], s = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) { c[k] = h[kPer - 1 - k]; s += c[k]; }
+    uint32_t total;
+    uint32_t ex = block_exclusive_scan(s, sm, total);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (ex < rank && rank <= ex + c[k]) {
+        found[0] = kSelBins - 1u - (kPer * threadIdx.x + (uint32_t)k);
+        found[1] = rank - ex;
+      }
+      ex += c[k];
+    }
+    __syncthreads();
+    prefix = (prefix << (l < 2 ? 11 : 10)) | found[0];
+    rank = found[1];
+    __syncthreads();
+  }
+}
+__device__ __forceinline__ uint32_t select_bits(const SelectArgs& a, const DevView& Vw, float dmax, int64_t v, int64_t i) {
+  const int64_t n = a.sc.n;
+  if (a.alpha && a.level > 0) return __float_as_uint(a.alpha[v * n + i]);
+  float ex, ey, ez;
+  const float d = cam_distance(Vw, a.sc.mean[i], a.sc.mean[n + i], a.sc.mean[2 * n + i], ex, ey, ez);
+  float alpha, q;
+  return __float_as_uint(attenuated(d, dmax, Vw.s_v, a.sc.decay[i], a.sc.opacity[i], a.prm.eps, alpha, q));
+}
+
+struct SelectLds {
+  uint32_t h[kSelBins];
+};
 // Block b of V * kSelBlocks: chunk b % kSelBlocks of view b / kSelBlocks.
-__device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b) {
-  __shared__ uint32_t h[256];
-  const clod_scene& sc = a.sc;
-  const DevView* __restrict__ views = a.views;
-  const clod_params& prm = a.prm;
-  const unsigned long long* __restrict__ dmax_key = a.dmax_key;
-  const SelState* __restrict__ state = a.state;
-  const int pass = a.pass;
-  uint32_t* __restrict__ hist = a.hist;   // [V][kSelBlocks][256]
+__device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b, SelectLds& S) {
+  __shared__ uint32_t sm[4];
   const int v = (int)(b.id / kSelBlocks);
   const uint32_t chunk = b.id % kSelBlocks;
-  const DevView& Vw = views[v];
-  const int64_t n = sc.n;
-  if (Vw.budget <= 0 || Vw.budget >= n) return;
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int shift = 56 - 8 * pass;
-  const unsigned long long pre = pass == 0 ? 0ull : state[v].prefix >> (shift + 8);
-  const float dmax = dmax_from_key(dmax_key[v]);
-  int64_t lo, hi;
-  block_chunk(n, Blk{chunk, (uint32_t)kSelBlocks}, lo, hi);
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kBlock) {
-    float ex, ey, ez;
-    const float d = cam_distance(Vw, sc.mean[i], sc.mean[n + i], sc.mean[2 * n + i], ex, ey, ez);
-    float alpha, q;
-    const float a2 = attenuated(d, dmax, Vw.s_v, sc.decay[i], sc.opacity[i], prm.eps, alpha, q);
-    const unsigned long long key = lod_key(a2, i);
-    if (pass == 0 || (key >> (shift + 8)) == pre) atomicAdd(&h[(uint32_t)(key >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  hist[((int64_t)v * kSelBlocks + chunk) * 256 + threadIdx.x] = h[threadIdx.x];
-}
-__global__ __launch_bounds__(kBlock) void k_select_hist(SelectArgs a) { select_hist_body(a, grid_blk()); }
-
-__device__ __forceinline__ void select_pick_body(const SelectArgs& a, Blk b) {
-  __shared__ uint32_t sm[4];
-  DevView* __restrict__ views = a.views;
+  const DevView& Vw = a.views[v];
   const int64_t n = a.sc.n;
-  const int pass = a.pass;
-  SelState* __restrict__ state = a.state;
-  const uint32_t* __restrict__ hist = a.hist;
-  const int v = (int)b.id;
-  DevView& Vw = views[v];
-  if (Vw.budget <= 0) return;
-  if (Vw.budget >= n) {
-    if (threadIdx.x == 0) Vw.mkey = 0ull;
+  if (Vw.budget <= 0 || Vw.budget >= n) return;
+  const int64_t per = select_chunk(n), lo = chunk * per, hi = lo + per < n ? lo + per : n;
+  if (lo >= n) return;
+  uint32_t* __restrict__ hist = a.hist + (size_t)v * kSelWords;
+  for (uint32_t j = threadIdx.x; j < kSelBins; j += kBlock) S.h[j] = 0u;
+  __syncthreads();
+  uint32_t prefix, rank;
+  select_derive(hist, a.level, Vw.budget, prefix, rank, sm);
+  const int shift = a.level == 0 ? 21 : a.level == 1 ? 10 : 0;
+  const uint32_t mask = a.level == 3 ? 0u : a.level == 2 ? 1023u : 2047u;
+  const float dmax = dmax_from_key(a.dmax_key[v]);
+  uint32_t zeros = 0;   // keys of digit 0 (of level 0 half the scene may be: alpha'' flushed to 0)
+  constexpr int kItems = 4;   // Gaussians per thread and round, read before any is used
+  for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kItems * kBlock) {
+    uint32_t k[kItems];
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const int64_t i = i0 + j * kBlock;
+      k[j] = select_bits(a, Vw, dmax, v, i < hi ? i : hi - 1);
+    }
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const int64_t i = i0 + j * kBlock;
+      if (i >= hi) break;
+      if (a.level == 0 && a.alpha) a.alpha[v * n + i] = __uint_as_float(k[j]);
+      const bool in = a.level == 0 || (a.level == 3 ? k[j] == prefix : (k[j] >> (a.level == 1 ? 21 : 10)) == prefix);
+      const uint32_t d = (k[j] >> shift) & mask;
+      if (in && d != 0u) atomicAdd(&S.h[d], 1u);
+      zeros += in && d == 0u ? 1u : 0u;
+    }
+  }
+  zeros = wave_sum(zeros);
+  if (lane_id() == 0 && zeros) atomicAdd(&S.h[0], zeros);
+  __syncthreads();
+  if (a.level == 3) {
+    if (threadIdx.x == 0) hist[3 * kSelBins + chunk] = S.h[0];
     return;
   }
-  const unsigned long long rank = pass == 0 ? (unsigned long long)Vw.budget : state[v].rank;
-  const unsigned long long prefix = pass == 0 ? 0ull : state[v].prefix;
-  // Thread t takes byte value d = 255 - t, so an inclusive scan over t counts the keys whose
-  // byte is >= d.
-  const uint32_t d = 255u - threadIdx.x;
-  uint32_t c = 0;
-  for (int b = 0; b < kSelBlocks; ++b) c += hist[((int64_t)v * kSelBlocks + b) * 256 + d];
-  uint32_t inc = c;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t up = __shfl_up(inc, o, 64);
-    if (lane_id() >= (uint32_t)o) inc += up;
+  for (uint32_t j = threadIdx.x; j < kSelBins; j += kBlock)
+    if (S.h[j]) atomicAdd(&hist[a.level * kSelBins + j], S.h[j]);
+}
+__global__ __launch_bounds__(kBlock) void k_select_hist(SelectArgs a) {
+  __shared__ SelectLds S;
+  select_hist_body(a, grid_blk(), S);
+}
+
+// Block v: the index of view v's last kept Gaussian among those at the threshold.
+__device__ __forceinline__ void select_pick_body(const SelectArgs& a, Blk b) {
+  __shared__ uint32_t sm[4];
+  __shared__ uint32_t found[2];
+  const int v = (int)b.id;
+  const DevView& Vw = a.views[v];
+  const int64_t n = a.sc.n;
+  if (Vw.budget <= 0) return;
+  if (Vw.budget >= n) {
+    if (threadIdx.x == 0) a.views_out[v].mkey = 0ull;
+    return;
   }
-  if (lane_id() == 63) sm[threadIdx.x >> 6] = inc;
+  uint32_t* hist = a.hist + (size_t)v * kSelWords;
+  uint32_t prefix, rank;
+  select_derive(hist, 3, Vw.budget, prefix, rank, sm);
+  // The chunk that holds the rank-th equal key (lowest index first).
+  const int64_t per = select_chunk(n);
+  const uint32_t chunks = (uint32_t)((n + per - 1) / per);
+  static_assert(kSelBlocks <= 4 * kBlock, "four chunks per thread");
+  uint32_t c[4], s = 0, total;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t q = 4 * threadIdx.x + k;
+    c[k] = q < chunks ? hist[3 * kSelBins + q] : 0u;
+    s += c[k];
+  }
+  uint32_t ex = block_exclusive_scan(s, sm, total);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (ex < rank && rank <= ex + c[k]) { found[0] = 4 * threadIdx.x + k; found[1] = rank - ex; }
+    ex += c[k];
+  }
   __syncthreads();
-  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) inc += sm[w];
-  const uint32_t excl = inc - c;
-  if (excl < rank && rank <= inc) {
-    const int shift = 56 - 8 * pass;
-    const unsigned long long np = prefix | ((unsigned long long)d << shift);
-    state[v].prefix = np;
-    state[v].rank = rank - excl;
-    if (pass == 7) Vw.mkey = np;
+  const uint32_t chunk = found[0];
+  rank = found[1];
+  const float dmax = dmax_from_key(a.dmax_key[v]);
+  const int64_t lo = chunk * per, hi = lo + per < n ? lo + per : n;
+  for (int64_t i0 = lo; i0 < hi; i0 += kBlock) {
+    const int64_t i = i0 + threadIdx.x;
+    const bool eq = i < hi && select_bits(a, Vw, dmax, v, i) == prefix;
+    const uint32_t before = block_exclusive_scan(eq ? 1u : 0u, sm, total);
+    if (eq && before + 1u == rank) a.views_out[v].mkey = ((unsigned long long)prefix << 32) | (0xFFFFFFFFu - (uint32_t)i);
+    if (rank <= total) break;
+    rank -= total;
   }
 }
 __global__ __launch_bounds__(kBlock) void k_select_pick(SelectArgs a) { select_pick_body(a, grid_blk()); }
 
+// The bins start clear (the frustum maximum's fold clears them).
 hipError_t launch_lod_select(const clod_scene& sc, DevView* vinfo, int V, clod_params prm,
-                             const unsigned long long* dmax_key, SelState* state, uint32_t* hist, const Sink& out) {
+                             const unsigned long long* dmax_key, uint32_t* hist, float* alpha, const Sink& out) {
   if (sc.n == 0) return hipSuccess;
-  for (int pass = 0; pass < 8; ++pass) {
-    Stage h{};
-    h.kind = kStSelectHist;
-    h.items = (uint32_t)(kSelBlocks * V);
-    h.block = kBlock;
-    h.a.select = SelectArgs{sc, vinfo, V, prm, dmax_key, state, hist, pass};
-    Stage p = h;
-    p.kind = kStSelectPick;
-    p.items = (uint32_t)V;
-    hipError_t e = out.put(h);
-    if (e == hipSuccess) e = out.put(p);
-    if (e != hipSuccess) return e;
+  Stage h{};
+  h.block = kBlock;
+  hipError_t e = hipSuccess;
+  for (int level = 0; level < 5 && e == hipSuccess; ++level) {
+    h.kind = level < 4 ? kStSelectHist : kStSelectPick;
+    h.items = (uint32_t)(level < 4 ? kSelBlocks * V : V);
+    h.a.select = SelectArgs{sc, vinfo, vinfo, V, prm, dmax_key, hist, alpha, level, 0};
+    e = out.put(h);
   }
-  return hipSuccess;
+  return e;
 }
 
 int proj_blocks(int64_t n) {
@@ -711,7 +786,8 @@ static Stage fold_stage(const unsigned long long* kpart, const uint32_t* cpart, 
 }
 
 hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V, float near_z,
-                              unsigned long long* kpart, unsigned long long* dmax_key, const Sink& out) {
+                              unsigned long long* kpart, unsigned long long* dmax_key, uint32_t* clear,
+                              uint32_t clear_words, const Sink& out) {
   if (sc.n == 0) return launch_fill_u32((uint32_t*)dmax_key, 0u, 2 * (int64_t)V, out);
   const int G = proj_blocks(sc.n);
   Stage st{};
@@ -721,7 +797,7 @@ hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V,
   st.a.frustum = FrustumArgs{sc.mean, sc.n, vinfo, V, near_z, kpart};
   hipError_t e = out.put(st);
   if (e == hipSuccess)
-    e = out.put(fold_stage(kpart, nullptr, G, V, dmax_key, nullptr, nullptr, sc.n, nullptr, nullptr, 0));
+    e = out.put(fold_stage(kpart, nullptr, G, V, dmax_key, nullptr, nullptr, sc.n, nullptr, clear, clear_words));
   return e;
 }
 

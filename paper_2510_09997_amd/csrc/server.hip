@@ -222,6 +222,7 @@ __device__ void srv_dispatch(SrvDev* D, SrvHost* H, uint64_t deadline) {
 union SrvLds {
   TileLds tile;
   RecLds rec;
+  SelectLds select;
   RadixLds radix;
   uint32_t row[row_lds_words(kRowBinsMax)];
   ColLds col;
@@ -269,7 +270,7 @@ __device__ bool srv_run(int32_t kind, const Stage& st, Blk b, SrvLds& U) {
       }
       return true;
     }
-    case kStSelectHist: select_hist_body(uniform_copy(st.a.select), b); return true;
+    case kStSelectHist: select_hist_body(uniform_copy(st.a.select), b, U.select); return true;
     case kStSelectPick: select_pick_body(uniform_copy(st.a.select), b); return true;
     case kStRecCount: rec_count_body(uniform_copy(st.a.depth), b); return true;
     case kStRecCompact: rec_compact_body(uniform_copy(st.a.depth), b, U.rec); return true;

@@ -78,3 +78,24 @@ def test_budget_counts_sixty_four_views_match_oracle_and_nest():
     for j in range(0, len(views), 7):
         vp = O.view_pass(sc, views[j])
         assert np.array_equal(cnt[j], vp["counts"]), (j, cnt[j], vp["counts"])
+
+
+@pytest.mark.parametrize("n", [700, 131073, 400_003])
+def test_budget_select_at_its_edges(n):
+    """The selection against a full sort on the host, over budgets from one Gaussian to all but one:
+    below and inside the block of equal alpha'' (half of the scene has sigma_d <= 0, so alpha'' = 0),
+    in chunks of one and of several rounds, counted with a workspace and rendered."""
+    log(f"case: budget select edges {n}")
+    import torch
+    from paper_2510_09997_amd import _clod as C
+    scene = Scene(synth.make_scene(n, 0, "mixture", seed=33))
+    view = synth.look_at((1.0, 2.0, -9.0), width=64, height=48, s_v=3.0)
+    for k in (1, 2, n // 100, n // 3, n // 2 + n // 8, n - 1):
+        b = Batch(n, [with_budget(view, k), view])
+        b.project(scene)
+        a2 = b.section(C.SEC_ALPHA)[:n].cpu().numpy()
+        kept = np.zeros(n, bool)
+        kept[np.lexsort((np.arange(n), -a2.astype(np.float64)))[:k]] = True
+        flags = b.section(C.SEC_FLAGS)[:n].cpu().numpy()
+        assert np.array_equal((flags & 2) != 0, kept), k
+        assert torch.equal(b.lod_count(scene), b.counts)
