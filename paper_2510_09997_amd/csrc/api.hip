@@ -132,7 +132,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.loss_acc = o; o = align256(o + (size_t)V * 4);
   L.ssim_acc = o; o = align256(o + (size_t)V * 4);
   L.loss_part = o; o = align256(o + ((size_t)tiles_total * 3 + (size_t)pixels_total * 3 / kLossChunk + V) * 4);
-  L.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 8);
+  L.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
   L.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
   L.gpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
   L.sel_hist = o; o = align256(o + (L.any_budget ? (size_t)V * kSelBytes : 0));
@@ -253,7 +253,7 @@ static CountLayout count_layout(int64_t n, int32_t V, bool any_budget) {
   C.vinfo = o; o = align256(o + (size_t)V * sizeof(DevView));
   C.dmax_key = o; o = align256(o + (size_t)V * 8);
   C.counts = o; o = align256(o + (size_t)V * 3 * 8);
-  C.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 8);
+  C.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
   C.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
   C.sel_hist = o; o = align256(o + (any_budget ? (size_t)V * kSelBytes : 0));
   C.lcount = o; o = align256(o + (size_t)kMaxProjBlocks * 4);
@@ -306,7 +306,7 @@ static hipError_t project_stages(const clod_scene& sc, const clod_view* views_de
   unsigned long long* dmax_key = (unsigned long long*)(w + L.dmax_key);
   hipError_t e = launch_view_setup(views_dev, L.V, prm, vinfo, (unsigned long long*)(w + L.hdr), out);
   if (e == hipSuccess)
-    e = launch_frustum_max(sc, vinfo, L.V, prm.near_z, (unsigned long long*)(w + L.kpart), dmax_key,
+    e = launch_frustum_max(sc, vinfo, L.V, prm.near_z, (uint32_t*)(w + L.kpart), dmax_key,
                            (uint32_t*)(w + L.sel_hist), L.any_budget ? kSelWords * (uint32_t)L.V : 0u, out);
   if (e == hipSuccess && L.any_budget)
     e = launch_lod_select(sc, vinfo, L.V, prm, dmax_key, (uint32_t*)(w + L.sel_hist), (float*)(w + L.alpha), out);
@@ -464,7 +464,7 @@ clod_status clod_lod_count(const clod_scene* scene, const clod_batch* batch, int
   char* w = (char*)batch->ws;
   DevView* vinfo = (DevView*)(w + L.vinfo);
   HIP_TRY(launch_view_setup(batch->views_dev, L.V, batch->params, vinfo, nullptr, s), "view setup");
-  HIP_TRY(launch_frustum_max(*scene, vinfo, L.V, batch->params.near_z, (unsigned long long*)(w + L.kpart),
+  HIP_TRY(launch_frustum_max(*scene, vinfo, L.V, batch->params.near_z, (uint32_t*)(w + L.kpart),
                              (unsigned long long*)(w + L.dmax_key), (uint32_t*)(w + L.sel_hist),
                              L.any_budget ? kSelWords * (uint32_t)L.V : 0u, s),
           "frustum max");
@@ -509,7 +509,7 @@ clod_status clod_lod_count_noalloc(const clod_scene* scene, int32_t n_views, con
   char* w = (char*)base;
   DevView* vinfo = (DevView*)(w + Cl.vinfo);
   HIP_TRY(launch_view_setup(views_dev, n_views, *params, vinfo, nullptr, s), "view setup");
-  HIP_TRY(launch_frustum_max(*scene, vinfo, n_views, params->near_z, (unsigned long long*)(w + Cl.kpart),
+  HIP_TRY(launch_frustum_max(*scene, vinfo, n_views, params->near_z, (uint32_t*)(w + Cl.kpart),
                              (unsigned long long*)(w + Cl.dmax_key), (uint32_t*)(w + Cl.sel_hist),
                              any_budget ? kSelWords * (uint32_t)n_views : 0u, s),
           "frustum max");

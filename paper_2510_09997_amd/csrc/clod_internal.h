@@ -62,6 +62,7 @@ struct DevView {
   int32_t cam_lead;              // first view of this view's run of consecutive views with the same
                                  // camera (pose, intrinsics, size, frame): they differ in s_v or
                                  // budget only, so positions, projections and colours are shared
+  float geo_k;                   // counting: bound on (projected variance z^2 / scale^2), inf if none (k_view_setup)
   int64_t budget;                // 0: threshold mask; K > 0: the K largest selection keys
   unsigned long long mkey;       // K > 0: smallest kept selection key (set by the radix select)
 };
@@ -92,6 +93,44 @@ constexpr uint32_t kDepthCounterWords = kGroups * (kDepthBins0 + 3 * kRowBinsMax
 struct RowTables {
   uint32_t *tile, *start, *ustart, *pairs, *urow;
 };
+
+// The constants of view v (uniform) as a copy.  kLaunch: read through the constant address space, so
+// with a few wide scalar loads wherever the copy stands; the compiler otherwise proves that only
+// where no store precedes, and reads the table lane by lane, again at each use, in the per-Gaussian
+// loops.  (The table is written by an earlier launch, and a launch starts with a clean scalar
+// cache; the resident serving kernel runs a job's stages in one launch and takes ordinary loads.)
+template <bool kLaunch>
+__device__ __forceinline__ DevView view_at(const DevView* views, int v) {
+  if constexpr (!kLaunch) {
+    return views[v];
+  } else {
+    typedef const __attribute__((address_space(4))) uint32_t* ConstWords32;
+    const ConstWords32 p = (ConstWords32)(uintptr_t)(views + v);
+    constexpr int kWords = sizeof(DevView) / 4;
+    uint32_t w[kWords];
+#pragma unroll
+    for (int j = 0; j < kWords; ++j) w[j] = p[j];
+    DevView d;
+    __builtin_memcpy(&d, w, sizeof(d));
+    return d;
+  }
+}
+
+// A view's camera and up to three further factors in LDS, from where a broadcast puts them into
+// vector registers: an FP32 instruction with a scalar register among its operands issues every four
+// cycles, one of vector registers only every two, and the per-Gaussian loops are bound by that.
+struct __attribute__((aligned(16))) CamLds {
+  float W[9], t[3], c[3], limx, limy, k[3];
+};
+__device__ __forceinline__ CamLds cam_lds(const DevView& V) {
+  CamLds c;
+  for (int j = 0; j < 9; ++j) c.W[j] = V.W[j];
+  for (int j = 0; j < 3; ++j) { c.t[j] = V.t[j]; c.c[j] = V.c[j]; c.k[j] = 0.f; }
+  c.limx = V.limx;
+  c.limy = V.limy;
+  return c;
+}
+constexpr int kCamWords = sizeof(CamLds) / 4;
 
 struct Layout {
   int64_t n = 0;
@@ -224,21 +263,33 @@ __device__ __forceinline__ void sh_basis(int deg, float X, float Y, float Z, flo
   y[15] = SHK::k3a * (X * (xx - 3.0f * yy));
 }
 
-// Camera-space position (rows of W applied with the fused order of the contract).
-__device__ __forceinline__ void to_camera(const DevView& V, float mx, float my, float mz,
+// Camera-space position (rows of W applied with the fused order of the contract).  View: DevView, or
+// the copy of its camera that the per-Gaussian loops keep in vector registers (CamLds).
+template <class View>
+__device__ __forceinline__ void to_camera(const View& V, float mx, float my, float mz,
                                           float& x, float& y, float& z) {
   x = fmaf_(V.W[0], mx, fmaf_(V.W[1], my, fmaf_(V.W[2], mz, V.t[0])));
   y = fmaf_(V.W[3], mx, fmaf_(V.W[4], my, fmaf_(V.W[5], mz, V.t[1])));
   z = fmaf_(V.W[6], mx, fmaf_(V.W[7], my, fmaf_(V.W[8], mz, V.t[2])));
 }
 
-__device__ __forceinline__ bool in_frustum(const DevView& V, float x, float y, float z, float near_z) {
-  return (z > near_z) && (fabsf(x) <= V.limx * z) && (fabsf(y) <= V.limy * z);
+template <class View>
+__device__ __forceinline__ bool in_frustum(const View& V, float x, float y, float z, float near_z) {
+  return (z > near_z) & (fabsf(x) <= V.limx * z) & (fabsf(y) <= V.limy * z);   // (no branches)
+}
+
+// The same as a lane mask of the wave (each comparison writes its mask to scalar registers, where
+// combining them is free for the vector units).
+template <class View>
+__device__ __forceinline__ uint64_t frustum_mask(const View& V, float x, float y, float z, float near_z) {
+  return __builtin_amdgcn_ballot_w64(z > near_z) & __builtin_amdgcn_ballot_w64(fabsf(x) <= V.limx * z) &
+         __builtin_amdgcn_ballot_w64(fabsf(y) <= V.limy * z);
 }
 
 // Squared camera distance; cam_distance is its correctly rounded square root, so the maximum
 // distance over a set is the root of the maximum of these.
-__device__ __forceinline__ float cam_distance2(const DevView& V, float mx, float my, float mz,
+template <class View>
+__device__ __forceinline__ float cam_distance2(const View& V, float mx, float my, float mz,
                                                float& ex, float& ey, float& ez) {
   ex = mx - V.c[0];
   ey = my - V.c[1];
@@ -252,6 +303,32 @@ __device__ __forceinline__ float cam_distance(const DevView& V, float mx, float 
 }
 
 __device__ __forceinline__ float sigmoid_c(float o) { return 1.0f / (1.0f + cexp(-o)); }
+
+// Correctly rounded square root and quotient in fewer instructions than the general ones, for
+// arguments whose intermediates stay normal (the caller checks: x in [2^-80, 2^80]; |a|, |b| in
+// [2^-60, 2^60] or a = 0).  The root is the Newton step on the hardware reciprocal root with a
+// final residual; the quotient takes rb = 1 / b correctly rounded and corrects a * rb by two
+// residuals, the second of which rounds correctly (Markstein: the first quotient is then within an
+// ulp and rb is the rounded reciprocal).  Both are bit-identical to sqrtf and a / b there.
+__device__ __forceinline__ float sqrt_normal(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  float g = x * y, h = 0.5f * y;
+  const float e = fmaf_(-h, g, 0.5f);
+  h = fmaf_(h, e, h);
+  g = fmaf_(g, e, g);
+  return fmaf_(fmaf_(-g, g, x), h, g);
+}
+__device__ __forceinline__ float div_normal(float a, float b, float rb) {
+  float q = a * rb;
+  q = fmaf_(fmaf_(-b, q, a), rb, q);
+  return fmaf_(fmaf_(-b, q, a), rb, q);
+}
+// x in [2^-e, 2^e) (false for NaN, infinities, zeros, subnormals and negative values).
+template <int kE>
+__device__ __forceinline__ bool in_exponents(float x) {
+  constexpr uint32_t lo = (uint32_t)(127 - kE) << 23, hi = (uint32_t)(127 + kE) << 23;
+  return __float_as_uint(x) - lo < hi - lo;
+}
 
 // The view-independent denominator of Eq. (2): 2 max(sigma_d, 0)^2 + eps.
 __device__ __forceinline__ float decay_den(float decay, float eps) {
@@ -529,10 +606,10 @@ struct FillArgs {
   uint32_t* p; uint32_t value; int64_t count;
 };
 struct FrustumArgs {
-  const float* mean; int64_t n; const DevView* views; int32_t V; float near_z; unsigned long long* part;
+  const float* mean; int64_t n; const DevView* views; int32_t V; float near_z; uint32_t* part;
 };
 struct FoldArgs {   // per-view folds of the per-block partials (frustum maximum or counts)
-  const unsigned long long* kpart; const uint32_t* cpart; int32_t G, V; unsigned long long* dmax_key;
+  const uint32_t* kpart; const uint32_t* cpart; int32_t G, V; unsigned long long* dmax_key;
   unsigned long long* counts; int64_t* counts_dev; int64_t n; float* eta_dev;
   uint32_t* clear; uint32_t clear_words;   // counters the depth sort starts with (or none)
 };
@@ -542,8 +619,8 @@ struct ClassifyArgs {
 };
 struct ProjectArgs {
   clod_scene sc; const DevView* views; int32_t V; clod_params prm; const unsigned long long* dmax_key;
-  uint32_t* cpart; const uint32_t* list; const uint32_t* lcount; uint8_t* flags; float4* rec;
-  int32_t write, packed;   // records written; colours from the packed coefficients
+  uint32_t* cpart; const uint32_t* list; const uint32_t* lcount; uint8_t* flags; const float* alpha; float4* rec;
+  int32_t write, packed;   // records written (else counting only); colours from the packed coefficients
 };
 struct SelectArgs {
   clod_scene sc; const DevView* views; DevView* views_out; int32_t V; clod_params prm;
@@ -679,7 +756,7 @@ hipError_t launch_view_setup(const clod_view* views_dev, int V, clod_params prm,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, const Sink& out);
 int proj_blocks(int64_t n);
 hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V, float near_z,
-                              unsigned long long* kpart, unsigned long long* dmax_key,
+                              uint32_t* kpart, unsigned long long* dmax_key,
                               uint32_t* clear, uint32_t clear_words, const Sink& out);
 // counts (workspace) and counts_dev (caller's int64 [V][3], nullable) receive the per-view
 // {frustum, mask, rendered} counts.

@@ -63,6 +63,23 @@ __device__ __forceinline__ void view_setup_body(const ViewSetupArgs& a, Blk b) {
     d.height = cv.height;
     d.tiles_x = (cv.width + kTile - 1) / kTile;
     d.tiles_y = (cv.height + kTile - 1) / kTile;
+    // Bound for the counting pass (count_body): a Gaussian of largest scale s at depth z and
+    // tangents (tx, ty) has projected variances of at most geo_k (1 + tx^2 + ty^2) (s / z)^2 +
+    // dilation (the largest row sum of |W W^T| bounds the norm of W W^T).  Infinite, so that every
+    // projection is evaluated, where the pixel error of its approximate centre is not far below
+    // the margin it uses.
+    {
+      float wb = 0.f;
+      for (int r = 0; r < 3; ++r) {
+        float row = 0.f;
+        for (int q = 0; q < 3; ++q)
+          row += fabsf(cv.W[3 * r] * cv.W[3 * q] + cv.W[3 * r + 1] * cv.W[3 * q + 1] + cv.W[3 * r + 2] * cv.W[3 * q + 2]);
+        wb = row > wb ? row : wb;
+      }
+      const float f = fmaxf(cv.fx, cv.fy), extent = prm.guard * (float)(fw > fh ? fw : fh);
+      const bool ok = wb < 4.0f && f < 1e6f && extent < 1e5f && fabsf(cv.cx) < 1e5f && fabsf(cv.cy) < 1e5f;
+      d.geo_k = ok ? 1.001f * wb * f * f : __builtin_inff();
+    }
     d.budget = cv.budget;
     d.mkey = 0ull;
     // Running bases: the sums over the views before this one.
@@ -99,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_u32(FillArgs a) { fill_body(a, 
 // counts_dev when non-NULL), the kept ratio eta = n_mask / n of Eq. (4) (to eta_dev when
 // non-NULL; binary32 quotient of the counts converted to binary32) and the lowest index at d_max
 // (min), which completes the low half of that key.
-__device__ __forceinline__ void fold_view(int v, const unsigned long long* __restrict__ kpart, const uint32_t* __restrict__ cpart,
+__device__ __forceinline__ void fold_view(int v, const uint32_t* __restrict__ kpart, const uint32_t* __restrict__ cpart,
                           int G, int V, int64_t n, unsigned long long* __restrict__ dmax_key,
                           unsigned long long* __restrict__ counts, int64_t* __restrict__ counts_dev,
                           float* __restrict__ eta_dev) {
@@ -174,16 +191,20 @@ __global__ __launch_bounds__(kBlock) void k_reduce_partials(FoldArgs a) { fold_b
 // into the key bits(d_max) << 32 (d_max its correctly rounded root, the largest distance),
 // and k_classify finds the lowest index at that distance, which completes the key with
 // 2^32 - 1 - index (so that ties resolve to the lowest index).
-__device__ __forceinline__ void frustum_max_body(const FrustumArgs& a, Blk b) {
+// words: LDS of kCamWords V words.
+__device__ __forceinline__ void frustum_max_body(const FrustumArgs& a, Blk b, uint32_t* words) {
   constexpr int kVG = 8;      // views per group (keys held in registers)
-  constexpr int kItems = 8;   // Gaussians per thread per round, loaded before any is used
-  __shared__ unsigned long long sm[kVG][4];
+  constexpr int kItems = 4;   // Gaussians per thread per round, loaded before any is used
+  __shared__ uint32_t sm[kVG][4];
   const float* __restrict__ mean = a.mean;
   const int64_t n = a.n;
   const DevView* __restrict__ views = a.views;
   const int V = a.V;
   const float near_z = a.near_z;
-  unsigned long long* __restrict__ part = a.part;   // [G][V]
+  uint32_t* __restrict__ part = a.part;   // [G][V]
+  CamLds* cam = reinterpret_cast<CamLds*>(words);
+  for (int v = threadIdx.x; v < V; v += kBlock) cam[v] = cam_lds(views[v]);
+  __syncthreads();
   int64_t lo, hi;
   block_chunk(n, b, lo, hi);
   for (int v0 = 0; v0 < V; v0 += kVG) {
@@ -198,30 +219,29 @@ __device__ __forceinline__ void frustum_max_body(const FrustumArgs& a, Blk b) {
 #pragma unroll
     for (int vv = 0; vv < kVG; ++vv) key[vv] = 0u;
     for (int64_t b0 = lo; b0 < hi; b0 += (int64_t)kItems * kBlock) {
+      // Past the chunk's end the last Gaussian is taken again (the maximum stays).
       float px[kItems], py[kItems], pz[kItems];
 #pragma unroll
       for (int k = 0; k < kItems; ++k) {
-        const int64_t i = b0 + (int64_t)k * kBlock + threadIdx.x;
-        const bool valid = i < hi;
-        px[k] = valid ? mean[i] : 0.f;
-        py[k] = valid ? mean[n + i] : 0.f;
-        pz[k] = valid ? mean[2 * n + i] : 0.f;
+        const int64_t j = b0 + (int64_t)k * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+        px[k] = mean[i];
+        py[k] = mean[n + i];
+        pz[k] = mean[2 * n + i];
       }
+      const int kn = hi - b0 >= kItems * kBlock ? kItems : (int)((hi - b0 + kBlock - 1) / kBlock);   // uniform
 #pragma unroll
-      for (int k = 0; k < kItems; ++k) {
-        const int64_t i = b0 + (int64_t)k * kBlock + threadIdx.x;
-        if (i >= hi) continue;
+      for (int vv = 0; vv < kVG; ++vv) {
+        if (vv >= vn) break;
+        if ((shared >> vv) & 1u) continue;
+        const CamLds Vw = cam[v0 + vv];
 #pragma unroll
-        for (int vv = 0; vv < kVG; ++vv) {
-          if (vv >= vn) break;
-          if ((shared >> vv) & 1u) continue;
-          const DevView& Vw = views[v0 + vv];
+        for (int k = 0; k < kItems; ++k) {
+          if (k >= kn) continue;
           float x, y, z, ex, ey, ez;
           to_camera(Vw, px[k], py[k], pz[k], x, y, z);
-          if (in_frustum(Vw, x, y, z, near_z)) {
-            const uint32_t kk = __float_as_uint(cam_distance2(Vw, px[k], py[k], pz[k], ex, ey, ez));
-            key[vv] = kk > key[vv] ? kk : key[vv];
-          }
+          const uint32_t kk = __float_as_uint(cam_distance2(Vw, px[k], py[k], pz[k], ex, ey, ez));
+          const uint32_t key2 = kk > key[vv] ? kk : key[vv];
+          key[vv] = in_frustum(Vw, x, y, z, near_z) ? key2 : key[vv];
         }
       }
     }
@@ -241,14 +261,54 @@ __device__ __forceinline__ void frustum_max_body(const FrustumArgs& a, Blk b) {
     __syncthreads();
     if (threadIdx.x < (unsigned)vn) {
       const int vv = threadIdx.x;
-      unsigned long long m = sm[vv][0];
-      for (int w = 1; w < 4; ++w) m = sm[vv][w] > m ? sm[vv][w] : m;
-      part[(int64_t)b.id * V + v0 + vv] = m;
+      part[(int64_t)b.id * V + v0 + vv] = max(max(sm[vv][0], sm[vv][1]), max(sm[vv][2], sm[vv][3]));
     }
     __syncthreads();
   }
 }
-__global__ __launch_bounds__(kBlock) void k_frustum_max(FrustumArgs a) { frustum_max_body(a, grid_blk()); }
+__global__ __launch_bounds__(kBlock) void k_frustum_max(FrustumArgs a) {
+  extern __shared__ __align__(16) uint32_t words_dyn[];
+  frustum_max_body(a, grid_blk(), words_dyn);
+}
+
+// Factors of Eq. (2) for the loops below, beside the camera in LDS (every block fills its own table).
+__device__ __forceinline__ CamLds classify_cam(const DevView& Vw, unsigned long long dk) {
+  CamLds L = cam_lds(Vw);
+  const float dmax = dmax_from_key(dk);   // frustum maximum (1 if empty)
+  L.k[0] = dmax;
+  L.k[1] = 1.0f / dmax;
+  L.k[2] = Vw.s_v;
+  return L;
+}
+// Counting: (s_v / d_max)^2 (NaN: no estimate), log2 of the mask's threshold, and the squared
+// distance below which a Gaussian cannot hold the frustum maximum.
+__device__ __forceinline__ CamLds count_cam(const DevView& Vw, unsigned long long dk, float eps) {
+  CamLds L = cam_lds(Vw);
+  const float dmax = dmax_from_key(dk), r = Vw.s_v / dmax, kv = r * r;
+  // The mask keeps alpha'' above tau s_v, or above (or at) the value of the budget's smallest key.
+  const float thr = Vw.budget > 0 ? __uint_as_float((uint32_t)(Vw.mkey >> 32)) : Vw.tau_sv;
+  const bool ok = in_exponents<60>(kv) && in_exponents<100>(thr) && eps > 1e-20f;
+  L.k[0] = ok ? kv : __builtin_nanf("");
+  L.k[1] = __builtin_amdgcn_logf(thr);
+  L.k[2] = dk ? (dmax * 0.999999f) * dmax : __builtin_inff();
+  return L;
+}
+
+// Whether Gaussian i at distance d, in the frustum, holds the frustum maximum: its index competes
+// for the lowest.
+__device__ __forceinline__ void dmax_tie(uint32_t* imin, float d, unsigned long long dk, int64_t i) {
+  if (dk != 0ull && __float_as_uint(d) == (uint32_t)(dk >> 32)) atomicMin(imin, (uint32_t)i);
+}
+
+// Appends the wave's lanes with `put` to the block's list segment (order arbitrary).
+__device__ __forceinline__ void list_append(uint32_t* list, uint32_t* sbase, bool put, int64_t i, uint64_t lt) {
+  const uint64_t bw = ballot64(put);
+  if (bw == 0ull) return;
+  uint32_t at = 0;
+  if (lane_id() == 0) at = atomicAdd(sbase, (uint32_t)__popcll(bw));
+  at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+  if (put) list[at + (uint32_t)__popcll(bw & lt)] = (uint32_t)i;
+}
 
 // Pass 1 over every Gaussian (block b owns the chunk [b*C, (b+1)*C)): per view the frustum
 // flag, Eq. (2) and the LoD mask (alpha'' and the F/M flags written for every (view,
@@ -256,241 +316,527 @@ __global__ __launch_bounds__(kBlock) void k_frustum_max(FrustumArgs a) { frustum
 // frustum and kept by its mask appended to the block's segment of the work list (order
 // within a segment is arbitrary).  Outside those, nothing else is computed, so the heavy
 // pass below runs on full waves instead of the ~40% of lanes a whole-scene pass keeps busy.
-// scnt: LDS of 3 V words ([V][3]: F count, M count, lowest index at d_max).
-template <bool kWrite>
-__device__ __forceinline__ void classify_body(const ClassifyArgs& a, Blk b, uint32_t* scnt) {
+//
+// A thread takes four Gaussians at a time, so that a view's constants (scalar loads) and the LDS
+// counters are paid once per 256 of them and four chains run side by side; the root and the two
+// quotients of Eq. (2) are the forms of sqrt_normal and div_normal wherever the arguments allow.
+// One Gaussian at a time, its view's constants read lane by lane behind each branch, it spent three
+// quarters of its wave cycles waiting: 107 us for six views of 3M, 162 us for 16 of 2M, 57 us for
+// one of 6M; now 64, 81 and 38 us, of which the stores of alpha'' and the flags and the reads
+// (20 + 5 V bytes per Gaussian) are 30, 40 and 30 us at the 5.1 TB/s of a large copy.
+// words: LDS of kClassifyWords V words ([V] CamLds, [V] counts F | M << 32, [V] lowest index at d_max).
+constexpr int kClassifyWords = 3 + kCamWords;
+template <bool kLaunch>
+__device__ __forceinline__ void classify_body(const ClassifyArgs& a, Blk b, uint32_t* words) {
+  constexpr int kItems = 4;
   __shared__ uint32_t sbase;
   const clod_scene& sc = a.sc;
   const DevView* __restrict__ views = a.views;
   const int V = a.V;
   const clod_params& prm = a.prm;
   const unsigned long long* __restrict__ dmax_key = a.dmax_key;
-  uint32_t* __restrict__ cpart = a.cpart;   // [G][V][4]
-  uint8_t* __restrict__ flags_out = a.flags;
-  float* __restrict__ alpha_out = a.alpha;
-  uint32_t* __restrict__ list = a.list;       // [n]
-  uint32_t* __restrict__ lcount = a.lcount;   // [G]
   const int64_t n = sc.n;
-  for (int j = threadIdx.x; j < 3 * V; j += kBlock) scnt[j] = j % 3 == 2 ? 0xFFFFFFFFu : 0u;
+  CamLds* cam = reinterpret_cast<CamLds*>(words);
+  unsigned long long* cnt = reinterpret_cast<unsigned long long*>(words + kCamWords * V);
+  uint32_t* imin = words + (kCamWords + 2) * V;
+  for (int j = threadIdx.x; j < V; j += kBlock) {
+    cnt[j] = 0ull;
+    imin[j] = 0xFFFFFFFFu;
+    cam[j] = classify_cam(views[j], dmax_key[j]);
+  }
   if (threadIdx.x == 0) sbase = 0;
   __syncthreads();
   int64_t lo, hi;
   block_chunk(n, b, lo, hi);
   const uint64_t lt = lanemask_lt();
-  const int64_t iters = (hi - lo + kBlock - 1) / kBlock;
-  // Software pipelined: the next round's parameters are loaded before this round's views are
-  // evaluated, so their latency overlaps the arithmetic.
-  float nmx = 0.f, nmy = 0.f, nmz = 0.f, nop = 0.f, ndc = 0.f;
-  {
-    const int64_t i = lo + threadIdx.x;
-    if (iters > 0 && i < hi) {
-      nmx = sc.mean[i]; nmy = sc.mean[n + i]; nmz = sc.mean[2 * n + i];
-      nop = sc.opacity[i]; ndc = sc.decay[i];
+  for (int64_t b0 = lo; b0 < hi; b0 += kItems * kBlock) {
+    const int kn = hi - b0 >= kItems * kBlock ? kItems : (int)((hi - b0 + kBlock - 1) / kBlock);   // uniform
+    float mx[kItems], my[kItems], mz[kItems], alpha[kItems], den[kItems], rden[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const int64_t j = b0 + k * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+      mx[k] = sc.mean[i]; my[k] = sc.mean[n + i]; mz[k] = sc.mean[2 * n + i];
+      alpha[k] = sc.opacity[i]; den[k] = sc.decay[i];
     }
-  }
-  for (int64_t it = 0; it < iters; ++it) {
-    const int64_t i = lo + it * kBlock + threadIdx.x;
-    const bool valid = i < hi;
-    const float mx = nmx, my = nmy, mz = nmz;
-    const float alpha = sigmoid_c(nop), den = decay_den(ndc, prm.eps);   // view independent
-    {
-      const int64_t i2 = i + kBlock;
-      if (it + 1 < iters && i2 < hi) {
-        nmx = sc.mean[i2]; nmy = sc.mean[n + i2]; nmz = sc.mean[2 * n + i2];
-        nop = sc.opacity[i2]; ndc = sc.decay[i2];
-      }
+    uint32_t any = 0;   // bit k: item k is in some view's frustum and kept
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      alpha[k] = sigmoid_c(alpha[k]);
+      den[k] = decay_den(den[k], prm.eps);   // view independent
+      rden[k] = 1.0f / den[k];
     }
-    bool any = false;
+    uint64_t vm[kItems];   // lanes with a Gaussian
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) vm[k] = ballot64(b0 + k * kBlock + threadIdx.x < hi);
     // The camera's part (frustum flag, distance, d / d_max) of the previous view, reused by the
     // views of the same camera run (which have the same frustum maximum).
     int lead = -1;
-    bool F = false;
-    float d = 0.f, dn = 0.f;
+    uint64_t F[kItems];
+    float d[kItems], dn[kItems];
     for (int v = 0; v < V; ++v) {
-      const DevView& Vw = views[v];
-      bool M = false;
-      if (!valid) F = false;
-      if (valid) {
-        const unsigned long long dk = dmax_key[v];
-        if (Vw.cam_lead != lead) {
-          float x, y, z, ex, ey, ez;
-          to_camera(Vw, mx, my, mz, x, y, z);
-          F = in_frustum(Vw, x, y, z, prm.near_z);
-          d = cam_distance(Vw, mx, my, mz, ex, ey, ez);
-          dn = d / dmax_from_key(dk);
-          lead = Vw.cam_lead;
-        }
-        if (F && dk != 0ull && __float_as_uint(d) == (uint32_t)(dk >> 32)) atomicMin(&scnt[3 * v + 2], (uint32_t)i);
-        float q;
-        const float a2 = attenuated_dn(dn, Vw.s_v, alpha, den, q);
-        M = lod_kept(Vw, a2, i);
-        if (kWrite) {
-          const int64_t f = (int64_t)v * n + i;
-          alpha_out[f] = a2;
-          flags_out[f] = (uint8_t)((F ? 1 : 0) | (M ? 2 : 0));
+      const DevView Vw = view_at<kLaunch>(views, v);
+      const CamLds C = cam[v];
+      const float dmax = C.k[0], rdmax = C.k[1], s_v = C.k[2];
+      uint32_t nF = 0, nM = 0, kept = 0;
+      const bool fresh = Vw.cam_lead != lead;
+      lead = Vw.cam_lead;
+      // Lanes whose arguments the short forms do not take, or at the frustum maximum.
+      uint64_t special = ballot64(!in_exponents<40>(dmax));
+#pragma unroll
+      for (int k = 0; k < kItems; ++k) {
+        if (k < kn) {
+          const int64_t i = b0 + k * kBlock + threadIdx.x;
+          if (fresh) {
+            float x, y, z, ex, ey, ez;
+            to_camera(C, mx[k], my[k], mz[k], x, y, z);
+            F[k] = frustum_mask(C, x, y, z, prm.near_z) & vm[k];
+            const float d2 = cam_distance2(C, mx[k], my[k], mz[k], ex, ey, ez);
+            d[k] = sqrt_normal(d2);
+            dn[k] = div_normal(d[k], dmax, rdmax);
+            special |= ballot64(!in_exponents<80>(d2));
+          }
+          const float u = dn[k] * s_v, num = u * u;
+          const float q = div_normal(num, den[k], rden[k]);
+          const float a2 = alpha[k] * (q > 86.0f ? 0.0f : cexp_core<true>(-q));
+          special |= ballot64(!in_exponents<60>(num)) | ballot64(!in_exponents<60>(den[k])) | (ballot64(d[k] == dmax) & F[k]);
+          const uint64_t M = (Vw.budget > 0 ? ballot64(lod_key(a2, i) >= Vw.mkey) : ballot64(a2 > Vw.tau_sv)) & vm[k];
+          const uint32_t fl = (__builtin_amdgcn_inverse_ballot_w64(F[k]) ? 1u : 0u) |
+                              (__builtin_amdgcn_inverse_ballot_w64(M) ? 2u : 0u);
+          if (__builtin_amdgcn_inverse_ballot_w64(vm[k])) {
+            const int64_t f = (int64_t)v * n + i;
+            a.alpha[f] = a2;
+            a.flags[f] = (uint8_t)fl;
+          }
+          kept |= fl == 3u ? 1u << k : 0u;
+          nF += (uint32_t)__popcll(F[k]);
+          nM += (uint32_t)__popcll(M);
         }
       }
-      any = any || (F && M);
-      const uint64_t bF = ballot64(F), bM = ballot64(M);
-      if (lane_id() == 0) {
-        if (bF) atomicAdd(&scnt[3 * v + 0], (uint32_t)__popcll(bF));
-        if (bM) atomicAdd(&scnt[3 * v + 1], (uint32_t)__popcll(bM));
+      if (special) {
+        // Once more with the general forms, from the planes; nothing is handed to the next view.
+        nF = nM = kept = 0u;
+        lead = -1;
+        for (int k = 0; k < kn; ++k) {
+          const int64_t i = b0 + k * kBlock + threadIdx.x;
+          bool Fk = false, M = false;
+          if (i < hi) {
+            const float px = sc.mean[i], py = sc.mean[n + i], pz = sc.mean[2 * n + i];
+            float x, y, z, ex, ey, ez, al, q;
+            to_camera(Vw, px, py, pz, x, y, z);
+            Fk = in_frustum(Vw, x, y, z, prm.near_z);
+            const float dk = cam_distance(Vw, px, py, pz, ex, ey, ez);
+            if (Fk) dmax_tie(&imin[v], dk, dmax_key[v], i);
+            const float a2 = attenuated(dk, dmax, Vw.s_v, sc.decay[i], sc.opacity[i], prm.eps, al, q);
+            M = lod_kept(Vw, a2, i);
+            const int64_t f = (int64_t)v * n + i;
+            a.alpha[f] = a2;
+            a.flags[f] = (uint8_t)((Fk ? 1 : 0) | (M ? 2 : 0));
+          }
+          kept |= Fk && M ? 1u << k : 0u;
+          nF += (uint32_t)__popcll(ballot64(Fk));
+          nM += (uint32_t)__popcll(ballot64(M));
+        }
       }
+      any |= kept;
+      if (lane_id() == 0 && (nF | nM)) atomicAdd(&cnt[v], (unsigned long long)nF | (unsigned long long)nM << 32);
     }
-    const uint64_t bw = ballot64(any);
-    uint32_t wbase = 0;
-    if (lane_id() == 0 && bw) wbase = atomicAdd(&sbase, (uint32_t)__popcll(bw));
-    wbase = __shfl(wbase, 0, 64);
-    if (any) list[lo + wbase + (uint32_t)__popcll(bw & lt)] = (uint32_t)i;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+      list_append(a.list + lo, &sbase, (any >> k) & 1u, b0 + k * kBlock + threadIdx.x, lt);
   }
   __syncthreads();
   for (int j = threadIdx.x; j < V; j += kBlock) {
-    cpart[((int64_t)b.id * V + j) * 4 + 0] = scnt[3 * j];
-    cpart[((int64_t)b.id * V + j) * 4 + 1] = scnt[3 * j + 1];
-    cpart[((int64_t)b.id * V + j) * 4 + 3] = scnt[3 * j + 2];
+    uint32_t* c = a.cpart + ((int64_t)b.id * V + j) * 4;   // [G][V][4]
+    c[0] = (uint32_t)cnt[j];
+    c[1] = (uint32_t)(cnt[j] >> 32);
+    c[3] = imin[j];
   }
-  if (threadIdx.x == 0) lcount[b.id] = sbase;
+  if (threadIdx.x == 0) a.lcount[b.id] = sbase;
 }
-template <bool kWrite>
 __global__ __launch_bounds__(kBlock) void k_classify(ClassifyArgs a) {
-  extern __shared__ uint32_t scnt_dyn[];
-  classify_body<kWrite>(a, grid_blk(), scnt_dyn);
+  extern __shared__ __align__(16) uint32_t words_dyn[];
+  classify_body<true>(a, grid_blk(), words_dyn);
 }
 
-// Pass 2 over the work list (entries spread evenly over the blocks): per listed Gaussian the
-// geometry of every view again (cheap), then for in-frustum kept views the EWA projection,
-// cull and rectangle, remembering which views render it; then the colour of each rendering
-// view is evaluated from its SH coefficients.  Records (with depth, rectangle and tiles
-// touched in their fourth quad) are written for rendered (view, Gaussian) pairs only.
-// sdyn: LDS of G + V words ([G] segment offsets, then [V] rendered counts).
-template <int DEG, bool kWriteRecords, bool kPacked>
-__device__ __forceinline__ void project_body(const ProjectArgs& a, Blk b, uint32_t* sdyn) {
-  __shared__ uint32_t sm[4];
+// Counting without rendering (clod_lod_count): nothing of Eq. (2) or of the projection is stored,
+// only compared with a threshold, so both are estimated first and evaluated only where the estimate
+// leaves the comparison open.  The counts are those of the full evaluation.  64 views of 6M
+// Gaussians: 1,198 us for the masks and 509 us for the projections in full, now 559 us (two thirds
+// of it vector issue) and 193 us.
+//
+// Mask: alpha'' > threshold is log2(alpha) - q log2(e) > log2(threshold), where the left side needs
+// no root, quotient or exponential per view.  alpha'' of the contract differs from the exact value
+// by a factor within 2^(5e-6 q + 1e-6) (q's roundings, E's 2 ulp, the last product), and the
+// estimate's by less than that (hardware log2 and reciprocal, five products), both far inside the
+// margin below; NaN and any case the factors cannot express (count_cam) stay open.
+struct LodItem {
+  float la, iden;   // log2(alpha), log2(e) / (2 max(sigma_d, 0)^2 + eps)
+};
+__device__ __forceinline__ LodItem lod_item(float opac, float decay, float eps) {
+  return LodItem{__builtin_amdgcn_logf(sigmoid_c(opac)), 1.44269504088896341f * __builtin_amdgcn_rcpf(decay_den(decay, eps))};
+}
+// (Lane masks of the wave.)
+__device__ __forceinline__ void mask_estimate(const LodItem& I, const CamLds& L, float d2, uint64_t& kept, uint64_t& dropped) {
+  const float x = (d2 * L.k[0]) * I.iden, y = I.la - L.k[1];
+  kept = ballot64(fmaf_(x, 1.00001f, 1e-4f) < y);
+  dropped = ballot64(fmaf_(x, 0.99999f, -1e-4f) > y);
+}
+__device__ __forceinline__ bool mask_exact(const clod_scene& sc, const DevView& Vw, unsigned long long dk, float d2,
+                                           float eps, int64_t i) {
+  float alpha, q;
+  return lod_kept(Vw, attenuated(__builtin_sqrtf(d2), dmax_from_key(dk), Vw.s_v, sc.decay[i], sc.opacity[i], eps, alpha, q), i);
+}
+
+// Projection of a Gaussian in the frustum: rendered if det > 0 and its rectangle meets the viewport.
+// Both projected variances are at most B (DevView::geo_k, the largest scale).  Centre inside the
+// viewport: the rectangle holds its tile, and det >= dilation^2 in exact arithmetic, while the
+// binary32 evaluation errs by at most 5e-5 B^2 (35 roundings along the chain, times the sums of
+// absolute values, at most 6 B each).  Centre farther outside than 3 sqrt(2 B) + 1, which bounds the
+// radius: no tile.  Anything else stays open, as do rotations or scales that are not plain numbers.
+__device__ __forceinline__ float geo_item(const clod_scene& sc, int64_t i) {   // largest scale squared, inf: open
+  const int64_t n = sc.n;
+  const float l0 = sc.log_scale[i], l1 = sc.log_scale[n + i], l2 = sc.log_scale[2 * n + i];
+  const float qw = sc.quat[i], qx = sc.quat[n + i], qy = sc.quat[2 * n + i], qz = sc.quat[3 * n + i];
+  const float n2 = qw * qw + qx * qx + qy * qy + qz * qz, ls = l0 + l1 + l2;
+  const float s2 = 1.001f * __builtin_amdgcn_exp2f(2.88539008177792681f * fmaxf(l0, fmaxf(l1, l2)));
+  return (n2 > 1e-30f) & (n2 < 1e30f) & (ls == ls) ? s2 : __builtin_inff();
+}
+__device__ __forceinline__ void geo_estimate(const DevView& Vw, float s2, float dil, float x, float y, float z,
+                                             uint64_t& in, uint64_t& out) {
+  const float iz = __builtin_amdgcn_rcpf(z), tx = x * iz, ty = y * iz;
+  const float B = fmaf_(Vw.geo_k * s2, fmaf_(tx, tx, fmaf_(ty, ty, 1.0f)) * (iz * iz), dil);
+  const float u = fmaf_(Vw.fx, tx, Vw.cx - (float)Vw.vx), v = fmaf_(Vw.fy, ty, Vw.cy - (float)Vw.vy);
+  const float far = fmaxf(fmaxf(-u, u - (float)(kTile * Vw.tiles_x)), fmaxf(-v, v - (float)(kTile * Vw.tiles_y)));
+  in = ballot64(u > 0.5f) & ballot64(u < (float)Vw.width - 0.5f) & ballot64(v > 0.5f) &
+       ballot64(v < (float)Vw.height - 0.5f) & ballot64(1e-4f * (B * B) < dil * dil);
+  // (For NaN none of the comparisons holds.)
+  out = ballot64(far > fmaf_(4.25f, __builtin_amdgcn_sqrtf(B), 2.0f)) & ~in;
+}
+
+// Pass 1 of the counting: F and M counts, the decided part of the rendered counts, and the Gaussians
+// whose projection is open in some view appended to the block's list segment.
+// words: LDS of kCountWords V words ([V] CamLds, [V] counts F | M << 32, [V] lowest index at d_max,
+// [V] rendered).
+constexpr int kCountWords = 4 + kCamWords;
+__device__ __forceinline__ void count_body(const ClassifyArgs& a, Blk b, uint32_t* words) {
+  constexpr int kItems = 4;
+  __shared__ uint32_t sbase;
   const clod_scene& sc = a.sc;
   const DevView* __restrict__ views = a.views;
   const int V = a.V;
   const clod_params& prm = a.prm;
   const unsigned long long* __restrict__ dmax_key = a.dmax_key;
-  uint32_t* __restrict__ cpart = a.cpart;   // [G][V][4]
-  const uint32_t* __restrict__ list = a.list;
-  const uint32_t* __restrict__ lcount = a.lcount;
-  uint8_t* __restrict__ flags_out = a.flags;
+  const int64_t n = sc.n;
+  CamLds* cam = reinterpret_cast<CamLds*>(words);
+  unsigned long long* cnt = reinterpret_cast<unsigned long long*>(words + kCamWords * V);
+  uint32_t* imin = words + (kCamWords + 2) * V;
+  uint32_t* rend = imin + V;
+  for (int j = threadIdx.x; j < V; j += kBlock) {
+    cnt[j] = 0ull;
+    imin[j] = 0xFFFFFFFFu;
+    rend[j] = 0u;
+    cam[j] = count_cam(views[j], dmax_key[j], prm.eps);
+  }
+  if (threadIdx.x == 0) sbase = 0;
+  __syncthreads();
+  int64_t lo, hi;
+  block_chunk(n, b, lo, hi);
+  const uint64_t lt = lanemask_lt();
+  for (int64_t b0 = lo; b0 < hi; b0 += kItems * kBlock) {
+    const int kn = hi - b0 >= kItems * kBlock ? kItems : (int)((hi - b0 + kBlock - 1) / kBlock);   // uniform
+    float mx[kItems], my[kItems], mz[kItems], s2[kItems];
+    LodItem it[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const int64_t j = b0 + k * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+      mx[k] = sc.mean[i]; my[k] = sc.mean[n + i]; mz[k] = sc.mean[2 * n + i];
+      it[k] = LodItem{sc.opacity[i], sc.decay[i]};
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) it[k] = lod_item(it[k].la, it[k].iden, prm.eps);
+    uint64_t vm[kItems];   // lanes with a Gaussian
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) vm[k] = ballot64(b0 + k * kBlock + threadIdx.x < hi);
+    uint32_t have = 0, open = 0;   // bit k: s2[k] read (uniform); some view's projection is open
+    for (int v = 0; v < V; ++v) {
+      const DevView Vw = view_at<true>(views, v);
+      const CamLds C = cam[v];
+      uint32_t nF = 0, nM = 0, nR = 0, opened = 0;
+      uint64_t special = 0;   // lanes whose mask is open, or that may hold the frustum maximum
+#pragma unroll
+      for (int k = 0; k < kItems; ++k) {
+        if (k < kn) {
+          float x, y, z, ex, ey, ez;
+          to_camera(C, mx[k], my[k], mz[k], x, y, z);
+          const uint64_t F = frustum_mask(C, x, y, z, prm.near_z) & vm[k];
+          const float d2 = cam_distance2(C, mx[k], my[k], mz[k], ex, ey, ez);
+          uint64_t kept, dropped;
+          mask_estimate(it[k], C, d2, kept, dropped);
+          special |= (vm[k] & ~(kept | dropped)) | (F & ballot64(d2 >= C.k[2]));
+          const uint64_t M = vm[k] & kept, FM = F & M;
+          nF += (uint32_t)__popcll(F);
+          nM += (uint32_t)__popcll(M);
+          if (FM) {
+            if (!((have >> k) & 1u)) {
+              uint32_t at = k * kBlock + threadIdx.x;
+              asm volatile("" : "+v"(at));   // (keeps these addresses out of the registers until here)
+              const int64_t i = b0 + at;
+              s2[k] = geo_item(sc, i < hi ? i : hi - 1);
+              have |= 1u << k;
+            }
+            uint64_t in, out;
+            geo_estimate(Vw, s2[k], prm.dilation, x, y, z, in, out);
+            nR += (uint32_t)__popcll(FM & in);
+            opened |= __builtin_amdgcn_inverse_ballot_w64(FM & ~(in | out)) ? 1u << k : 0u;
+          }
+        }
+      }
+      if (special) {
+        // Once more with the mask evaluated in full where it is open.
+        nF = nM = nR = opened = 0u;
+        for (int k = 0; k < kn; ++k) {
+          const int64_t j = b0 + k * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+          const uint64_t valid = ballot64(j < hi);
+          const float px = sc.mean[i], py = sc.mean[n + i], pz = sc.mean[2 * n + i];
+          float x, y, z, ex, ey, ez;
+          to_camera(C, px, py, pz, x, y, z);
+          const uint64_t F = frustum_mask(C, x, y, z, prm.near_z) & valid;
+          const float d2 = cam_distance2(C, px, py, pz, ex, ey, ez);
+          if (__builtin_amdgcn_inverse_ballot_w64(F)) dmax_tie(&imin[v], __builtin_sqrtf(d2), dmax_key[v], i);
+          uint64_t kept, dropped;
+          mask_estimate(lod_item(sc.opacity[i], sc.decay[i], prm.eps), C, d2, kept, dropped);
+          const uint64_t M = (kept | (ballot64(mask_exact(sc, Vw, dmax_key[v], d2, prm.eps, i)) & ~dropped)) & valid;
+          uint64_t in, out;
+          geo_estimate(Vw, geo_item(sc, i), prm.dilation, x, y, z, in, out);
+          nF += (uint32_t)__popcll(F);
+          nM += (uint32_t)__popcll(M);
+          nR += (uint32_t)__popcll(F & M & in);
+          opened |= __builtin_amdgcn_inverse_ballot_w64(F & M & ~(in | out)) ? 1u << k : 0u;
+        }
+      }
+      open |= opened;
+      if (lane_id() == 0 && (nF | nM)) {
+        atomicAdd(&cnt[v], (unsigned long long)nF | (unsigned long long)nM << 32);
+        if (nR) atomicAdd(&rend[v], nR);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+      list_append(a.list + lo, &sbase, (open >> k) & 1u, b0 + k * kBlock + threadIdx.x, lt);
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < V; j += kBlock) {
+    uint32_t* c = a.cpart + ((int64_t)b.id * V + j) * 4;   // [G][V][4]
+    c[0] = (uint32_t)cnt[j];
+    c[1] = (uint32_t)(cnt[j] >> 32);
+    c[2] = rend[j];
+    c[3] = imin[j];
+  }
+  if (threadIdx.x == 0) a.lcount[b.id] = sbase;
+}
+__global__ __launch_bounds__(kBlock) void k_count(ClassifyArgs a) {
+  extern __shared__ __align__(16) uint32_t words_dyn[];
+  count_body(a, grid_blk(), words_dyn);
+}
+
+// The work list: G segments (block g's at g * per, its length in lcount[g]).  Every block scans the
+// lengths (G <= kMaxProjBlocks: eight per thread) into soff[0 .. kMaxProjBlocks], the segments'
+// first entries (past the last segment the number of entries); returns that number.
+constexpr int kSegWords = kMaxProjBlocks + 1;
+__device__ __forceinline__ uint32_t scan_segments(const uint32_t* __restrict__ lcount, int G, uint32_t* soff) {
+  __shared__ uint32_t sm[4];
+  constexpr int kPer = kMaxProjBlocks / kBlock;
+  static_assert(kPer * kBlock == kMaxProjBlocks, "segment scan layout");
+  const int j0 = threadIdx.x * kPer;
+  uint32_t c[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    c[k] = j0 + k < G ? lcount[j0 + k] : 0u;
+    sum += c[k];
+  }
+  uint32_t tot;
+  uint32_t off = block_exclusive_scan(sum, sm, tot);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    soff[j0 + k] = off;
+    off += c[k];
+  }
+  if (threadIdx.x == 0) soff[kMaxProjBlocks] = tot;
+  __syncthreads();
+  return tot;
+}
+// The Gaussian of entry e (of the wave's first entry e0 onwards, e0 uniform and below the number of
+// entries): the wave finds the segment of e0 with two 64-wide comparisons (a binary search is eleven
+// dependent LDS reads), and the lanes walk on from there.
+__device__ __forceinline__ int64_t list_entry(const uint32_t* __restrict__ list, const uint32_t* soff, int64_t per,
+                                              uint32_t e0, uint32_t e) {
+  constexpr uint32_t kFine = kMaxProjBlocks / 64;
+  const uint32_t lane = lane_id();
+  const uint32_t c = (uint32_t)__popcll(ballot64(soff[lane * kFine] <= e0)) - 1u;   // soff[0] = 0
+  const uint32_t f = (uint32_t)__popcll(ballot64(lane < kFine && soff[c * kFine + (lane % kFine)] <= e0)) - 1u;
+  uint32_t s = c * kFine + f;
+  while (soff[s + 1] <= e) ++s;
+  return (int64_t)list[(int64_t)s * per + (e - soff[s])];
+}
+
+// Pass 2 of the counting, over the listed Gaussians: the open projections evaluated in full.
+// sdyn: LDS of kSegWords + kCountWords V words ([V] CamLds, segment offsets, [V] rendered counts).
+__device__ __forceinline__ void count_rest_body(const ProjectArgs& a, Blk b, uint32_t* sdyn) {
+  const clod_scene& sc = a.sc;
+  const DevView* __restrict__ views = a.views;
+  const int V = a.V, G = (int)b.n;
+  const clod_params& prm = a.prm;
+  const int64_t n = sc.n;
+  CamLds* cam = reinterpret_cast<CamLds*>(sdyn);
+  uint32_t* soff = sdyn + kCamWords * V;
+  uint32_t* scnt = soff + kSegWords;
+  for (int j = threadIdx.x; j < V; j += kBlock) {
+    scnt[j] = 0u;
+    cam[j] = count_cam(views[j], a.dmax_key[j], prm.eps);
+  }
+  const uint32_t L = scan_segments(a.lcount, G, soff);
+  const int64_t per = (n + G - 1) / G;
+  for (int64_t base = (int64_t)b.id * kBlock + (threadIdx.x & ~63u); base < L; base += (int64_t)G * kBlock) {
+    const uint32_t e0 = (uint32_t)base, e = min(e0 + lane_id(), L - 1u);
+    const uint64_t valid = ballot64(e0 + lane_id() < L);
+    const int64_t i = list_entry(a.list, soff, per, e0, e);
+    const float mx = sc.mean[i], my = sc.mean[n + i], mz = sc.mean[2 * n + i];
+    const LodItem it = lod_item(sc.opacity[i], sc.decay[i], prm.eps);
+    const float s2 = geo_item(sc, i);
+    const float s0 = cexp(sc.log_scale[i]), s1 = cexp(sc.log_scale[n + i]), s2c = cexp(sc.log_scale[2 * n + i]);
+    float Rm[9], S[9], w_, x_, y_, z_, rn;
+    quat_rot(sc.quat[i], sc.quat[n + i], sc.quat[2 * n + i], sc.quat[3 * n + i], Rm, w_, x_, y_, z_, rn);
+    cov3(Rm, s0, s1, s2c, S);
+    for (int v = 0; v < V; ++v) {
+      const DevView Vw = view_at<true>(views, v);
+      const CamLds C = cam[v];
+      float x, y, z, ex, ey, ez;
+      to_camera(C, mx, my, mz, x, y, z);
+      uint64_t in, out, kept, dropped;
+      geo_estimate(Vw, s2, prm.dilation, x, y, z, in, out);
+      const uint64_t F = frustum_mask(C, x, y, z, prm.near_z) & valid & ~(in | out);
+      if (!F) continue;
+      const float d2 = cam_distance2(C, mx, my, mz, ex, ey, ez);
+      mask_estimate(it, C, d2, kept, dropped);
+      const uint64_t open = F & ~dropped;
+      bool R = false;
+      if (__builtin_amdgcn_inverse_ballot_w64(open)) {
+        Proj P;
+        R = ewa(Vw, x, y, z, S, prm.dilation, P) &&
+            (__builtin_amdgcn_inverse_ballot_w64(kept) || mask_exact(sc, Vw, a.dmax_key[v], d2, prm.eps, i));
+      }
+      const uint32_t nR = (uint32_t)__popcll(ballot64(R));
+      if (lane_id() == 0 && nR) atomicAdd(&scnt[v], nR);
+    }
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < V; j += kBlock) a.cpart[((int64_t)b.id * V + j) * 4 + 2] += scnt[j];
+}
+__global__ __launch_bounds__(kBlock) void k_count_rest(ProjectArgs a) {
+  extern __shared__ __align__(16) uint32_t words_dyn[];
+  count_rest_body(a, grid_blk(), words_dyn);
+}
+
+// Pass 2 over the work list (entries spread evenly over the blocks): per listed Gaussian the
+// EWA projection, cull and rectangle in the views that keep it (the flags and alpha'' of pass 1),
+// remembering which views render it; then the colour of each rendering view is evaluated from its
+// SH coefficients.  Records (with depth, rectangle and tiles touched in their fourth quad) are
+// written for rendered (view, Gaussian) pairs only.  The pass waits for its gathers more than it
+// computes: the parameters and the first flags of an entry are all requested before any is used.
+// Eq. (2) is read, not evaluated again, and no plane address outlives its use (the 3K addresses of
+// plane-major coefficients, formed ahead of the loop, left two waves per SIMD): six views of 3M
+// 168 -> 152 us, 5 views of a camera 47 -> 40 us, 16 views of 2M with plane-major coefficients
+// 336 -> 245 us.
+// sdyn: LDS of kSegWords + V words ([kSegWords] segment offsets, then [V] rendered counts).
+template <int DEG, bool kPacked, bool kLaunch>
+__device__ __forceinline__ void project_body(const ProjectArgs& a, Blk b, uint32_t* sdyn) {
+  const clod_scene& sc = a.sc;
+  const DevView* __restrict__ views = a.views;
+  const int V = a.V;
+  const clod_params& prm = a.prm;
+  uint8_t* __restrict__ flags = a.flags;
+  const float* __restrict__ alpha = a.alpha;
   float4* __restrict__ rec = a.rec;
   constexpr int K = (DEG + 1) * (DEG + 1);
   const int64_t n = sc.n;
   const int G = (int)b.n;
   uint32_t* soff = sdyn;
-  uint32_t* scnt = sdyn + G;
-  // Exclusive offsets of the G list segments and the list length: every block scans the
-  // segment counts itself (G <= 2048: eight per thread, blocked).
-  int64_t L;
-  {
-    constexpr int kPer = kMaxProjBlocks / kBlock;
-    static_assert(kPer * kBlock == kMaxProjBlocks, "segment scan layout");
-    const int j0 = threadIdx.x * kPer;
-    uint32_t c[kPer], sum = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      c[k] = j0 + k < G ? lcount[j0 + k] : 0u;
-      sum += c[k];
-    }
-    uint32_t tot;
-    uint32_t off = block_exclusive_scan(sum, sm, tot);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      if (j0 + k < G) soff[j0 + k] = off;
-      off += c[k];
-    }
-    L = tot;
-  }
+  uint32_t* scnt = sdyn + kSegWords;
   for (int j = threadIdx.x; j < V; j += kBlock) scnt[j] = 0;
-  __syncthreads();
+  const uint32_t L = scan_segments(a.lcount, G, soff);
   const int64_t per = (n + G - 1) / G;   // chunk length of the first pass
-  const int64_t stride = (int64_t)G * kBlock;
-  // Every lane of the block runs the same number of rounds (ballots stay uniform).
-  for (int64_t base = (int64_t)b.id * kBlock; base < L; base += stride) {
-    const int64_t e = base + threadIdx.x;
-    const bool valid = e < L;
-    int64_t i = 0;
-    if (valid) {
-      int blo = 0, bhi = G - 1;   // last segment whose offset is <= e
-      while (blo < bhi) {
-        const int mid = (blo + bhi + 1) >> 1;
-        if ((int64_t)soff[mid] <= e) blo = mid; else bhi = mid - 1;
-      }
-      i = (int64_t)list[(int64_t)blo * per + (e - (int64_t)soff[blo])];
-    }
-    float mx = 0.f, my = 0.f, mz = 0.f, op = 0.f, dc = 0.f;
-    if (valid) {
-      mx = sc.mean[i]; my = sc.mean[n + i]; mz = sc.mean[2 * n + i];
-      op = sc.opacity[i]; dc = sc.decay[i];
-    }
-    const float alpha = sigmoid_c(op), den = decay_den(dc, prm.eps);   // view independent
-    // Rotation and 3D covariance are view independent: computed on first use.
-    bool have_cov = false;
-    float S[9];
+  for (int64_t base = (int64_t)b.id * kBlock + (threadIdx.x & ~63u); base < L; base += (int64_t)G * kBlock) {
+    const uint32_t e0 = (uint32_t)base, e = min(e0 + lane_id(), L - 1u);
+    const bool valid = e0 + lane_id() < L;
+    const int64_t i = list_entry(a.list, soff, per, e0, e);
+    const float mx = sc.mean[i], my = sc.mean[n + i], mz = sc.mean[2 * n + i];
+    const float l0 = sc.log_scale[i], l1 = sc.log_scale[n + i], l2 = sc.log_scale[2 * n + i];
+    const float qw = sc.quat[i], qx = sc.quat[n + i], qy = sc.quat[2 * n + i], qz = sc.quat[3 * n + i];
+    float S[9];   // 3D covariance (view independent)
     // The projection (and below the colour) of the last camera run evaluated: views of one run
     // share them (only alpha'' and the mask depend on s_v).
     int geo_lead = -1, col_lead = -1;
     Proj P;
-    bool pok = false;
+    float z = 0.f;
+    bool pok = false, have_cov = false;
     float col[3] = {0.f, 0.f, 0.f};
     uint8_t cfl = 0;
     for (int v0 = 0; v0 < V; v0 += 32) {
       const int vn = V - v0 < 32 ? V - v0 : 32;
-      uint32_t rmask = 0;   // rendered views of the group
+      uint32_t kmask = 0, rmask = 0;   // views of the group that keep the Gaussian; that render it
+#pragma unroll 8
+      for (int vv = 0; vv < vn; ++vv)
+        kmask |= (flags[(int64_t)(v0 + vv) * n + i] & 3u) == 3u ? 1u << vv : 0u;
+      if (!valid) kmask = 0;
+      if (!have_cov) {
+        have_cov = true;
+        float Rm[9], w_, x_, y_, z_, rn;
+        quat_rot(qw, qx, qy, qz, Rm, w_, x_, y_, z_, rn);
+        cov3(Rm, cexp(l0), cexp(l1), cexp(l2), S);
+      }
       for (int vv = 0; vv < vn; ++vv) {
+        const bool kept = ((kmask >> vv) & 1u) != 0u;
+        if (!ballot64(kept)) continue;
         const int v = v0 + vv;
-        const DevView& Vw = views[v];
+        const DevView Vw = view_at<kLaunch>(views, v);
         bool R = false;
-        if (valid) {
-          float x, y, z, ex, ey, ez;
-          to_camera(Vw, mx, my, mz, x, y, z);
-          const bool F = in_frustum(Vw, x, y, z, prm.near_z);
-          const float d = cam_distance(Vw, mx, my, mz, ex, ey, ez);
-          float q;
-          const float a2 = attenuated_pre(d, dmax_from_key(dmax_key[v]), Vw.s_v, alpha, den, q);
-          if (F && lod_kept(Vw, a2, i)) {
-            if (!have_cov) {
-              const float s0 = cexp(sc.log_scale[i]), s1 = cexp(sc.log_scale[n + i]), s2 = cexp(sc.log_scale[2 * n + i]);
-              float Rm[9], w_, x_, y_, z_, rn;
-              quat_rot(sc.quat[i], sc.quat[n + i], sc.quat[2 * n + i], sc.quat[3 * n + i], Rm, w_, x_, y_, z_, rn);
-              cov3(Rm, s0, s1, s2, S);
-              have_cov = true;
-            }
-            if (Vw.cam_lead != geo_lead) {
-              pok = ewa(Vw, x, y, z, S, prm.dilation, P);
-              geo_lead = Vw.cam_lead;
-            }
-            if (pok) {
-              R = true;
-              if (kWriteRecords) {
-                const int64_t f = (int64_t)v * n + i;
-                rec[kRecQuads * f] = make_float4(P.u, P.v, a2, P.rad);
-                rec[kRecQuads * f + 1] = make_float4(P.A, P.B, P.C, 0.f);
-                // Depth, tile rectangle and tiles touched: the fourth quad, so the record is
-                // written whole (no partial 64-byte segments, no separate scattered planes).
-                rec[kRecQuads * f + 3] =
-                    make_float4(z, __uint_as_float((uint32_t)P.x0 | ((uint32_t)P.x1 << 16)),
-                                __uint_as_float((uint32_t)P.y0 | ((uint32_t)P.y1 << 16)),
-                                __uint_as_float((uint32_t)((P.x1 - P.x0) * (P.y1 - P.y0))));
-              }
-            }
+        if (kept) {
+          const int64_t f = (int64_t)v * n + i;
+          const float a2 = alpha[f];
+          if (Vw.cam_lead != geo_lead) {
+            float x, y;
+            to_camera(Vw, mx, my, mz, x, y, z);
+            pok = ewa(Vw, x, y, z, S, prm.dilation, P);
+            geo_lead = Vw.cam_lead;
+          }
+          R = pok;
+          if (R) {
+            rec[kRecQuads * f] = make_float4(P.u, P.v, a2, P.rad);
+            rec[kRecQuads * f + 1] = make_float4(P.A, P.B, P.C, 0.f);
+            // Depth, tile rectangle and tiles touched: the fourth quad, so the record is
+            // written whole (no partial 64-byte segments, no separate scattered planes).
+            rec[kRecQuads * f + 3] =
+                make_float4(z, __uint_as_float((uint32_t)P.x0 | ((uint32_t)P.x1 << 16)),
+                            __uint_as_float((uint32_t)P.y0 | ((uint32_t)P.y1 << 16)),
+                            __uint_as_float((uint32_t)((P.x1 - P.x0) * (P.y1 - P.y0))));
           }
         }
         rmask |= (R ? 1u : 0u) << vv;
         const uint64_t bR = ballot64(R);
         if (lane_id() == 0 && bR) atomicAdd(&scnt[v], (uint32_t)__popcll(bR));
       }
-      if (kWriteRecords && rmask) {
-        // Plane-major coefficients are gathered once into registers; a packed per-Gaussian
-        // block is instead re-read for every rendering view (cache hits after the first one,
-        // float4 chunks when 3K % 4 == 0), which keeps the kernel at half the registers.
+      if (rmask) {
+        // Plane-major coefficients are gathered once into registers (read again for every rendering
+        // view, whose lanes differ, they cost 456 us instead of 245 for 16 views of 2M); a packed
+        // per-Gaussian block is instead re-read for every rendering view (cache hits after the
+        // first one, float4 chunks when 3K % 4 == 0), which keeps the kernel at half the registers.
         // Either way each channel accumulates in coefficient order.
         float shc[kPacked ? 1 : 3 * K];
         if constexpr (!kPacked) {
+          int64_t at = i;
+          asm volatile("" : "+v"(at));   // (keeps the 3K addresses from being formed ahead of the loop)
 #pragma unroll
-          for (int k = 0; k < 3 * K; ++k) shc[k] = sc.sh[(int64_t)k * n + i];
+          for (int k = 0; k < 3 * K; ++k) shc[k] = sc.sh[(int64_t)k * n + at];
         }
         uint32_t m = rmask;
         while (m) {
@@ -546,20 +892,20 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, Blk b, uint32
           }
           }
           rec[kRecQuads * f + 2] = make_float4(col[0], col[1], col[2], 0.f);
-          flags_out[f] = cfl;
+          flags[f] = cfl;
         }
       }
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < V; j += kBlock) cpart[((int64_t)b.id * V + j) * 4 + 2] = scnt[j];
+  for (int j = threadIdx.x; j < V; j += kBlock) a.cpart[((int64_t)b.id * V + j) * 4 + 2] = scnt[j];
 }
 
-// Plane-major coefficients (or no records).
-template <int DEG, bool kWriteRecords>
+// Plane-major coefficients.
+template <int DEG>
 __global__ __launch_bounds__(kBlock) void k_project(ProjectArgs a) {
   extern __shared__ uint32_t sdyn[];
-  project_body<DEG, kWriteRecords, false>(a, grid_blk(), sdyn);
+  project_body<DEG, false, true>(a, grid_blk(), sdyn);
 }
 
 // Packed coefficients: fits 128 registers, so four waves per SIMD hide the gather latency.
@@ -745,8 +1091,12 @@ hipError_t launch_lod_select(const clod_scene& sc, DevView* vinfo, int V, clod_p
   return e;
 }
 
+// Blocks of the per-Gaussian passes: four Gaussians per thread and more where the scene fills the
+// chip that way, one per thread in small scenes.
 int proj_blocks(int64_t n) {
-  int64_t g = (n + 4 * kBlock - 1) / (4 * kBlock);
+  int64_t g = (n + 4 * kBlock - 1) / (4 * kBlock), least = (n + kBlock - 1) / kBlock;
+  if (least > 512) least = 512;
+  if (g < least) g = least;
   if (g < 1) g = 1;
   if (g > kMaxProjBlocks) g = kMaxProjBlocks;
   return (int)g;
@@ -774,7 +1124,7 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, const Sin
   return out.put(st);
 }
 
-static Stage fold_stage(const unsigned long long* kpart, const uint32_t* cpart, int G, int V,
+static Stage fold_stage(const uint32_t* kpart, const uint32_t* cpart, int G, int V,
                         unsigned long long* dmax_key, unsigned long long* counts, int64_t* counts_dev, int64_t n,
                         float* eta_dev, uint32_t* clear, uint32_t clear_words) {
   Stage st{};
@@ -786,7 +1136,7 @@ static Stage fold_stage(const unsigned long long* kpart, const uint32_t* cpart, 
 }
 
 hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V, float near_z,
-                              unsigned long long* kpart, unsigned long long* dmax_key, uint32_t* clear,
+                              uint32_t* kpart, unsigned long long* dmax_key, uint32_t* clear,
                               uint32_t clear_words, const Sink& out) {
   if (sc.n == 0) return launch_fill_u32((uint32_t*)dmax_key, 0u, 2 * (int64_t)V, out);
   const int G = proj_blocks(sc.n);
@@ -794,6 +1144,7 @@ hipError_t launch_frustum_max(const clod_scene& sc, const DevView* vinfo, int V,
   st.kind = kStFrustumMax;
   st.items = (uint32_t)G;
   st.block = kBlock;
+  st.lds = (uint32_t)(kCamWords * V * sizeof(uint32_t));
   st.a.frustum = FrustumArgs{sc.mean, sc.n, vinfo, V, near_z, kpart};
   hipError_t e = out.put(st);
   if (e == hipSuccess)
@@ -818,7 +1169,7 @@ static hipError_t project_impl(const clod_scene& sc, const DevView* vinfo, int V
   c.kind = kStClassify;
   c.items = (uint32_t)G;
   c.block = kBlock;
-  c.lds = (uint32_t)(3 * V * sizeof(uint32_t));
+  c.lds = (uint32_t)((kWrite ? kClassifyWords : kCountWords) * V * sizeof(uint32_t));
   c.a.classify = ClassifyArgs{sc, vinfo, V, kWrite ? 1 : 0, prm, dmax_key, cpart, flags, alpha, list, lcount};
   hipError_t e = out.put(c);
   if (e != hipSuccess) return e;
@@ -827,8 +1178,8 @@ static hipError_t project_impl(const clod_scene& sc, const DevView* vinfo, int V
   p.kind = kStProject;
   p.items = (uint32_t)G;
   p.block = kBlock;
-  p.lds = (uint32_t)((G + V) * sizeof(uint32_t));
-  p.a.project = ProjectArgs{sc, vinfo, V, prm, dmax_key, cpart, list, lcount, flags, rec, kWrite ? 1 : 0,
+  p.lds = (uint32_t)((kSegWords + (kWrite ? 1 : kCountWords) * V) * sizeof(uint32_t));
+  p.a.project = ProjectArgs{sc, vinfo, V, prm, dmax_key, cpart, list, lcount, flags, alpha, rec, kWrite ? 1 : 0,
                             kWrite && sc.sh_packed != nullptr ? 1 : 0};
   e = out.put(p);
   if (e != hipSuccess) return e;
@@ -858,21 +1209,22 @@ hipError_t launch_project_stage(const Stage& st, hipStream_t s) {
   switch (st.kind) {
     case kStViewSetup: hipLaunchKernelGGL(k_view_setup, g, blk, 0, s, st.a.view_setup); break;
     case kStFill: hipLaunchKernelGGL(k_fill_u32, g, blk, 0, s, st.a.fill); break;
-    case kStFrustumMax: hipLaunchKernelGGL(k_frustum_max, g, blk, 0, s, st.a.frustum); break;
+    case kStFrustumMax: hipLaunchKernelGGL(k_frustum_max, g, blk, st.lds, s, st.a.frustum); break;
     case kStFold: hipLaunchKernelGGL(k_reduce_partials, g, blk, 0, s, st.a.fold); break;
     case kStClassify:
-      if (st.a.classify.write) hipLaunchKernelGGL(k_classify<true>, g, blk, st.lds, s, st.a.classify);
-      else hipLaunchKernelGGL(k_classify<false>, g, blk, st.lds, s, st.a.classify);
+      if (st.a.classify.write) hipLaunchKernelGGL(k_classify, g, blk, st.lds, s, st.a.classify);
+      else hipLaunchKernelGGL(k_count, g, blk, st.lds, s, st.a.classify);
       break;
     case kStProject: {
       const ProjectArgs& a = st.a.project;
-      auto kern = a.packed ? k_project_packed<3> : (a.write ? k_project<3, true> : k_project<3, false>);
+      auto kern = a.packed ? k_project_packed<3> : k_project<3>;
       switch (a.sc.sh_degree) {
-        case 0: kern = a.packed ? k_project_packed<0> : (a.write ? k_project<0, true> : k_project<0, false>); break;
-        case 1: kern = a.packed ? k_project_packed<1> : (a.write ? k_project<1, true> : k_project<1, false>); break;
-        case 2: kern = a.packed ? k_project_packed<2> : (a.write ? k_project<2, true> : k_project<2, false>); break;
+        case 0: kern = a.packed ? k_project_packed<0> : k_project<0>; break;
+        case 1: kern = a.packed ? k_project_packed<1> : k_project<1>; break;
+        case 2: kern = a.packed ? k_project_packed<2> : k_project<2>; break;
         default: break;
       }
+      if (!a.write) kern = k_count_rest;
       hipLaunchKernelGGL(kern, g, blk, st.lds, s, a);
       break;
     }

@@ -230,7 +230,7 @@ union SrvLds {
   DownsweepLds down;
   OffsetsLds offsets;
   EmitLds emit;
-  uint32_t words[kMaxProjBlocks + 3 * kSrvMaxViews];   // classify: 3 V words; projection: G + V
+  uint32_t words[kSegWords + kClassifyWords * kSrvMaxViews];   // classify: kClassifyWords V words; projection: kSegWords + V
 };
 
 // Arguments read from LDS into wave-uniform registers.
@@ -251,22 +251,22 @@ __device__ bool srv_run(int32_t kind, const Stage& st, Blk b, SrvLds& U) {
   switch (kind) {
     case kStViewSetup: view_setup_body(uniform_copy(st.a.view_setup), b); return true;
     case kStFill: fill_body(uniform_copy(st.a.fill), b); return true;
-    case kStFrustumMax: frustum_max_body(uniform_copy(st.a.frustum), b); return true;
+    case kStFrustumMax: frustum_max_body(uniform_copy(st.a.frustum), b, U.words); return true;
     case kStFold: fold_body(uniform_copy(st.a.fold), b); return true;
     case kStClassify: {
       const ClassifyArgs a = uniform_copy(st.a.classify);
-      if (a.write) classify_body<true>(a, b, U.words);
-      else classify_body<false>(a, b, U.words);
+      if (!a.write) return false;
+      classify_body<false>(a, b, U.words);
       return true;
     }
     case kStProject: {
       const ProjectArgs a = uniform_copy(st.a.project);
       if (!a.packed || !a.write) return false;
       switch (a.sc.sh_degree) {
-        case 0: project_body<0, true, true>(a, b, U.words); break;
-        case 1: project_body<1, true, true>(a, b, U.words); break;
-        case 2: project_body<2, true, true>(a, b, U.words); break;
-        default: project_body<3, true, true>(a, b, U.words); break;
+        case 0: project_body<0, true, false>(a, b, U.words); break;
+        case 1: project_body<1, true, false>(a, b, U.words); break;
+        case 2: project_body<2, true, false>(a, b, U.words); break;
+        default: project_body<3, true, false>(a, b, U.words); break;
       }
       return true;
     }
