@@ -176,22 +176,14 @@ int sorted_buffer(const Layout& L);        // ping-pong buffer (0/1) holding the
 // ----------------------------------------------------------------------------------------
 __device__ __forceinline__ float fmaf_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
-// Float to int32 as the hardware converts (saturating; NaN gives 0).  A C++ conversion of a
-// value outside the int32 range is undefined, which matters where lanes outside the live set
-// evaluate the exponential on arbitrary arguments (their results are discarded).
-__device__ __forceinline__ int cvt_i32_sat(float k) {
-  int r;
-  asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(k));
-  return r;
-}
-
 // Contract exponential: Cody-Waite reduction with a 16-bit head of ln 2, degree-7 Taylor
 // polynomial (1/j! rounded to binary32) in Horner form, scale by 2^k; zero below -86.
 // The contract exponential for x in [-86, 88] (no range or NaN handling): cexp below adds
-// those; the blend calls this directly on arguments it has already bounded (kAnyArg: or on any
-// argument, for lanes whose result it discards; the result is then unspecified, but no
-// operation is undefined, and inside the range it is the same).
-template <bool kAnyArg = false>
+// those; the blend calls this directly on arguments it has already bounded, or on any argument for
+// lanes whose result it discards (the result is then unspecified, but no operation is undefined).
+// The integer k is rounded and shifted into the exponent by the addition of 1.5 * 2^23, whose low
+// bits then hold it: an addition, a subtraction and a shift-and-add (8 issue cycles) instead of
+// v_rndne, v_cvt and v_ldexp (12), with the same result.
 __device__ __forceinline__ float cexp_core(float x) {
   constexpr float kL2E = 1.44269502162933349609375f;          // fl(1/ln 2)
   constexpr float kLn2Hi = 0.693145751953125f;                // floor(ln2 * 2^16) / 2^16
@@ -201,7 +193,9 @@ __device__ __forceinline__ float cexp_core(float x) {
   constexpr float c5 = 8.3333337679505348205566406250e-03f;       // fl(1/120)
   constexpr float c4 = 4.1666667908430099487304687500e-02f;       // fl(1/24)
   constexpr float c3 = 1.6666667163372039794921875000e-01f;       // fl(1/6)
-  float k = __builtin_rintf(x * kL2E);
+  constexpr float kRound = 12582912.0f;   // 1.5 * 2^23
+  const float t = x * kL2E + kRound;
+  const float k = t - kRound;
   float r = fmaf_(-k, kLn2Hi, x);
   r = fmaf_(-k, kLn2Lo, r);
   float p = c7;
@@ -213,7 +207,7 @@ __device__ __forceinline__ float cexp_core(float x) {
   p = fmaf_(p, r, 1.0f);
   p = fmaf_(p, r, 1.0f);
   // p * 2^k, exact for every k that cexp's clamped range produces (the result stays normal).
-  return __builtin_amdgcn_ldexpf(p, kAnyArg ? cvt_i32_sat(k) : (int)k);
+  return __uint_as_float(__float_as_uint(p) + (__float_as_uint(t) << 23));
 }
 
 __device__ __forceinline__ float cexp(float x) {
@@ -275,7 +269,8 @@ __device__ __forceinline__ void to_camera(const View& V, float mx, float my, flo
 
 template <class View>
 __device__ __forceinline__ bool in_frustum(const View& V, float x, float y, float z, float near_z) {
-  return (z > near_z) & (fabsf(x) <= V.limx * z) & (fabsf(y) <= V.limy * z);   // (no branches)
+  const bool front = z > near_z, in_x = fabsf(x) <= V.limx * z, in_y = fabsf(y) <= V.limy * z;
+  return front & in_x & in_y;   // (no branches)
 }
 
 // The same as a lane mask of the wave (each comparison writes its mask to scalar registers, where
@@ -520,12 +515,11 @@ __device__ __forceinline__ float dpp_read(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, kRowMask, 0xF, false));
 }
 
-// Totals over the wave of eight per-lane values at once: lanes 8g .. 8g+7 end with the total of
-// v[g].  Each exchange halves the number of live values: permlane32 swaps (halves of the wave),
-// permlane16 swaps (rows of a half), a rotation by 8 within rows, then three DPP steps within
-// groups of 8 lanes.  18 instructions instead of eight separate reductions.  Every lane of the
-// wave must be active.
-__device__ __forceinline__ float wave_sum8(const float (&v)[8]) {
+// Sums of eight per-lane values over the eight rows of eight lanes (lanes of equal lane % 8), at
+// once: lane 8 g + e ends with the sum of v[g] over the lanes e, e + 8, ..., e + 56.  Each exchange
+// halves the number of live values: permlane32 swaps (halves of the wave), permlane16 swaps (rows
+// of a half), a rotation by 8 within rows.  Every lane of the wave must be active.
+__device__ __forceinline__ float row_sum8(const float (&v)[8]) {
   auto swap32 = [](float a, float b) {   // [a_lo + a_hi | b_lo + b_hi]
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -538,25 +532,7 @@ __device__ __forceinline__ float wave_sum8(const float (&v)[8]) {
   const float s0 = swap16(r0, r2), s1 = swap16(r1, r3);   // rows: (v0 v2 v4 v6), (v1 v3 v5 v7)
   const bool hi8 = (__lane_id() & 8u) != 0u;
   const float keep = hi8 ? s1 : s0, send = hi8 ? s0 : s1;
-  float u = keep + dpp_read<0x128, 0xF>(send);           // row_ror:8; lanes 8g..8g+7 hold v[g]
-  u += dpp_read<0x141, 0xF>(u);                          // row_half_mirror
-  u += dpp_read<0x4E, 0xF>(u);                           // quad_perm (2, 3, 0, 1)
-  u += dpp_read<0xB1, 0xF>(u);                           // quad_perm (1, 0, 3, 2)
-  return u;
-}
-
-// Sum over the 64 lanes of a wave with DPP lane moves fused into the adds (no LDS traffic):
-// quad swaps give quad sums, the half-row and row mirrors give row (16-lane) sums, and the
-// two row broadcasts fold rows 0-2 into row 3.  Returns the total as a wave-uniform value.
-// Every lane of the wave must be active.
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-  v += dpp_read<0xB1, 0xF>(v);    // quad_perm (1, 0, 3, 2)
-  v += dpp_read<0x4E, 0xF>(v);    // quad_perm (2, 3, 0, 1)
-  v += dpp_read<0x141, 0xF>(v);   // row_half_mirror
-  v += dpp_read<0x140, 0xF>(v);   // row_mirror
-  v += dpp_read<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-  v += dpp_read<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+  return keep + dpp_read<0x128, 0xF>(send);              // row_ror:8
 }
 
 // Weight of Eq. (5): w_s = (1 - 0.5 s_v / max(s_v))^2.

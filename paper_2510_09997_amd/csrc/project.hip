@@ -397,7 +397,7 @@ __device__ __forceinline__ void classify_body(const ClassifyArgs& a, Blk b, uint
           }
           const float u = dn[k] * s_v, num = u * u;
           const float q = div_normal(num, den[k], rden[k]);
-          const float a2 = alpha[k] * (q > 86.0f ? 0.0f : cexp_core<true>(-q));
+          const float a2 = alpha[k] * (q > 86.0f ? 0.0f : cexp_core(-q));
           special |= ballot64(!in_exponents<60>(num)) | ballot64(!in_exponents<60>(den[k])) | (ballot64(d[k] == dmax) & F[k]);
           const uint64_t M = (Vw.budget > 0 ? ballot64(lod_key(a2, i) >= Vw.mkey) : ballot64(a2 > Vw.tau_sv)) & vm[k];
           const uint32_t fl = (__builtin_amdgcn_inverse_ballot_w64(F[k]) ? 1u : 0u) |
