@@ -232,8 +232,8 @@ clod_status clod_lod_count_noalloc(const clod_scene *scene, int32_t n_views, con
    Writes loss_dev (device float [n_views]), dL_drgb (the gradient of L_v with respect to the
    view's rgb; sign(0) = 0) and dL_deta_dev (device float [n_views], nullable) = w_s lambda_reg
    dL_reg/deta.  lambda_dssim in [0, 1]; when it is > 0, ssim_scratch is a device buffer of at
-   least 36 bytes per pixel of the batch (per-pixel SSIM derivatives); with 0 it may be NULL and
-   L_render = L1. */
+   least 36 bytes per pixel of the batch (room for per-pixel SSIM derivatives; its contents are
+   unspecified afterwards); with 0 it may be NULL and L_render = L1. */
 clod_status clod_loss(const clod_batch *batch, const float *rgb, const float *target,
                       float s_max, float lambda_reg, float lambda_dssim, float *ssim_scratch,
                       size_t ssim_scratch_bytes, float *loss_dev, float *dL_drgb,

@@ -131,7 +131,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.gdmax = o; o = align256(o + (size_t)V * 4);
   L.loss_acc = o; o = align256(o + (size_t)V * 4);
   L.ssim_acc = o; o = align256(o + (size_t)V * 4);
-  L.loss_part = o; o = align256(o + ((size_t)tiles_total * 3 + (size_t)pixels_total * 3 / kLossChunk + V) * 4);
+  L.loss_part = o; o = align256(o + ((size_t)tiles_total * 6 + (size_t)pixels_total * 3 / kLossChunk + V) * 4);
   L.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
   L.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
   L.gpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
@@ -226,7 +226,8 @@ static clod_status prepare(const clod_batch* b, bool need_full_ws, Ctx& cx) {
   for (int v = 0; v < b->n_views; ++v) any_budget = any_budget || b->views_host[v].budget > 0;
   cx.L = make_layout(n, b->n_views, totals, any_budget);
   for (int v = 0; v < b->n_views; ++v)
-    cx.L.ssim_regions += (uint32_t)(((cx.hv[v].tiles_x + 1) / 2) * ((cx.hv[v].tiles_y + 1) / 2));
+    cx.L.ssim_regions += (uint32_t)(((cx.hv[v].width + kSsimRegionW - 1) / kSsimRegionW) *
+                                    ((cx.hv[v].height + kSsimRegionH - 1) / kSsimRegionH));
   // The per-view area and the projection work list precede the per-(view, Gaussian) planes.
   const size_t need = need_full_ws ? cx.L.total : cx.L.flags;
   if (b->ws_bytes < need) return fail(CLOD_E_ARG, "ws_bytes %zu < required %zu", b->ws_bytes, need);
@@ -601,7 +602,7 @@ clod_status clod_loss(const clod_batch* batch, const float* rgb, const float* ta
   }
   for (int v = 0; v < batch->n_views; ++v)
     if (batch->views_host[v].s_v > s_max) return fail(CLOD_E_ARG, "view %d: s_v exceeds s_max", v);
-  HIP_TRY(launch_loss(cx.L, batch->ws, batch->n, rgb, target, s_max, lambda_reg, lambda_dssim, ssim_scratch,
+  HIP_TRY(launch_loss(cx.L, batch->ws, batch->n, rgb, target, s_max, lambda_reg, lambda_dssim,
                       loss_dev, dL_drgb, dL_deta_dev, cx.loss_blocks, (hipStream_t)stream),
           "loss");
   return CLOD_OK;

@@ -10,6 +10,7 @@
 namespace clod {
 
 constexpr int kTile = 16;                  // 16x16-pixel tiles
+constexpr int kSsimRegionW = 54, kSsimRegionH = 22;   // pixels of an SSIM block (no more regions than tiles)
 constexpr int kBlock = 256;                // threads per workgroup (4 wave64)
 // One 64-byte record per (view, Gaussian), so the blend's gather of an entry touches one
 // aligned 64-byte segment: (u, v, alpha'', radius), (conic A, B, C, 0), (r, g, b, 0), unused.
@@ -55,7 +56,7 @@ struct DevView {
   float fx, fy, cx, cy;
   float s_v, limx, limy, tau_sv;
   int32_t width, height, tiles_x, tiles_y;
-  uint32_t tile_base, pix_base, loss_block_base, rgn_base;   // rgn_base: first 32 x 32 SSIM region
+  uint32_t tile_base, pix_base, loss_block_base, rgn_base;   // rgn_base: first SSIM region
   uint32_t row_base;             // first tile row in the batch
   int32_t ftiles_x, ftiles_y;    // tiles of the frame (the view's own when it is not a viewport)
   int32_t vx, vy;                // viewport origin in the frame, pixels (multiples of 16)
@@ -137,7 +138,7 @@ struct Layout {
   int32_t V = 0;
   int64_t VN = 0;
   uint32_t tiles_total = 0;   // sum over views of tiles_x * tiles_y
-  uint32_t ssim_regions = 0;  // sum over views of ceil(tiles_x / 2) * ceil(tiles_y / 2)
+  uint32_t ssim_regions = 0;  // sum over views of their SSIM regions
   int64_t pixels_total = 0;
   int32_t scan_blocks = 0;
   bool any_budget = false;    // some view selects by budget (allocates the select histograms)
@@ -782,7 +783,7 @@ hipError_t launch_gauss_bwd(const clod_scene& sc, const Layout& L, void* ws, clo
                             const float* dL_deta, int accumulate, const clod_scene_grad& g,
                             hipStream_t s);
 hipError_t launch_loss(const Layout& L, void* ws, int64_t n, const float* rgb, const float* target,
-                       float s_max, float lambda_reg, float lambda_dssim, float* ssim_scratch, float* loss,
+                       float s_max, float lambda_reg, float lambda_dssim, float* loss,
                        float* dL_drgb, float* dL_deta, uint32_t loss_blocks, hipStream_t s);
 // Persistent server (server.hip): jobs are forward-render Programs.
 constexpr int kSrvSlots = 16;      // jobs in flight
@@ -801,7 +802,6 @@ int server_stage_times(Server* S, int64_t seq, int64_t* ns, int32_t* kinds, int3
 hipError_t server_stop(Server* S, int32_t* status);
 
 hipError_t launch_ssim(const Layout& L, void* ws, const float* rgb, const float* target, float lambda,
-                       float s_max, float* coef, float* ssim_part, float* dL_drgb, hipStream_t s);
-constexpr int kSsimRegion = 32;   // output edge of one SSIM block (2 x 2 tiles)
+                       float s_max, float* part, float* dL_drgb, hipStream_t s);
 
 }  // namespace clod

@@ -1,6 +1,6 @@
 // Training loss of Sec. 3.3: L_render = (1 - lambda_dssim) L1 + lambda_dssim (1 - SSIM) (the 3DGS
-// rendering loss; the SSIM part is in ssim.hip), per view the mean absolute error and its
-// gradient (1 - lambda_dssim) w_s sign(rgb - target) / (3 H W), the point-count regulariser of
+// rendering loss; with lambda_dssim > 0 both parts and their gradient come from ssim.hip), per view
+// the mean absolute error and its gradient w_s sign(rgb - target) / (3 H W), the point-count regulariser of
 // Eq. (4) on eta = n_mask / n with target s_v^-1.5 (Eq. 3), and the weighted total of Eq. (5).
 #include "clod_internal.h"
 
@@ -11,7 +11,7 @@ namespace clod {
 __global__ __launch_bounds__(kBlock) void k_loss_l1(const DevView* __restrict__ views, int V,
                                                     const float* __restrict__ rgb,
                                                     const float* __restrict__ target, float s_max,
-                                                    float l1_weight, float* __restrict__ dL_drgb,
+                                                    float* __restrict__ dL_drgb,
                                                     float* __restrict__ l1_part) {
   __shared__ float sred[4];
   int lo = 0, hi = V - 1;
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kBlock) void k_loss_l1(const DevView* __restrict__ 
   const int64_t base = 3ll * Vw.pix_base;
   const int64_t j0 = (int64_t)(blockIdx.x - Vw.loss_block_base) * kLossChunk;
   const float ws = w_s_weight(Vw.s_v, s_max);
-  const float scale = l1_weight * ws / (float)cnt;
+  const float scale = ws / (float)cnt;
   float s = 0.f;
   auto one = [&](float r, float t, float& g) {
     const float diff = r - t;
@@ -72,31 +72,51 @@ __global__ __launch_bounds__(kBlock) void k_loss_l1(const DevView* __restrict__ 
   if (threadIdx.x == 0) l1_part[blockIdx.x] = sred[0] + sred[1] + sred[2] + sred[3];
 }
 
-// Block v folds view v's partial sums: its L1 blocks and, with the D-SSIM term, the three
-// channel partials of each of its SSIM regions.
-__global__ __launch_bounds__(kBlock) void k_loss_reduce(const DevView* __restrict__ views, int V,
-                                                        uint32_t loss_blocks, const float* __restrict__ l1_part,
-                                                        const float* __restrict__ ssim_part, int with_ssim,
-                                                        uint32_t ssim_regions,
-                                                        float* __restrict__ l1_acc, float* __restrict__ ssim_acc) {
-  __shared__ float sm[2][4];
+// Block v folds view v's partial sums: its L1 blocks or, with the D-SSIM term, the (SSIM, L1) pairs
+// of the three channels of its SSIM regions.  A thousand threads with four loads in flight each: the
+// block runs alone, so its time is their latency (256 threads, one load at a time: 16 us for two
+// 1080p images).
+constexpr int kFoldThreads = 1024;
+__global__ __launch_bounds__(kFoldThreads) void k_loss_reduce(const DevView* __restrict__ views, int V,
+                                                              uint32_t loss_blocks, const float* __restrict__ l1_part,
+                                                              const float2* __restrict__ ssim_part, int with_ssim,
+                                                              uint32_t ssim_regions, float* __restrict__ l1_acc,
+                                                              float* __restrict__ ssim_acc) {
+  __shared__ float sm[2][kFoldThreads / 64];
   const int v = blockIdx.x;
   const DevView& Vw = views[v];
-  const uint32_t b0 = Vw.loss_block_base;
-  const uint32_t b1 = v + 1 < V ? views[v + 1].loss_block_base : loss_blocks;
   float a = 0.f, s = 0.f;
-  for (uint32_t j = b0 + threadIdx.x; j < b1; j += kBlock) a += l1_part[j];
   if (with_ssim) {
     const int64_t t0 = 3ll * Vw.rgn_base, t1 = 3ll * (v + 1 < V ? views[v + 1].rgn_base : ssim_regions);
-    for (int64_t j = t0 + threadIdx.x; j < t1; j += kBlock) s += ssim_part[j];
+    for (int64_t j = t0 + threadIdx.x; j < t1; j += 4 * kFoldThreads) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t q = j + k * kFoldThreads;
+        const float2 p = ssim_part[q < t1 ? q : t1 - 1];
+        s += q < t1 ? p.x : 0.f;
+        a += q < t1 ? p.y : 0.f;
+      }
+    }
+  } else {
+    const int64_t b0 = Vw.loss_block_base, b1 = v + 1 < V ? views[v + 1].loss_block_base : loss_blocks;
+    for (int64_t j = b0 + threadIdx.x; j < b1; j += 4 * kFoldThreads) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t q = j + k * kFoldThreads;
+        const float p = l1_part[q < b1 ? q : b1 - 1];
+        a += q < b1 ? p : 0.f;
+      }
+    }
   }
   a = wave_sum(a);
   s = wave_sum(s);
   if (lane_id() == 0) { sm[0][threadIdx.x >> 6] = a; sm[1][threadIdx.x >> 6] = s; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    l1_acc[v] = sm[0][0] + sm[0][1] + sm[0][2] + sm[0][3];
-    ssim_acc[v] = sm[1][0] + sm[1][1] + sm[1][2] + sm[1][3];
+    float ta = 0.f, ts = 0.f;
+    for (int w = 0; w < kFoldThreads / 64; ++w) { ta += sm[0][w]; ts += sm[1][w]; }
+    l1_acc[v] = ta;
+    ssim_acc[v] = ts;
   }
 }
 
@@ -123,23 +143,22 @@ __global__ void k_loss_scalars(const DevView* __restrict__ views, int V, int64_t
 }
 
 hipError_t launch_loss(const Layout& L, void* ws, int64_t n, const float* rgb, const float* target,
-                       float s_max, float lambda_reg, float lambda_dssim, float* ssim_scratch, float* loss,
+                       float s_max, float lambda_reg, float lambda_dssim, float* loss,
                        float* dL_drgb, float* dL_deta, uint32_t loss_blocks, hipStream_t s) {
   char* w = (char*)ws;
   float* acc = (float*)(w + L.loss_acc);
   float* sacc = (float*)(w + L.ssim_acc);
-  float* spart = (float*)(w + L.loss_part);                   // [regions][3] SSIM partials
-  float* lpart = spart + 3 * (int64_t)L.tiles_total;          // [loss blocks] L1 partials
+  float* spart = (float*)(w + L.loss_part);                   // [regions][3] (SSIM, L1) partials
+  float* lpart = spart + 6 * (int64_t)L.tiles_total;          // [loss blocks] L1 partials
   const DevView* views = (const DevView*)(w + L.vinfo);
-  if (loss_blocks > 0)
-    hipLaunchKernelGGL(k_loss_l1, dim3(loss_blocks), dim3(kBlock), 0, s, views, L.V, rgb, target, s_max,
-                       1.0f - lambda_dssim, dL_drgb, lpart);
-  if (lambda_dssim > 0.f) {
-    hipError_t e = launch_ssim(L, ws, rgb, target, lambda_dssim, s_max, ssim_scratch, spart, dL_drgb, s);
+  if (lambda_dssim > 0.f) {   // the L1 part in the same pass
+    hipError_t e = launch_ssim(L, ws, rgb, target, lambda_dssim, s_max, spart, dL_drgb, s);
     if (e != hipSuccess) return e;
+  } else if (loss_blocks > 0) {
+    hipLaunchKernelGGL(k_loss_l1, dim3(loss_blocks), dim3(kBlock), 0, s, views, L.V, rgb, target, s_max, dL_drgb, lpart);
   }
-  hipLaunchKernelGGL(k_loss_reduce, dim3(L.V), dim3(kBlock), 0, s, views, L.V, loss_blocks, (const float*)lpart,
-                     (const float*)spart, lambda_dssim > 0.f ? 1 : 0, L.ssim_regions, acc, sacc);
+  hipLaunchKernelGGL(k_loss_reduce, dim3(L.V), dim3(kFoldThreads), 0, s, views, L.V, loss_blocks, (const float*)lpart,
+                     (const float2*)spart, lambda_dssim > 0.f ? 1 : 0, L.ssim_regions, acc, sacc);
   hipLaunchKernelGGL(k_loss_scalars, dim3((L.V + 63) / 64), dim3(64), 0, s, views, L.V, n,
                      (const unsigned long long*)(w + L.counts), (const float*)acc, (const float*)sacc, s_max,
                      lambda_reg, lambda_dssim, loss, dL_deta);

@@ -97,7 +97,8 @@ __device__ __forceinline__ void view_setup_body(const ViewSetupArgs& a, Blk b) {
     };
     const uint32_t px = (uint32_t)(cv.width * cv.height);
     d.tile_base = before((uint32_t)(d.tiles_x * d.tiles_y), tile_base);
-    d.rgn_base = before((uint32_t)(((d.tiles_x + 1) / 2) * ((d.tiles_y + 1) / 2)), rgn_base);
+    d.rgn_base = before((uint32_t)(((cv.width + kSsimRegionW - 1) / kSsimRegionW) *
+                                   ((cv.height + kSsimRegionH - 1) / kSsimRegionH)), rgn_base);
     d.pix_base = before(px, pix_base);
     d.loss_block_base = before((3u * px + kLossChunk - 1) / kLossChunk, loss_base);
     d.row_base = before((uint32_t)d.tiles_y, row_base);
