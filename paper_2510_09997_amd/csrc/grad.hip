@@ -5,13 +5,13 @@
 // The normalised distance also depends on the frustum maximum (Sec. 3.2); its partial is
 // reduced per view here and applied to the argmax Gaussian by k_dmax_fix.
 //
-// One thread per Gaussian loops over the batch's views and writes each gradient plane once
-// (coalesced, no atomics): k_gauss_bwd everything but the SH colour, k_sh_bwd the SH
-// coefficients and the view-direction part of the mean's gradient.  Forward intermediates of rendered (view, Gaussian) pairs are
-// recomputed with the contract arithmetic of the projection.  The Eq. (2) adjoint, which the
-// point-count term needs for every (view, Gaussian), uses the hardware reciprocal, square root
-// and exp2 instead (relative errors of a few 1e-7, far inside the gradients' 1e-4 tolerance),
-// with the per-Gaussian and per-view factors hoisted out of the view loop.
+// One thread per Gaussian writes each gradient plane once (coalesced, no atomics): k_gauss_bwd
+// everything but the SH colour, k_sh_bwd the SH coefficients and the view-direction part of the
+// mean's gradient.  Forward intermediates of rendered (view, Gaussian) pairs are recomputed with the
+// contract arithmetic of the projection.  The Eq. (2) adjoint, which the point-count term needs for
+// every (view, Gaussian), uses the hardware reciprocal and exp2 instead (relative errors of a few
+// 1e-7, far inside the gradients' 1e-4 tolerance), with the per-Gaussian and per-view factors
+// hoisted out of the view loop.
 
 #include "clod_internal.h"
 
@@ -19,148 +19,187 @@ namespace clod {
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
+// Sum over the 64 lanes of a wave with DPP lane moves fused into the adds: quad swaps give quad
+// sums, the half-row and row mirrors row (16-lane) sums, and the two row broadcasts fold rows 0-2
+// into row 3.  The total is in lane 63.  Every lane of the wave must be active.
+__device__ __forceinline__ float wave_total63(float v) {
+  v += dpp_read<0xB1, 0xF>(v);    // quad_perm (1, 0, 3, 2)
+  v += dpp_read<0x4E, 0xF>(v);    // quad_perm (2, 3, 0, 1)
+  v += dpp_read<0x141, 0xF>(v);   // row_half_mirror
+  v += dpp_read<0x140, 0xF>(v);   // row_mirror
+  v += dpp_read<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_read<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Eq. (2): alpha'' = alpha exp(-q), q = d^2 k / den with k = (s_v / d_max)^2 and den the decay's
+// denominator.  With t = dL/dalpha'' alpha'': dL/dlogit = t (1 - alpha), dL/dden = t q / den,
+// dL/dmu = -2 t k (mu - c) / den, dL/dd_max = 2 t q / d_max.  Every term is linear in dL/dalpha'',
+// so the point-count term's part (the same for every Gaussian of a view) and the blend's part (the
+// few percent of pairs that are rendered) are summed apart: the first in a loop over all views that
+// needs four sums per view and no branch, the second over the rendered views of each lane only.
+// One loop over all views, the projection's adjoint behind a branch that some lane of every wave
+// took, kept 5 % of its lanes busy there and reduced the d_max term through LDS at every step: 377 us
+// for 16 views of 2M Gaussians, now 266 us (the scattered partials of the rendered pairs and their
+// latency, four waves per SIMD); one view of 1M 37 us as before, an autograd step of 20k 26 -> 10 us
+// (with a block per 256 Gaussians).
+// words: LDS of (kCamWords + 1) V words ([V] camera, k, point-count gradient; [V] sums of t q).
 __global__ __launch_bounds__(kBlock) void k_gauss_bwd(
     clod_scene sc, const DevView* __restrict__ views, int V, clod_params prm,
     const unsigned long long* __restrict__ dmax_key, const uint8_t* __restrict__ flags,
     const float* __restrict__ gscreen, int64_t VN, const float* __restrict__ dL_deta,
     float* __restrict__ gpart /* [G][V] */, int accumulate, clod_scene_grad g) {
-  // Dynamic LDS: [V] per-block sums of the frustum-maximum partial.  The SH coefficients'
-  // gradients and the view-direction term of the mean's are left to k_sh_bwd.
-  extern __shared__ float lds[];
-  float* gsum = lds;
+  extern __shared__ __align__(16) uint32_t words_dyn[];
+  CamLds* cam = reinterpret_cast<CamLds*>(words_dyn);
+  float* gsum = reinterpret_cast<float*>(words_dyn + kCamWords * V);
   const int64_t n = sc.n;
   const float inv_n = 1.0f / (float)n;
-  for (int v = threadIdx.x; v < V; v += kBlock) gsum[v] = 0.f;
+  for (int v = threadIdx.x; v < V; v += kBlock) {
+    gsum[v] = 0.f;
+    CamLds c = cam_lds(views[v]);
+    const float a = views[v].s_v * frcp(dmax_from_key(dmax_key[v]));
+    c.k[0] = a * a;
+    c.k[1] = dL_deta ? dL_deta[v] * inv_n : 0.f;
+    cam[v] = c;
+  }
   __syncthreads();
   int64_t lo, hi;
   block_chunk(n, lo, hi);
   const int64_t iters = (hi - lo + kBlock - 1) / kBlock;
   for (int64_t it = 0; it < iters; ++it) {
-  const int64_t i = lo + it * kBlock + threadIdx.x;
-  const bool valid = i < hi;
-  float mx = 0.f, my = 0.f, mz = 0.f, op = 0.f, dc = 0.f;
-  if (valid) {
-    mx = sc.mean[i]; my = sc.mean[n + i]; mz = sc.mean[2 * n + i];
-    op = sc.opacity[i]; dc = sc.decay[i];
-  }
-  float gmx = 0.f, gmy = 0.f, gmz = 0.f, gop = 0.f, gdc = 0.f;
+  const int64_t j = lo + it * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+  const bool valid = j < hi;
+  const float mx = sc.mean[i], my = sc.mean[n + i], mz = sc.mean[2 * n + i];
+  const float op = sc.opacity[i], dc = sc.decay[i];
   float gls[3] = {0.f, 0.f, 0.f}, gq[4] = {0.f, 0.f, 0.f, 0.f};
   // View-independent factors of Eq. (2): alpha = sigmoid(o), 1 / (2 relu(sigma)^2 + eps).
   const float alpha = frcp(1.0f + fexp(-op));
   const float r = fmaxf(dc, 0.0f);
-  const float iden = frcp(2.f * r * r + prm.eps);
+  const float iden = frcp(2.f * r * r + prm.eps), i2 = 1.44269504088896341f * iden;
+  float st = 0.f, stq = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;   // sums of t, t q, t k (mu - c)
+  if (dL_deta) {
+    for (int v = 0; v < V; ++v) {
+      const CamLds& C = cam[v];
+      const float ex = mx - C.c[0], ey = my - C.c[1], ez = mz - C.c[2];
+      const float x = fmaf_(ex, ex, fmaf_(ey, ey, ez * ez)) * C.k[0];
+      float t = (C.k[1] * alpha) * __builtin_amdgcn_exp2f(-(x * i2));
+      t = valid ? t : 0.f;
+      const float tq = t * (x * iden), tk = t * C.k[0];
+      st += t;
+      stq += tq;
+      sx = fmaf_(tk, ex, sx);
+      sy = fmaf_(tk, ey, sy);
+      sz = fmaf_(tk, ez, sz);
+      const float w = wave_total63(tq);
+      if (lane_id() == 63u && w != 0.f) atomicAdd(&gsum[v], w);
+    }
+  }
+  float gmx = 0.f, gmy = 0.f, gmz = 0.f;   // through the projection
   bool have_cov = false;
   float s[3], Rm[9], S[9], qn[4], rn = 0.f;
   // dL/dSigma summed over the rendering views (Sigma is view independent, so the chain
   // Sigma -> M -> (scale, rotation) -> quaternion runs once, after the view loop).
   float gSig[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // (0,0) (0,1) (0,2) (1,1) (1,2) (2,2)
-  for (int v = 0; v < V; ++v) {
-    const DevView& Vw = views[v];
-    float gdm = 0.f;
-    if (valid) {
-      const int64_t f = (int64_t)v * n + i;
-      const uint8_t fl = flags[f];
-      float ex, ey, ez;
-      const float d = __builtin_amdgcn_sqrtf(cam_distance2(Vw, mx, my, mz, ex, ey, ez));
-      const float idmax = frcp(dmax_from_key(dmax_key[v]));
-      const float uu = d * idmax * Vw.s_v;   // s_v-scaled normalised distance
-      const float q = uu * uu * iden;
-      const float a2 = alpha * fexp(-q);
-      float ga2 = dL_deta ? dL_deta[v] * inv_n : 0.f;
-      float gx = 0.f, gy = 0.f, gz = 0.f;     // camera-space position
-      float gex = 0.f, gey = 0.f, gez = 0.f;  // world offset mu - c
-      if (fl & 4) {
-        const float* gs = gscreen + f * kGscreen;
-        const float gu = gs[0], gv = gs[1];
-        const float gA = gs[2], gB = gs[3], gC = gs[4];
-        ga2 += gs[5];
-        float x, y, z;
-        to_camera(Vw, mx, my, mz, x, y, z);
-        if (!have_cov) {
-          s[0] = cexp(sc.log_scale[i]); s[1] = cexp(sc.log_scale[n + i]); s[2] = cexp(sc.log_scale[2 * n + i]);
-          quat_rot(sc.quat[i], sc.quat[n + i], sc.quat[2 * n + i], sc.quat[3 * n + i], Rm, qn[0], qn[1], qn[2], qn[3], rn);
-          cov3(Rm, s[0], s[1], s[2], S);
-          have_cov = true;
-        }
-        // Mean in screen space.
-        const float iz = 1.0f / z;
-        gx += gu * Vw.fx * iz;
-        gy += gv * Vw.fy * iz;
-        gz += -(gu * Vw.fx * x + gv * Vw.fy * y) * iz * iz;
-        // Conic -> 2D covariance (a, b, c include the dilation).
-        Proj P;
-        ewa(Vw, x, y, z, S, prm.dilation, P);
-        const float a = P.ca, b = P.cb, c = P.cc;
-        const float id2 = 1.0f / (P.det * P.det);
-        const float ga = (-c * c * gA + b * c * gB - b * b * gC) * id2;
-        const float gb = (2.f * b * c * gA - (a * c + b * b) * gB + 2.f * a * b * gC) * id2;
-        const float gcc = (-b * b * gA + a * b * gB - a * a * gC) * id2;
-        // Sigma' = T Sigma T^T with T = J W; symmetric gradient G' = [[ga, gb/2], [gb/2, gcc]].
-        const float j00 = Vw.fx * iz, j02 = -Vw.fx * x * iz * iz;
-        const float j11 = Vw.fy * iz, j12 = -Vw.fy * y * iz * iz;
-        float T[6];
-        for (int k = 0; k < 3; ++k) {
-          T[k] = j00 * Vw.W[k] + j02 * Vw.W[6 + k];
-          T[3 + k] = j11 * Vw.W[3 + k] + j12 * Vw.W[6 + k];
-        }
-        const float Gp00 = ga, Gp01 = 0.5f * gb, Gp11 = gcc;
-        // TS = T Sigma (2x3)
-        float TS[6];
-        for (int r = 0; r < 2; ++r)
-          for (int k = 0; k < 3; ++k)
-            TS[3 * r + k] = T[3 * r] * S[k] + T[3 * r + 1] * S[3 + k] + T[3 * r + 2] * S[6 + k];
-        // dL/dT = 2 G' T Sigma
-        float gT[6];
-        for (int k = 0; k < 3; ++k) {
-          gT[k] = 2.f * (Gp00 * TS[k] + Gp01 * TS[3 + k]);
-          gT[3 + k] = 2.f * (Gp01 * TS[k] + Gp11 * TS[3 + k]);
-        }
-        // dL/dSigma = T^T G' T (symmetric 3x3), accumulated over the views.
-        {
-          const float u0 = Gp00 * T[0] + Gp01 * T[3], u1 = Gp00 * T[1] + Gp01 * T[4], u2 = Gp00 * T[2] + Gp01 * T[5];
-          const float w0 = Gp01 * T[0] + Gp11 * T[3], w1 = Gp01 * T[1] + Gp11 * T[4], w2 = Gp01 * T[2] + Gp11 * T[5];
-          gSig[0] += T[0] * u0 + T[3] * w0;
-          gSig[1] += T[0] * u1 + T[3] * w1;
-          gSig[2] += T[0] * u2 + T[3] * w2;
-          gSig[3] += T[1] * u1 + T[4] * w1;
-          gSig[4] += T[1] * u2 + T[4] * w2;
-          gSig[5] += T[2] * u2 + T[5] * w2;
-        }
-        // dL/dJ = dL/dT W^T; J depends on (x, y, z).
-        float gJ00 = 0.f, gJ02 = 0.f, gJ11 = 0.f, gJ12 = 0.f;
-        for (int k = 0; k < 3; ++k) {
-          gJ00 += gT[k] * Vw.W[k];
-          gJ02 += gT[k] * Vw.W[6 + k];
-          gJ11 += gT[3 + k] * Vw.W[3 + k];
-          gJ12 += gT[3 + k] * Vw.W[6 + k];
-        }
-        const float iz2 = iz * iz, iz3 = iz2 * iz;
-        gz += -Vw.fx * iz2 * gJ00 + 2.f * Vw.fx * x * iz3 * gJ02 - Vw.fy * iz2 * gJ11 + 2.f * Vw.fy * y * iz3 * gJ12;
-        gx += -Vw.fx * iz2 * gJ02;
-        gy += -Vw.fy * iz2 * gJ12;
+  for (int v0 = 0; v0 < V; v0 += 32) {
+    const int vn = V - v0 < 32 ? V - v0 : 32;
+    uint32_t rmask = 0;   // rendering views of the group
+#pragma unroll 8
+    for (int q = 0; q < vn; ++q) rmask |= (uint32_t)((flags[(int64_t)(v0 + q) * n + i] >> 2) & 1u) << q;
+    if (!valid) rmask = 0;
+    while (rmask) {
+      const int v = v0 + __builtin_ctz(rmask);
+      rmask &= rmask - 1;
+      const DevView& Vw = views[v];
+      const CamLds& C = cam[v];
+      const float* gs = gscreen + ((int64_t)v * n + i) * kGscreen;
+      const float gu = gs[0], gv = gs[1];
+      const float gA = gs[2], gB = gs[3], gC = gs[4], ga2 = gs[5];
+      if (!have_cov) {
+        s[0] = cexp(sc.log_scale[i]); s[1] = cexp(sc.log_scale[n + i]); s[2] = cexp(sc.log_scale[2 * n + i]);
+        quat_rot(sc.quat[i], sc.quat[n + i], sc.quat[2 * n + i], sc.quat[3 * n + i], Rm, qn[0], qn[1], qn[2], qn[3], rn);
+        cov3(Rm, s[0], s[1], s[2], S);
+        have_cov = true;
       }
-      // Eq. (2): alpha'' = sigmoid(o) exp(-q), q = (d' s_v)^2 / (2 relu(sigma)^2 + eps).
-      gop += ga2 * a2 * (1.0f - alpha);
-      const float gqv = -ga2 * a2;
-      const float gnum = gqv * iden;
-      const float gden = -gqv * q * iden;
-      if (dc > 0.0f) gdc += gden * 4.f * r;
-      const float gdn = gnum * 2.f * uu * Vw.s_v;
-      const float gd = gdn * idmax;
-      gdm = -gdn * d * idmax * idmax;
-      const float gdd = gd * frcp(d);
-      gex += gdd * ex;
-      gey += gdd * ey;
-      gez += gdd * ez;
+      {   // Eq. (2)
+        const float ex = mx - C.c[0], ey = my - C.c[1], ez = mz - C.c[2];
+        const float x = fmaf_(ex, ex, fmaf_(ey, ey, ez * ez)) * C.k[0];
+        const float t = (ga2 * alpha) * __builtin_amdgcn_exp2f(-(x * i2));
+        const float tq = t * (x * iden), tk = t * C.k[0];
+        st += t;
+        stq += tq;
+        sx = fmaf_(tk, ex, sx);
+        sy = fmaf_(tk, ey, sy);
+        sz = fmaf_(tk, ez, sz);
+        atomicAdd(&gsum[v], tq);
+      }
+      float x, y, z;
+      to_camera(C, mx, my, mz, x, y, z);
+      // Mean in screen space.
+      const float iz = 1.0f / z;
+      float gx = gu * Vw.fx * iz, gy = gv * Vw.fy * iz;   // camera-space position
+      float gz = -(gu * Vw.fx * x + gv * Vw.fy * y) * iz * iz;
+      // Conic -> 2D covariance (a, b, c include the dilation).
+      Proj P;
+      ewa(Vw, x, y, z, S, prm.dilation, P);
+      const float a = P.ca, b = P.cb, c = P.cc;
+      const float id2 = 1.0f / (P.det * P.det);
+      const float ga = (-c * c * gA + b * c * gB - b * b * gC) * id2;
+      const float gb = (2.f * b * c * gA - (a * c + b * b) * gB + 2.f * a * b * gC) * id2;
+      const float gcc = (-b * b * gA + a * b * gB - a * a * gC) * id2;
+      // Sigma' = T Sigma T^T with T = J W; symmetric gradient G' = [[ga, gb/2], [gb/2, gcc]].
+      const float j00 = Vw.fx * iz, j02 = -Vw.fx * x * iz * iz;
+      const float j11 = Vw.fy * iz, j12 = -Vw.fy * y * iz * iz;
+      float T[6];
+      for (int k = 0; k < 3; ++k) {
+        T[k] = j00 * C.W[k] + j02 * C.W[6 + k];
+        T[3 + k] = j11 * C.W[3 + k] + j12 * C.W[6 + k];
+      }
+      const float Gp00 = ga, Gp01 = 0.5f * gb, Gp11 = gcc;
+      // TS = T Sigma (2x3)
+      float TS[6];
+      for (int q = 0; q < 2; ++q)
+        for (int k = 0; k < 3; ++k)
+          TS[3 * q + k] = T[3 * q] * S[k] + T[3 * q + 1] * S[3 + k] + T[3 * q + 2] * S[6 + k];
+      // dL/dT = 2 G' T Sigma
+      float gT[6];
+      for (int k = 0; k < 3; ++k) {
+        gT[k] = 2.f * (Gp00 * TS[k] + Gp01 * TS[3 + k]);
+        gT[3 + k] = 2.f * (Gp01 * TS[k] + Gp11 * TS[3 + k]);
+      }
+      // dL/dSigma = T^T G' T (symmetric 3x3), accumulated over the views.
+      {
+        const float u0 = Gp00 * T[0] + Gp01 * T[3], u1 = Gp00 * T[1] + Gp01 * T[4], u2 = Gp00 * T[2] + Gp01 * T[5];
+        const float w0 = Gp01 * T[0] + Gp11 * T[3], w1 = Gp01 * T[1] + Gp11 * T[4], w2 = Gp01 * T[2] + Gp11 * T[5];
+        gSig[0] += T[0] * u0 + T[3] * w0;
+        gSig[1] += T[0] * u1 + T[3] * w1;
+        gSig[2] += T[0] * u2 + T[3] * w2;
+        gSig[3] += T[1] * u1 + T[4] * w1;
+        gSig[4] += T[1] * u2 + T[4] * w2;
+        gSig[5] += T[2] * u2 + T[5] * w2;
+      }
+      // dL/dJ = dL/dT W^T; J depends on (x, y, z).
+      float gJ00 = 0.f, gJ02 = 0.f, gJ11 = 0.f, gJ12 = 0.f;
+      for (int k = 0; k < 3; ++k) {
+        gJ00 += gT[k] * C.W[k];
+        gJ02 += gT[k] * C.W[6 + k];
+        gJ11 += gT[3 + k] * C.W[3 + k];
+        gJ12 += gT[3 + k] * C.W[6 + k];
+      }
+      const float iz2 = iz * iz, iz3 = iz2 * iz;
+      gz += -Vw.fx * iz2 * gJ00 + 2.f * Vw.fx * x * iz3 * gJ02 - Vw.fy * iz2 * gJ11 + 2.f * Vw.fy * y * iz3 * gJ12;
+      gx += -Vw.fx * iz2 * gJ02;
+      gy += -Vw.fy * iz2 * gJ12;
       // Camera-space gradient back to the world mean (p = W mu + t).
-      gmx += Vw.W[0] * gx + Vw.W[3] * gy + Vw.W[6] * gz + gex;
-      gmy += Vw.W[1] * gx + Vw.W[4] * gy + Vw.W[7] * gz + gey;
-      gmz += Vw.W[2] * gx + Vw.W[5] * gy + Vw.W[8] * gz + gez;
+      gmx += C.W[0] * gx + C.W[3] * gy + C.W[6] * gz;
+      gmy += C.W[1] * gx + C.W[4] * gy + C.W[7] * gz;
+      gmz += C.W[2] * gx + C.W[5] * gy + C.W[8] * gz;
     }
-    // Per-view, per-block sum of the frustum-maximum partial (LDS, one add per wave).
-    gdm = wave_sum(gdm);
-    if (lane_id() == 0 && gdm != 0.f) atomicAdd(&gsum[v], gdm);
   }
+  gmx += -2.f * iden * sx;
+  gmy += -2.f * iden * sy;
+  gmz += -2.f * iden * sz;
+  const float gop = st * (1.0f - alpha);
+  const float gdc = dc > 0.0f ? stq * iden * 4.f * r : 0.f;
   if (have_cov) {
     // Sigma = M M^T, M = R diag(s): dL/dM = 2 (dL/dSigma) M.
     const float gS[9] = {gSig[0], gSig[1], gSig[2], gSig[1], gSig[3], gSig[4], gSig[2], gSig[4], gSig[5]};
@@ -204,7 +243,8 @@ __global__ __launch_bounds__(kBlock) void k_gauss_bwd(
   }
   }
   __syncthreads();
-  for (int v = threadIdx.x; v < V; v += kBlock) gpart[(int64_t)blockIdx.x * V + v] = gsum[v];
+  for (int v = threadIdx.x; v < V; v += kBlock)
+    gpart[(int64_t)blockIdx.x * V + v] = 2.f * gsum[v] * frcp(dmax_from_key(dmax_key[v]));
 }
 
 // The SH colour's adjoint for one rendering view, in double precision: the basis values Y_k of
@@ -452,7 +492,7 @@ hipError_t launch_gauss_bwd(const clod_scene& sc, const Layout& L, void* ws, clo
   float* gpart = (float*)(w + L.gpart);
   // One partial per block and view: the grid is capped and each block walks a chunk.
   const int grid = proj_blocks(sc.n);
-  hipLaunchKernelGGL(k_gauss_bwd, dim3(grid), dim3(kBlock), (size_t)L.V * sizeof(float), s, sc,
+  hipLaunchKernelGGL(k_gauss_bwd, dim3(grid), dim3(kBlock), (size_t)(kCamWords + 1) * L.V * sizeof(uint32_t), s, sc,
                      (const DevView*)(w + L.vinfo), L.V, prm, (const unsigned long long*)(w + L.dmax_key),
                      (const uint8_t*)(w + L.flags), (const float*)(w + L.gscreen), L.VN, dL_deta, gpart,
                      accumulate, g);
