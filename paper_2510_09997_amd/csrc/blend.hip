@@ -5,10 +5,9 @@
 // are staged in LDS (one per lane or thread, a coalesced gather of the records) and read back
 // as LDS broadcasts; entries that provably cannot reach a quadrant are dropped for it (see
 // quadrant_mask).  Blocks take tiles longest list first (the order clod_bin_sort computes),
-// so the long tiles, not stragglers, start the launch.  Lists of 8,192 entries or more are
-// blended with 4x4-pixel blocks per wave (four workgroups per tile); for lists of 65,536 or
-// more, a stage before the blend marks per entry the blocks it may reach, and each block's
-// wave walks only those entries.
+// so the long tiles, not stragglers, start the launch.  Long lists (long_tile_count) are blended with
+// 4x4-pixel blocks per wave (four workgroups per tile); a stage before the blend marks per entry the
+// blocks it may reach, and each block's wave walks only those entries.
 #include "clod_internal.h"
 
 namespace clod {
@@ -22,7 +21,7 @@ namespace clod {
 // rounded up to a multiple of 8C; the map is a bijection on it and blocks past the last tile
 // exit at once.
 constexpr uint32_t kXcds = 8, kXcdRun = 16;
-constexpr uint32_t kLongMaskBlocks = 1024;   // grid of the very-long-tile mask stage
+constexpr uint32_t kLongMaskBlocks = 1024;   // grid of the long-tile mask stage
 
 __device__ __forceinline__ uint32_t xcd_tile_pos(uint32_t b) {
   const uint32_t x = b % kXcds, j = b / kXcds, r = j / kXcdRun, i = j % kXcdRun;
@@ -39,15 +38,10 @@ __host__ __device__ inline uint32_t long_grid(uint32_t long_tiles) {
 }
 
 // The long tiles of this blend: the first tord[kTileLongWord] positions of the tile order
-// (written by the tile ordering stage), within the bound the launch was sized for; the very
-// long ones (65,536 entries or more) are the first tord[kTileVeryLongWord] of them.
-__device__ __forceinline__ uint32_t long_tiles(const BlendArgs& a) {
-  const uint32_t nl = a.tord[kTileLongWord];
-  return nl < a.long_max ? nl : a.long_max;
-}
-__device__ __forceinline__ uint32_t very_long_tiles(const uint32_t* tord, uint32_t vl_max) {
-  const uint32_t nv = tord[kTileVeryLongWord];
-  return nv < vl_max ? nv : vl_max;
+// (written by the tile ordering stage), within the bound the launch was sized for.
+__device__ __forceinline__ uint32_t long_tiles(const uint32_t* tord, uint32_t bound) {
+  const uint32_t nl = tord[kTileLongWord];
+  return nl < bound ? nl : bound;
 }
 
 __device__ __forceinline__ int view_of_tile(const DevView* views, int V, uint32_t tile) {
@@ -144,13 +138,11 @@ __device__ __forceinline__ uint32_t quadrant_mask1(float u, float v, float A, fl
   return (ddx * ddx + ddy * ddy <= rc * rc && ellipse_reaches<kB>(u, v, A, B, C, cut, x0, y0)) ? 1u : 0u;
 }
 
-// Tiles whose list holds at least 2^(kLongBucket - 1) entries (the dense far views of a large
-// scene) are blended with 4x4-pixel blocks per wave: a wave walks only the entries that may
-// reach its block, and sixteen waves share the tile instead of four.  The tile order puts them
-// first (longest first): they are the first tord[kTileLongWord] positions, taken by the leading
-// workgroups of the launch.  Of these, the tiles of at least 2^(kVeryLongBucket - 1) entries
-// (the first tord[kTileVeryLongWord]) get their block tests from k_long_mask and their waves
-// walk compacted lists.
+// Long tiles (long_tile_count) are blended with 4x4-pixel blocks per wave: a wave walks only the
+// entries that may reach its block, and sixteen waves share the tile instead of four.  The tile
+// order puts them first (longest first): they are taken by the leading workgroups of the launch.
+// They get their block tests from k_long_mask and their waves walk compacted lists (where the bit
+// planes find no room, and in the resident server, the waves test the entries themselves).
 
 // Forward blend.  Each wave owns one 8x8 quadrant of a tile (lane l: pixel (l & 7, l >> 3))
 // and runs on its own: it takes 64 entries of the tile's sorted list at a time (one entry per
@@ -161,7 +153,7 @@ __device__ __forceinline__ uint32_t quadrant_mask1(float u, float v, float A, fl
 // final reduction of the optional pair counters.
 struct TileLds {
   float4 st[4][3][64];   // per wave: (u, v, hA, nB), (hC, alpha'', r, g), (b, cut, list position, -)
-  uint32_t q[4][256];    // per wave: ring of the list positions that reach its 4x4 block (very long tiles)
+  uint32_t q[4][256];    // per wave: ring of the list positions that reach its 4x4 block (long tiles)
 };
 
 // One tile, at position pos of the batch's tile order, by the 256 threads of the block (four
@@ -189,7 +181,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   if (a.hdr[kHdrOverflow]) return;
   if (pos >= tiles_total) return;
   // The long tiles are taken as 4x4 blocks.
-  if ((kB == 8) != (pos >= long_tiles(a))) return;
+  if ((kB == 8) != (pos >= long_tiles(a.tord, a.long_max))) return;
   const int tile_i = (int)order[pos];
   const int v = view_of_tile(views, V, (uint32_t)tile_i);
   const DevView& Vw = views[v];
@@ -217,78 +209,114 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   uint32_t last = 0, term = 0xFFFFFFFFu, nexp = 0, nblend = 0;
   // Lanes whose pixel has terminated (or lies outside the frame), as a wave-uniform mask: the
   // per-entry predicates below are formed as lane masks and turned back into execution masks
-  // with inverse ballots, so the termination bookkeeping stays in scalar registers.
-  uint64_t dm = ballot64(!own);
+  // with inverse ballots, so the termination bookkeeping stays in scalar registers.  (4x4 blocks:
+  // the 16 pixels' bits four times, once per row of lanes.)
+  uint64_t dm = ballot64(!inside);
   // 4x4 blocks: the n entries of a batch that may reach the block (staged compacted in list
-  // order, slots 0 .. n-1), four at a time.  Row g of the wave evaluates entry g of the group
-  // for the block's 16 pixels (power, live test, exponential, clamp: the four exponentials are
-  // computed side by side, on every lane: lanes outside the live set are masked off after);
-  // row 0 then takes the four entries in list order through the contract's termination test
-  // and blend, the same operations in the same order as one entry at a time.  Terminated
-  // pixels (dm, bits 0..15) drop out of the later entries of a group; their values for those
-  // entries are never used.
-  auto walk4 = [&](const uint32_t n) {
+  // order, slots 0 .. n-1), four at a time.  Row g of the wave evaluates entry g of the group for
+  // the block's 16 pixels (power, live test, exponential, clamp, skip test: four exponentials side
+  // by side) and keeps its opacity, or 0 where the contract skips the pair.  The opacities then go
+  // to all rows (whole-wave row swaps), and every row takes the four entries in list order through
+  // the same transmittance, row c adding up colour channel c: the contract's operations in its
+  // order, an opacity of 0 leaving T and the sums as they are (T * 1 and fma(c, 0, sum); colours
+  // are finite here).  T never grows, so if no pixel is below the termination threshold after the
+  // group, none was inside it; else (at most once per pixel) the group is taken again from the
+  // state before it, one entry at a time with the contract's termination test.  `last` is kept by
+  // the row that evaluated the entry (the largest of a pixel's four counts).
+  // A wave walks these lists all but alone on its SIMD, so the chain of a group is what counts: with
+  // the tests, masks and branches of every entry in it a group took 740 cycles, and the longest
+  // of the 6M far frame's 6,500-entry chains set its 558 us; now 300.
+  auto walk4 = [&](const uint32_t n, const bool finite) {
     const uint32_t row = lane >> 4;
-    // One entry of the group for row 0's pixels: alpha (valid on the live lanes lv, bits
-    // 0..15), the entry's colour and list position.
-    auto step = [&](const float al, const uint64_t lv, const float c0, const float c1, const float c2,
-                    const uint32_t pos) {
-      const uint64_t lm = lv & ~dm & 0xFFFFull;
-      if (lm == 0ull) return;
-      const float Tn = T * (1.0f - al);   // used on the live lanes only
-      const uint64_t um = ballot64(al >= kSkip) & lm;
-      const uint64_t km = ballot64(Tn >= kTmin);
-      const uint64_t bm = um & km;
-      dm |= um & ~km;
-      if (__builtin_amdgcn_inverse_ballot_w64(bm)) {
-        const float w = al * T;
-        cr = fmaf_(c0, w, cr);
-        cg = fmaf_(c1, w, cg);
-        cb = fmaf_(c2, w, cb);
-        T = Tn;
-        last = pos + 1u;
+    struct Set {
+      float4 a; float2 c; float2 b;   // (u, v, -A/2, -B), (-C/2, alpha''), (cut, list position)
+      float k[4];                     // the row's channel of the four entries
+    };
+    const float* colour = row == 0u ? &s1[0].z : row == 1u ? &s1[0].w : &s2[0].x;
+    auto load = [&](const uint32_t k, Set& q) {
+      const uint32_t fr = k + row;
+      q.a = s0[fr];
+      q.c = *reinterpret_cast<const float2*>(&s1[fr].x);
+      q.b = *reinterpret_cast<const float2*>(&s2[fr].y);
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) q.k[e] = colour[4u * (k + e)];
+    };
+    auto group = [&](const uint32_t k, const Set& q) {
+      const float dx = q.a.x - pcx, dy = q.a.y - pcy;
+      const float power = fmaf_(q.a.z * dx, dx, fmaf_(q.c.x * dy, dy, (q.a.w * dx) * dy));
+      const uint32_t left = n - k;   // slots at or past n hold stale entries
+      const uint64_t slots = left >= 4u ? ~0ull : (1ull << (16u * left)) - 1ull;
+      const uint64_t live = ballot64(__builtin_amdgcn_fmed3f(power, q.b.x, 0.0f) == power) & ~dm & slots;
+      if (live == 0ull) return;
+      const float al = fminf(0.99f, q.c.y * cexp_core(power));
+      const uint64_t um = ballot64(al >= kSkip) & live;
+      if (um == 0ull) {
+        if (kCount) nexp += __builtin_amdgcn_inverse_ballot_w64(live) ? 1u : 0u;
+        return;
       }
-      if (kCount) {
-        if (__builtin_amdgcn_inverse_ballot_w64(um & ~km)) term = pos;
-        nexp += __builtin_amdgcn_inverse_ballot_w64(lm) ? 1u : 0u;
-        nblend += __builtin_amdgcn_inverse_ballot_w64(bm) ? 1u : 0u;
+      const float am = __builtin_amdgcn_inverse_ballot_w64(um) ? al : 0.0f;
+      // Rows 0 .. 3 of am to every row.
+      const auto x32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(am), __float_as_uint(am), false, false);
+      const auto x01 = __builtin_amdgcn_permlane16_swap(x32[0], x32[0], false, false);
+      const auto x23 = __builtin_amdgcn_permlane16_swap(x32[1], x32[1], false, false);
+      const float al4[4] = {__uint_as_float(x01[0]), __uint_as_float(x01[1]), __uint_as_float(x23[0]), __uint_as_float(x23[1])};
+      const uint32_t count = __float_as_uint(q.b.y) + 1u;
+      float Tn = T, sum = cr;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float w = al4[e] * Tn;
+        sum = fmaf_(q.k[e], w, sum);
+        Tn = Tn * (1.0f - al4[e]);
+      }
+      if ((ballot64(Tn < kTmin) & ~dm) == 0ull && finite) {
+        T = Tn;
+        cr = sum;
+        last = __builtin_amdgcn_inverse_ballot_w64(um) ? count : last;
+        if (kCount) {
+          nexp += __builtin_amdgcn_inverse_ballot_w64(live) ? 1u : 0u;
+          nblend += __builtin_amdgcn_inverse_ballot_w64(um) ? 1u : 0u;
+        }
+        return;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t rows = 0xFFFFull << (16 * e);
+        const uint64_t lm = live & rows & ~dm;   // pairs of entry e
+        const uint64_t take = ballot64(al4[e] > 0.0f) & ~dm, ends = ballot64(T * (1.0f - al4[e]) < kTmin) & take;
+        if (__builtin_amdgcn_inverse_ballot_w64(take & ~ends)) {
+          const float w = al4[e] * T;
+          cr = fmaf_(q.k[e], w, cr);
+          T = T * (1.0f - al4[e]);
+        }
+        last = __builtin_amdgcn_inverse_ballot_w64(take & ~ends & rows) ? count : last;
+        if (kCount) {
+          if (__builtin_amdgcn_inverse_ballot_w64(ends)) term = __float_as_uint(s2[k + (uint32_t)e].z);
+          nexp += __builtin_amdgcn_inverse_ballot_w64(lm) ? 1u : 0u;
+          nblend += __builtin_amdgcn_inverse_ballot_w64(take & ~ends & rows) ? 1u : 0u;
+        }
+        dm |= ends;
       }
     };
-    // Slots k .. k + 3 lie in the wave's 64-entry slice (k is a multiple of 4 below n <= 64);
-    // those at or past n hold stale entries, masked off by `slots`.
-    for (uint32_t k = 0; k < n; k += 4) {
-      const uint32_t fr = k + row;
-      const float4 a = s0[fr], c = s1[fr];
-      const float4 bc = s2[fr];
-      // Colours and list positions of entries 1..3 for row 0 (LDS broadcasts).
-      const float4 q1 = s1[k + 1u], q2 = s1[k + 2u], q3 = s1[k + 3u];
-      const float4 r1 = s2[k + 1u], r2 = s2[k + 2u], r3 = s2[k + 3u];
-      const float dx = a.x - pcx, dy = a.y - pcy;
-      const float power = fmaf_(a.z * dx, dx, fmaf_(c.x * dy, dy, (a.w * dx) * dy));
-      const uint32_t left = n - k;
-      const uint64_t slots = left >= 4u ? ~0ull : (1ull << (16u * left)) - 1ull;
-      const uint64_t dm4 = (dm & 0xFFFFull) * 0x0001000100010001ull;
-      const uint64_t live = ballot64(power <= 0.0f) & ballot64(power >= bc.y) & ~dm4 & slots;
-      if (live == 0ull) continue;
-      const float al = fminf(0.99f, c.y * cexp_core(power));
-      // Rows 1, 2, 3 of al into row 0 (whole-wave row swaps).
-      const auto x16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(al), __float_as_uint(al), false, false);
-      const auto x32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(al), __float_as_uint(al), false, false);
-      const auto x48 = __builtin_amdgcn_permlane32_swap(x16[1], x16[1], false, false);
-      step(al, live, c.z, c.w, bc.x, __float_as_uint(bc.z));
-      step(__uint_as_float(x16[1]), live >> 16, q1.z, q1.w, r1.x, __float_as_uint(r1.z));
-      step(__uint_as_float(x32[1]), live >> 32, q2.z, q2.w, r2.x, __float_as_uint(r2.z));
-      step(__uint_as_float(x48[1]), live >> 48, q3.z, q3.w, r3.x, __float_as_uint(r3.z));
+    // Two register sets in alternation, as below.
+    Set A, B;
+    load(0u, A);
+    for (uint32_t k = 0; k < n; k += 8) {
+      load(k + 4u, B);   // (k + 4 <= 60)
+      group(k, A);
+      load(k + 8u < 60u ? k + 8u : 60u, A);
+      if (k + 4u < n) group(k + 4u, B);
       if (dm == ~0ull) break;
     }
   };
   // One batch of up to 64 entries, its records (g0, g1, g2) already in registers, lane l's
   // at list position j: staged in this wave's LDS slice, culled against the quadrant, then
-  // walked.  The entries of a very long tile arrive already compacted to those that may reach
+  // walked.  The entries of a premasked long tile arrive already compacted to those that may reach
   // the 4x4 block (relc); elsewhere the batch is 64 consecutive entries and is culled here.
-  const bool pre = kB == 4 && pos < very_long_tiles(a.tord, a.vl_max);
+  const bool pre = kB == 4 && pos < long_tiles(a.tord, a.pre_max);
+  // next() runs between the staging and the walk: it requests the next batch's records, into the
+  // same registers.
   auto batch = [&](const uint32_t j, const float4& g0, const float4& g1, const float4& g2,
-                   const bool relc) {
+                   const bool relc, auto&& next) {
     bool rel = false;
     float cut = 0.0f;
     if (kB == 4 && pre) {
@@ -305,7 +333,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
     uint64_t mask = ballot64(rel);
     // The entries that may reach the quadrant (block) are staged compacted, in list order
     // (slot = rank of the lane among them), so that the walks below step a counter.  (Those of
-    // a very long tile are the leading lanes already.)
+    // a premasked tile are the leading lanes already.)
     if (!(kB == 4 && pre)) {
       if (rel) {
         const uint32_t slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -319,15 +347,23 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       s0[n] = make_float4(__builtin_nanf(""), __builtin_nanf(""), 0.0f, 0.0f);
       s2[n] = make_float4(0.0f, __builtin_inff(), 0.0f, 0.0f);
     }
+    if (kB == 4 && lane >= n && lane < ((n + 3u) & ~3u)) {   // the last group's empty slots: colour 0
+      s1[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      s2[lane] = make_float4(0.0f, __builtin_inff(), 0.0f, 0.0f);
+    }
     // The staged entries are read by other lanes of this wave: wait for the LDS writes.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (mask == 0ull) return;
     if constexpr (kB == 4) {
-      walk4(n);
+      // Colours are at least 0 (or NaN, which fails the comparison as infinity does).
+      const uint64_t odd = ballot64(rel && !(g2.x < __builtin_inff() && g2.y < __builtin_inff() && g2.z < __builtin_inff()));
+      next();
+      walk4(n, odd == 0ull);
       return;
     }
+    next();
+    if (mask == 0ull) return;
     // One entry: the contract's skip, exponential, clamp, termination and blend.  Below the
     // entry's cut (or above 0) the contract skips the pair whatever E returns; live pairs have
     // power in [cut, 0] with cut >= ln(1/255) - 0.01, inside cexp_core's range.  Once some
@@ -381,12 +417,12 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       pair(a1, c1, b1);
     }
   };
-  // Software pipeline over the batches, unrolled by two with a register set each (A, B), so
-  // that nothing is copied between batches: while one batch is staged and walked, the records
-  // of the next and the sorted indices of the one after are in flight (index -> record is two
-  // dependent memory latencies per batch, which few resident waves -- a far frame's handful of
-  // long tiles -- cannot hide).  Every load is issued (positions past the list end read its
-  // last entry, which is not staged), so the wait counts stay static.
+  // Software pipeline over the batches: while one batch is walked, the records of the next and the
+  // sorted indices of the one after are in flight (index -> record is two dependent memory latencies
+  // per batch, which few resident waves -- a far frame's handful of long tiles -- cannot hide).  A
+  // batch's records leave their registers when it is staged, so one set of them is enough (two, in
+  // alternation, cost eight waves' worth of registers per CU).  Every load is issued (positions past
+  // the list end read its last entry, which is not staged), so the wait counts stay static.
   if (rg.y > rg.x) {
     const uint32_t jmax = rg.y - 1;
     auto index_at = [&](uint32_t q) {
@@ -394,7 +430,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       return (int64_t)f < VN ? f : 0u;   // defensive: the sort only emits indices < V*n
     };
     if (kB == 4 && pre) {
-      // Very long tile: the wave scans its block's bit plane (one word per 64 entries, read
+      // The wave scans its block's bit plane (one word per 64 entries, read
       // with scalar loads: they do not enter the vector-memory wait count, so the pipeline's
       // gathers stay in flight while it scans), appends the positions of the entries that may
       // reach the block to its LDS ring, and takes them 64 at a time into the same two-set
@@ -439,65 +475,58 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       // not clamped (a clamp of each loaded index would make the wave wait for every gather in
       // flight).
       auto index_of = [&](uint32_t q) { return svals[q < jmax ? q : jmax]; };
-      uint32_t qa, qb, ja, jb;
-      bool va, vb, ra, rb;
-      take(qa, va);
-      uint32_t ia = index_of(qa);
-      take(qb, vb);
-      uint32_t ib = index_of(qb);
-      float4 a0 = rec[kRecQuads * (int64_t)ia], a1 = rec[kRecQuads * (int64_t)ia + 1], a2 = rec[kRecQuads * (int64_t)ia + 2];
-      float4 b0, b1, b2;
-      ja = qa;
-      ra = va;
-      take(qa, va);
-      ia = index_of(qa);
-      while (ballot64(ra) != 0ull && dm != ~0ull) {
-        b0 = rec[kRecQuads * (int64_t)ib];
-        b1 = rec[kRecQuads * (int64_t)ib + 1];
-        b2 = rec[kRecQuads * (int64_t)ib + 2];
-        jb = qb;
-        rb = vb;
-        take(qb, vb);
-        ib = index_of(qb);
-        batch(ja, a0, a1, a2, ra);
-        if (ballot64(rb) == 0ull || dm == ~0ull) break;
-        a0 = rec[kRecQuads * (int64_t)ia];
-        a1 = rec[kRecQuads * (int64_t)ia + 1];
-        a2 = rec[kRecQuads * (int64_t)ia + 2];
-        ja = qa;
-        ra = va;
-        take(qa, va);
-        ia = index_of(qa);
-        batch(jb, b0, b1, b2, rb);
+      uint32_t q, qn;
+      bool v, vn;
+      take(q, v);
+      uint32_t f = index_of(q);
+      float4 g0 = rec[kRecQuads * (int64_t)f], g1 = rec[kRecQuads * (int64_t)f + 1], g2 = rec[kRecQuads * (int64_t)f + 2];
+      take(qn, vn);
+      f = index_of(qn);
+      while (ballot64(v) != 0ull && dm != ~0ull) {
+        batch(q, g0, g1, g2, v, [&]() {
+          g0 = rec[kRecQuads * (int64_t)f];
+          g1 = rec[kRecQuads * (int64_t)f + 1];
+          g2 = rec[kRecQuads * (int64_t)f + 2];
+          q = qn;
+          v = vn;
+          take(qn, vn);
+          f = index_of(qn);
+        });
       }
     } else {
-    uint32_t ia = index_at(rg.x + lane);
-    uint32_t ib = index_at(rg.x + 64 + lane);
-    float4 a0 = rec[kRecQuads * (int64_t)ia], a1 = rec[kRecQuads * (int64_t)ia + 1], a2 = rec[kRecQuads * (int64_t)ia + 2];
-    float4 b0, b1, b2;
-    ia = index_at(rg.x + 128 + lane);
-    for (uint32_t base = rg.x; base < rg.y && dm != ~0ull; base += 128) {
-      b0 = rec[kRecQuads * (int64_t)ib];
-      b1 = rec[kRecQuads * (int64_t)ib + 1];
-      b2 = rec[kRecQuads * (int64_t)ib + 2];
-      ib = index_at(base + 192 + lane);
-      batch(base + lane, a0, a1, a2, false);
-      if (base + 64 >= rg.y || dm == ~0ull) break;
-      a0 = rec[kRecQuads * (int64_t)ia];
-      a1 = rec[kRecQuads * (int64_t)ia + 1];
-      a2 = rec[kRecQuads * (int64_t)ia + 2];
-      ia = index_at(base + 256 + lane);
-      batch(base + 64 + lane, b0, b1, b2, false);
+      uint32_t f = index_at(rg.x + lane);
+      float4 g0 = rec[kRecQuads * (int64_t)f], g1 = rec[kRecQuads * (int64_t)f + 1], g2 = rec[kRecQuads * (int64_t)f + 2];
+      f = index_at(rg.x + 64 + lane);
+      for (uint32_t base = rg.x; base < rg.y && dm != ~0ull; base += 64) {
+        batch(base + lane, g0, g1, g2, false, [&]() {
+          g0 = rec[kRecQuads * (int64_t)f];
+          g1 = rec[kRecQuads * (int64_t)f + 1];
+          g2 = rec[kRecQuads * (int64_t)f + 2];
+          f = index_at(base + 128 + lane);
+        });
+      }
     }
+  }
+  if constexpr (kB == 4) {   // a channel per row; the counts of the rows folded
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+      const uint32_t q = __shfl_xor(last, o, 64);
+      last = q > last ? q : last;
     }
+    const uint32_t row = lane >> 4;
+    if (inside && row < 3u)
+      rgb[3 * (int64_t)Vw.pix_base + (int64_t)row * Vw.width * Vw.height + (int64_t)py * Vw.width + px] =
+          fmaf_(T, row == 0u ? bg0 : row == 1u ? bg1 : bg2, cr);
   }
   if (own) {
     const int64_t P = (int64_t)Vw.pix_base;
     const int64_t HW = (int64_t)Vw.width * Vw.height;
     const int64_t p = (int64_t)py * Vw.width + px;
+    if constexpr (kB == 8) {
     rgb[3 * P + p] = fmaf_(T, bg0, cr);
     rgb[3 * P + HW + p] = fmaf_(T, bg1, cg);
     rgb[3 * P + 2 * HW + p] = fmaf_(T, bg2, cb);
+    }
     Tout[P + p] = T;
     lastout[P + p] = last;
   }
@@ -518,40 +547,56 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   }
 }
 
-// Very long tiles, per entry of their lists: the 4x4 blocks of the tile the entry may reach (the
+// Long tiles, per entry of their lists: the 4x4 blocks of the tile the entry may reach (the
 // blend's own block test, run once per entry here instead of once per entry in each of the
 // tile's sixteen waves, which all walk these lists to the end in the far views of a large
-// scene), as sixteen bit planes: per block, one bit per entry, 64 entries per word.  Wave w of
-// the grid takes the 64-entry chunks w, w + W, ... of each very long tile and writes the
-// chunk's sixteen words (lane b the word of block b).
+// scene), as sixteen bit planes: per block, one bit per entry, 64 entries per word.  The tiles'
+// 64-entry chunks are numbered through 256 tiles at a time (a block scan of their counts), and wave
+// w of the grid takes the chunks w, w + W, ..., writing a chunk's sixteen words (lane b the word of
+// block b).  (Every wave walking the list of tiles for its own chunks, a chain of loads per tile,
+// took 480 us for 150 tiles of 1.9M entries; now 72 us for 300 of 2.3M.)
 __device__ __forceinline__ void long_mask_body(const LongMaskArgs& a, Blk b) {
+  __shared__ uint32_t first[kBlock + 1], start[kBlock], len[kBlock], tile[kBlock], sm[4];
+  __shared__ float ox[kBlock], oy[kBlock];
   if (a.hdr[kHdrOverflow]) return;
-  const uint32_t nl = very_long_tiles(a.tord, a.vl_max);
-  if (nl == 0u) return;
-  const uint32_t lane = lane_id();
-  const uint32_t gw = b.id * (kBlock / 64u) + (threadIdx.x >> 6), GW = b.n * (kBlock / 64u);
-  for (uint32_t p = 0; p < nl; ++p) {
-    const int tile_i = (int)a.order[p];
-    const int v = view_of_tile(a.views, a.V, (uint32_t)tile_i);
-    const DevView& Vw = a.views[v];
-    const int local = tile_i - (int)Vw.tile_base;
-    const int tx = local % Vw.tiles_x, ty = local / Vw.tiles_x;
-    const uint2 rg = a.ranges[tile_i];
-    const uint32_t nchunks = ((rg.y - rg.x) + 63u) >> 6;
-    unsigned long long* __restrict__ out = a.lplane + (rg.x >> 6) + (uint32_t)tile_i;
-    for (uint32_t c = gw; c < nchunks; c += GW) {
-      const uint32_t j = rg.x + 64u * c + lane;
+  const uint32_t nl = long_tiles(a.tord, a.pre_max);
+  const uint32_t lane = lane_id(), t = threadIdx.x;
+  const uint32_t gw = b.id * (kBlock / 64u) + (t >> 6), GW = b.n * (kBlock / 64u);
+  for (uint32_t p0 = 0; p0 < nl; p0 += kBlock) {
+    uint32_t chunks = 0;
+    if (p0 + t < nl) {
+      const uint32_t tile_i = a.order[p0 + t];
+      const DevView& Vw = a.views[view_of_tile(a.views, a.V, tile_i)];
+      const int local = (int)(tile_i - Vw.tile_base);
+      const uint2 rg = a.ranges[tile_i];
+      ox[t] = (float)(local % Vw.tiles_x * kTile + Vw.vx);
+      oy[t] = (float)(local / Vw.tiles_x * kTile + Vw.vy);
+      start[t] = rg.x;
+      len[t] = rg.y - rg.x;
+      tile[t] = tile_i;
+      chunks = (len[t] + 63u) >> 6;
+    }
+    uint32_t total;
+    first[t] = block_exclusive_scan(chunks, sm, total);
+    if (t == 0) first[kBlock] = total;
+    __syncthreads();
+    for (uint32_t c = gw; c < total; c += GW) {
+      uint32_t lo = 0, hi = kBlock - 1;   // last tile whose first chunk is at most c
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= c) lo = mid; else hi = mid - 1;
+      }
+      const uint32_t word = c - first[lo], e = 64u * word + lane;
       uint32_t m = 0u;
-      if (j < rg.y) {
-        uint32_t f = a.svals[j];
+      if (e < len[lo]) {
+        uint32_t f = a.svals[start[lo] + e];
         if ((int64_t)f >= a.VN) f = 0u;   // defensive: the sort only emits indices < V*n
         const float4 g0 = a.rec[kRecQuads * (int64_t)f], g1 = a.rec[kRecQuads * (int64_t)f + 1];
         const float cut = entry_cut(g0.z);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const float x0 = (float)(tx * kTile + (q % 4) * 4 + Vw.vx), y0 = (float)(ty * kTile + (q / 4) * 4 + Vw.vy);
-          m |= quadrant_mask1<4>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, x0, y0) << q;
-        }
+        for (int q = 0; q < 16; ++q)
+          m |= quadrant_mask1<4>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, ox[lo] + (float)(q % 4 * 4),
+                                 oy[lo] + (float)(q / 4 * 4)) << q;
       }
       unsigned long long mine = 0ull;
 #pragma unroll
@@ -559,8 +604,9 @@ __device__ __forceinline__ void long_mask_body(const LongMaskArgs& a, Blk b) {
         const unsigned long long w = ballot64(((m >> q) & 1u) != 0u);
         if (lane == (uint32_t)q) mine = w;
       }
-      if (lane < 16u) out[(int64_t)lane * a.pw + c] = mine;
+      if (lane < 16u) a.lplane[(int64_t)lane * a.pw + (start[lo] >> 6) + tile[lo] + word] = mine;
     }
+    __syncthreads();
   }
 }
 __global__ __launch_bounds__(kBlock) void k_long_mask(LongMaskArgs a) { long_mask_body(a, grid_blk()); }
@@ -579,7 +625,7 @@ __device__ __forceinline__ void long_item(uint32_t b, uint32_t& pos, uint32_t& s
 // sized for the most long tiles the pair capacity allows) map past the last tile and exit.
 template <bool kCount>
 __device__ __forceinline__ void blend_item(const BlendArgs& a, uint32_t b, TileLds& S) {
-  const uint32_t lb = long_grid(long_tiles(a));
+  const uint32_t lb = long_grid(long_tiles(a.tord, a.long_max));
   if (b < lb) {
     uint32_t pos, sub;
     long_item(b, pos, sub);
@@ -592,12 +638,13 @@ __device__ __forceinline__ void blend_item(const BlendArgs& a, uint32_t b, TileL
 // Items a blend stage needs once the tile order is known (the resident kernel sizes its
 // claims by it; a per-stage launch covers the bound instead).
 __device__ __forceinline__ uint32_t blend_items(const BlendArgs& a) {
-  return long_grid(long_tiles(a)) + xcd_grid(a.tiles_total);
+  return long_grid(long_tiles(a.tord, a.long_max)) + xcd_grid(a.tiles_total);
 }
 
-// Per-batch launch: one workgroup per tile (four per long tile).
+// Per-batch launch: one workgroup per tile (four per long tile).  Seven waves per SIMD (the 4x4
+// walk alone would take the kernel to 76 registers and six: 2 to 4 % on frames without long tiles).
 template <bool kCount>
-__global__ __launch_bounds__(kBlock) void k_blend_fwd(BlendArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_blend_fwd(BlendArgs a) {
   __shared__ TileLds S;
   blend_item<kCount>(a, blockIdx.x, S);
 }
@@ -627,18 +674,13 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
     hipError_t e = launch_fill_u32((uint32_t*)part, 0u, 6 * (int64_t)L.tiles_total, out);
     if (e != hipSuccess) return e;
   }
-  // At most cap / 2^(kLongBucket - 1) tiles can be long: the launch covers that many.
-  const int64_t cap_long = bb.cap / (1ll << (kLongBucket - 1));
-  const uint32_t long_max = (uint32_t)(cap_long < (int64_t)L.tiles_total ? cap_long : (int64_t)L.tiles_total);
-  // Very long tiles: at most cap / 2^(kVeryLongBucket - 1); their bit planes (16 planes of
-  // pw words) must fit the arrays the tile-id sort left free, else they are blended like the
-  // other long tiles.
-  const int64_t cap_vl = bb.cap / (1ll << (kVeryLongBucket - 1));
+  const uint32_t long_max = long_tile_bound(bb.cap, L.tiles_total);
+  // Their bit planes (16 planes of pw words) must fit the arrays the tile-id sort left free, else
+  // each wave tests the entries itself.
   const uint32_t pw = (uint32_t)((bb.cap + 63) / 64 + (int64_t)L.tiles_total + 1);
   const bool planes_fit = (size_t)16 * pw * sizeof(unsigned long long) <= bb.spare_bytes;
-  const uint32_t vl_max =
-      planes_fit ? (uint32_t)(cap_vl < (int64_t)L.tiles_total ? cap_vl : (int64_t)L.tiles_total) : 0u;
-  if (vl_max > 0) {
+  const uint32_t pre_max = planes_fit ? long_max : 0u;
+  if (pre_max > 0) {
     Stage m{};
     m.kind = kStLongMask;
     m.items = kLongMaskBlocks;
@@ -646,7 +688,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
     m.a.long_mask = LongMaskArgs{(const DevView*)(w + L.vinfo), L.V, (const uint2*)(w + L.ranges),
                                  (const uint32_t*)(w + L.order), (const uint32_t*)(w + L.tord), bb.svals,
                                  (const float4*)(w + L.rec), L.VN, (const unsigned long long*)(w + L.hdr),
-                                 bb.spare, pw, vl_max};
+                                 bb.spare, pw, pre_max};
     const hipError_t e = out.put(m);
     if (e != hipSuccess) return e;
   }
@@ -657,7 +699,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
   st.a.blend = BlendArgs{(const DevView*)(w + L.vinfo), L.V, L.tiles_total, L.VN, (const float4*)(w + L.rec),
                          (const uint2*)(w + L.ranges), bb.svals, (const unsigned long long*)(w + L.hdr), prm.bg[0],
                          prm.bg[1], prm.bg[2], rgb, T, last, part, (const uint32_t*)(w + L.order),
-                         (const uint32_t*)(w + L.tord), long_max, part ? 1 : 0, bb.spare, pw, vl_max};
+                         (const uint32_t*)(w + L.tord), long_max, part ? 1 : 0, bb.spare, pw, pre_max};
   hipError_t e = out.put(st);
   if (e == hipSuccess && part) {
     Stage r{};

@@ -18,15 +18,20 @@ constexpr int kRecQuads = 4;
 constexpr int kRecBytes = kRecQuads * 16;
 constexpr int kScanItems = 16;             // items per thread in the emission's chunks
 constexpr int kScanChunk = kBlock * kScanItems;
-// Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the number of long
-// tiles (lists of at least 2^(kLongBucket - 1) entries, the leading positions of the order).
+// Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the number of long tiles
+// (the leading positions of the order), which the blend takes as sixteen 4x4-pixel blocks.  A tile
+// is long from 8,192 entries, or from 2,048 in a batch with at most kSparseTiles tiles that are not
+// empty: there the launch lasts as long as its longest chain of entries, and the chip has room for
+// the waves (far frame of 6M, 318 tiles: 614 us with the line at 8,192, 375 at 4,096, 384 to 290 at
+// 2,048; 2M Gaussians at half the distance: 360, 275 and 185 us), while in a full frame the shorter
+// lists are cheaper as four quadrants (one 1080p view of 3M: 150 us with the line at 8,192 and 212 at
+// 1,024; six views of 3M: 657 and, at 2,048, 790).
 constexpr int kEmitTile = 2048;            // tile pairs per output chunk of the emission
 constexpr int kTileBuckets = 33;
-constexpr int kLongBucket = 14;            // long tiles: 8,192 entries or more
-constexpr int kVeryLongBucket = 17;        // very long tiles: 65,536 entries or more
+constexpr int kLongBucket = 14, kLongBucketSparse = 12;
+constexpr uint32_t kSparseTiles = 2048;
 constexpr int kTileLongWord = 2 * kTileBuckets;
-constexpr int kTileVeryLongWord = 2 * kTileBuckets + 1;
-constexpr int kTileOrderWords = 2 * kTileBuckets + 2;
+constexpr int kTileOrderWords = 2 * kTileBuckets + 1;
 constexpr int kTileOrderChunk = 1024;       // tiles per block in the ordering kernels
 constexpr int kSortItems = 8;              // keys per thread per radix tile
 constexpr int kSortTile = kBlock * kSortItems;   // 2048 keys per radix tile
@@ -474,6 +479,21 @@ __device__ __forceinline__ void block_chunk(int64_t n, Blk b, int64_t& lo, int64
 }
 __device__ __forceinline__ void block_chunk(int64_t n, int64_t& lo, int64_t& hi) { block_chunk(n, grid_blk(), lo, hi); }
 
+// The long tiles, from the number of tiles per length class.
+__device__ __forceinline__ uint32_t long_tile_count(const uint32_t* classes) {
+  uint32_t filled = 0, n = 0;
+  for (int c = 1; c < kTileBuckets; ++c) filled += classes[c];
+  for (int c = filled <= kSparseTiles ? kLongBucketSparse : kLongBucket; c < kTileBuckets; ++c) n += classes[c];
+  return n;
+}
+// A bound on them for `cap` pairs in `tiles` tiles.
+inline uint32_t long_tile_bound(int64_t cap, uint32_t tiles) {
+  int64_t n = cap >> (kLongBucketSparse - 1);
+  if (n > (int64_t)kSparseTiles) n = (int64_t)kSparseTiles;
+  if (n < cap >> (kLongBucket - 1)) n = cap >> (kLongBucket - 1);
+  return n < (int64_t)tiles ? (uint32_t)n : tiles;
+}
+
 // Wave64 helpers.
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
@@ -651,15 +671,15 @@ struct BlendArgs {
   unsigned long long* pair_part; const uint32_t* order; const uint32_t* tord;
   uint32_t long_max;      // most long tiles the launch covers (the pair capacity's bound)
   int32_t count;
-  // Very long tiles (at most vl_max of them): per 4x4 block b of the tile, one bit per list
+  // Long tiles (the first pre_max of them): per 4x4 block b of the tile, one bit per list
   // entry (set if the entry may reach the block), 64 entries per word, the tile's words at
   // lplane[b * pw + rg.x / 64 + tile + w] (from kStLongMask).
-  const unsigned long long* lplane; uint32_t pw; uint32_t vl_max;
+  const unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };
 struct LongMaskArgs {
   const DevView* views; int32_t V; const uint2* ranges; const uint32_t* order; const uint32_t* tord;
   const uint32_t* svals; const float4* rec; int64_t VN; const unsigned long long* hdr;
-  unsigned long long* lplane; uint32_t pw; uint32_t vl_max;
+  unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };
 struct ReducePairsArgs {
   const unsigned long long* part; uint32_t tiles; unsigned long long* out;
@@ -769,7 +789,7 @@ hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* 
 hipError_t launch_ranges(const Layout& L, void* ws, const DupLayout& D, void* dup, const Sink& out);
 
 // The pair buffers the forward blend reads: the sorted record indices, and the two arrays the
-// tile-id sort left free (they hold the very long tiles' block bit planes).
+// tile-id sort left free (they hold the long tiles' block bit planes).
 struct BlendBufs {
   const uint32_t* svals; unsigned long long* spare; size_t spare_bytes; int64_t cap;
 };

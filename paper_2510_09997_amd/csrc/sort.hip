@@ -754,10 +754,7 @@ __device__ __forceinline__ void tile_scatter_body(const TileOrderArgs& a, Blk bl
     uint32_t start = 0;
     for (uint32_t c = b + 1; c < (uint32_t)kTileBuckets; ++c) start += tord[c];
     cur[b] = cnt[b] ? start + atomicAdd(&tord[kTileBuckets + b], cnt[b]) : 0u;
-    // The counts of the long and of the very long tiles (the starts of the first buckets below
-    // them), for the blend.
-    if (b == kLongBucket - 1 && blk.id == 0) tord[kTileLongWord] = start;
-    if (b == kVeryLongBucket - 1 && blk.id == 0) tord[kTileVeryLongWord] = start;
+    if (b == 0 && blk.id == 0) tord[kTileLongWord] = long_tile_count(tord);
   }
   __syncthreads();
   for (uint32_t t = t0 + threadIdx.x; t < tiles && t < t0 + kTileOrderChunk; t += kBlock) {
