@@ -615,7 +615,8 @@ def run_serve_stream(args, torch, Scene, synth):
 STAGE_NAMES = ["end", "view_setup", "fill", "frustum_max", "fold", "classify", "project", "select_hist",
                "select_pick", "rec_count", "rec_compact", "depth_up", "depth_down", "row_up", "row_down", "col_up", "col_scan",
                "col_down", "radix_up", "radix_scan", "radix_down", "emit_reduce", "emit_partials", "emit_offsets",
-               "emit", "ranges", "tile_count", "tile_scatter", "blend", "reduce_pairs", "long_mask"]
+               "emit", "ranges", "tile_count", "tile_scatter", "blend", "reduce_pairs", "long_mask",
+               "select_first"]
 
 
 def server_timeline(torch, scene, synth, reps=12):

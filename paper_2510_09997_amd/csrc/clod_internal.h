@@ -77,6 +77,7 @@ struct DevView {
 // bins and the chunk counts (the workspace keeps kSelBytes for them).
 constexpr uint32_t kSelBins = 2048;
 constexpr int kSelBlocks = 512;
+constexpr int kSelViews = 4, kSelFirst = 768;   // level 0: views of a block, parts of the scene
 constexpr uint32_t kSelWords = 3 * kSelBins + kSelBlocks;
 constexpr size_t kSelBytes = 128 * 256 * 4;
 static_assert(kSelWords * 4 <= kSelBytes, "select bins");
@@ -593,7 +594,7 @@ enum StageKind : int32_t {
   kStRecCount, kStRecCompact, kStDepthUp, kStDepthDown, kStRowUp, kStRowDown, kStColUp, kStColScan, kStColDown,
   kStRadixUp, kStRadixScan, kStRadixDown, kStEmitReduce,
   kStEmitPartials, kStEmitOffsets, kStEmit, kStRanges, kStTileCount, kStTileScatter, kStBlend, kStReducePairs,
-  kStLongMask
+  kStLongMask, kStSelectFirst
 };
 
 struct ViewSetupArgs {

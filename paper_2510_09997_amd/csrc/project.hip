@@ -919,8 +919,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // Budgeted LoD (a view with budget K, 0 < K < n): the K-th largest selection key.  alpha'' (as
 // bits) is found by an MSD radix select in three levels of 11, 11 and 10 bits; among equal
 // alpha'' the lowest indices are kept, so the last stage finds the index at the remaining rank.
-//   k_select_hist   levels 0 to 2: counts of the level's digit over the keys that share the digits
-//                   found so far (LDS counts, added to the view's bins)
+//   k_select_first  level 0: counts of the leading digit (LDS counts, added to the view's bins)
+//   k_select_hist   levels 1 and 2: counts of the level's digit over the keys that share the digits
+//                   found so far
 //   k_select_hist   level 3: keys equal to the threshold per chunk of the view's Gaussians
 //   k_select_pick   the chunk and then the index at the rank; the threshold key to the view
 // Every block finds the digits of the levels before its own itself from the view's bins, so no
@@ -928,7 +929,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // where there is a plane for it (not in the counting entry points), stores it for the other
 // levels to read instead of computing it again.  Five launches; the eight 8-bit levels over the
 // whole 64-bit key that these replaced took sixteen and computed alpha'' eight times (3M
-// Gaussians in four viewports: 540 us, now 134 us).  K >= n keeps everything (threshold 0).
+// Gaussians in four viewports: 540 us, now 114 us).  K >= n keeps everything (threshold 0).
+//
+// Level 0 is bound by vector issue and, at its end, by the atomics of its blocks' bins.  A block
+// takes its Gaussians through up to four views, so that sigmoid and reciprocal denominator are
+// formed once for them and the distance once per camera run, with the short root and quotients of
+// k_classify where the arguments allow (else once more with the general forms): 45 us for the four
+// viewports, against 68 us a view at a time with the general forms.  Three blocks' worth of parts per
+// CU: with 512 parts 50 us (too few waves), with 1024 48 us and with 2048 76 us (their bins).
 __device__ __forceinline__ int64_t select_chunk(int64_t n) {   // Gaussians per chunk
   const int64_t c = (n + kSelBlocks - 1) / kSelBlocks;
   return (c + kBlock - 1) / kBlock * kBlock;
@@ -973,10 +981,119 @@ __device__ __forceinline__ uint32_t select_bits(const SelectArgs& a, const DevVi
 }
 
 struct SelectLds {
-  uint32_t h[kSelBins];
+  uint32_t h[kSelViews][kSelBins];   // (the levels after the first use one row)
 };
+// Block b of ceil(V / kSelViews) * kSelFirst: part b % kSelFirst of the Gaussians, in the views of
+// group b / kSelFirst.
+__device__ __forceinline__ void select_first_body(const SelectArgs& a, Blk b, SelectLds& S) {
+  constexpr int kItems = 4;
+  __shared__ float vk[kSelViews][6];   // camera centre, d_max, its reciprocal, s_v
+  const int v0 = (int)(b.id / kSelFirst) * kSelViews;
+  const uint32_t part = b.id % kSelFirst;
+  const clod_scene& sc = a.sc;
+  const int64_t n = sc.n;
+  int64_t per = (n + kSelFirst - 1) / kSelFirst;
+  per = (per + kBlock - 1) / kBlock * kBlock;
+  const int64_t lo = part * per, hi = lo + per < n ? lo + per : n;
+  if (lo >= n) return;
+  uint32_t active = 0;   // uniform: views of the group that select
+  for (int w = 0; w < kSelViews && v0 + w < a.V; ++w) {
+    const int64_t k = a.views[v0 + w].budget;
+    active |= k > 0 && k < n ? 1u << w : 0u;
+  }
+  if (active == 0u) return;
+  for (uint32_t j = threadIdx.x; j < kSelViews * kSelBins; j += kBlock) (&S.h[0][0])[j] = 0u;
+  if (threadIdx.x < kSelViews && ((active >> threadIdx.x) & 1u)) {
+    const int w = (int)threadIdx.x;
+    const float dmax = dmax_from_key(a.dmax_key[v0 + w]);
+    for (int j = 0; j < 3; ++j) vk[w][j] = a.views[v0 + w].c[j];
+    vk[w][3] = dmax;
+    vk[w][4] = 1.0f / dmax;
+    vk[w][5] = a.views[v0 + w].s_v;
+  }
+  __syncthreads();
+  for (int64_t b0 = lo; b0 < hi; b0 += kItems * kBlock) {
+    float mx[kItems], my[kItems], mz[kItems], alpha[kItems], den[kItems], rden[kItems], dn[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const int64_t j = b0 + k * kBlock + threadIdx.x, i = j < hi ? j : hi - 1;
+      mx[k] = sc.mean[i]; my[k] = sc.mean[n + i]; mz[k] = sc.mean[2 * n + i];
+      alpha[k] = sc.opacity[i]; den[k] = sc.decay[i];
+    }
+    uint64_t own = 0;   // lanes whose arguments the short forms do not take, whatever the view
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      alpha[k] = sigmoid_c(alpha[k]);
+      den[k] = decay_den(den[k], a.prm.eps);
+      rden[k] = 1.0f / den[k];
+      own |= ballot64(!in_exponents<60>(den[k]));
+    }
+    int lead = -1;         // camera run whose distances dn holds
+    uint64_t far = 0;      // lanes whose distance the short forms do not take
+#pragma unroll 1
+    for (int w = 0; w < kSelViews; ++w) {
+      if (!((active >> w) & 1u)) continue;
+      const int v = v0 + w;
+      if (a.views[v].cam_lead != lead) {
+        lead = a.views[v].cam_lead;
+        const float c0 = vk[w][0], c1 = vk[w][1], c2 = vk[w][2], dmax = vk[w][3], rdmax = vk[w][4];
+        far = ballot64(!in_exponents<40>(dmax));
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+          const float ex = mx[k] - c0, ey = my[k] - c1, ez = mz[k] - c2;   // as cam_distance2
+          const float d2 = fmaf_(ex, ex, fmaf_(ey, ey, ez * ez));
+          dn[k] = div_normal(sqrt_normal(d2), dmax, rdmax);
+          far |= ballot64(!in_exponents<80>(d2));
+        }
+      }
+      const float s_v = vk[w][5];
+      uint64_t special = own | far;
+      uint32_t key[kItems];
+#pragma unroll
+      for (int k = 0; k < kItems; ++k) {
+        const float u = dn[k] * s_v, num = u * u;
+        const float q = div_normal(num, den[k], rden[k]);
+        special |= ballot64(!in_exponents<60>(num));
+        key[k] = __float_as_uint(alpha[k] * (q > 86.0f ? 0.0f : cexp_core(-q)));
+      }
+      if (special) {   // the general forms, for the whole wave
+        const float dmax = vk[w][3];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+          float ex, ey, ez, q;
+          const float d = cam_distance(a.views[v], mx[k], my[k], mz[k], ex, ey, ez);
+          key[k] = __float_as_uint(attenuated_pre(d, dmax, s_v, alpha[k], den[k], q));
+        }
+      }
+      uint32_t zeros = 0;   // keys of digit 0: half the scene may be (alpha'' flushed to 0)
+#pragma unroll
+      for (int k = 0; k < kItems; ++k) {
+        const int64_t i = b0 + k * kBlock + threadIdx.x;
+        if (i < hi) {
+          if (a.alpha) a.alpha[(int64_t)v * n + i] = __uint_as_float(key[k]);
+          const uint32_t d = (key[k] >> 21) & 2047u;
+          if (d != 0u) atomicAdd(&S.h[w][d], 1u);
+          zeros += d == 0u ? 1u : 0u;
+        }
+      }
+      zeros = wave_sum(zeros);
+      if (lane_id() == 0 && zeros) atomicAdd(&S.h[w][0], zeros);
+    }
+  }
+  __syncthreads();
+  // (Each block starts at bins of its own: blocks end together, and met at the same ones.)
+  for (uint32_t j0 = threadIdx.x; j0 < kSelViews * kSelBins; j0 += kBlock) {
+    const uint32_t j = (j0 + part * kBlock) % (kSelViews * kSelBins);
+    const uint32_t w = j / kSelBins, c = S.h[w][j % kSelBins];
+    if (c) atomicAdd(a.hist + (size_t)(v0 + (int)w) * kSelWords + j % kSelBins, c);
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_select_first(SelectArgs a) {
+  __shared__ SelectLds S;
+  select_first_body(a, grid_blk(), S);
+}
 // Block b of V * kSelBlocks: chunk b % kSelBlocks of view b / kSelBlocks.
-__device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b, SelectLds& S) {
+__device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b, uint32_t* h) {
   __shared__ uint32_t sm[4];
   const int v = (int)(b.id / kSelBlocks);
   const uint32_t chunk = b.id % kSelBlocks;
@@ -986,14 +1103,14 @@ __device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b, Sel
   const int64_t per = select_chunk(n), lo = chunk * per, hi = lo + per < n ? lo + per : n;
   if (lo >= n) return;
   uint32_t* __restrict__ hist = a.hist + (size_t)v * kSelWords;
-  for (uint32_t j = threadIdx.x; j < kSelBins; j += kBlock) S.h[j] = 0u;
+  for (uint32_t j = threadIdx.x; j < kSelBins; j += kBlock) h[j] = 0u;
   __syncthreads();
   uint32_t prefix, rank;
   select_derive(hist, a.level, Vw.budget, prefix, rank, sm);
-  const int shift = a.level == 0 ? 21 : a.level == 1 ? 10 : 0;
+  const int shift = a.level == 1 ? 10 : 0;
   const uint32_t mask = a.level == 3 ? 0u : a.level == 2 ? 1023u : 2047u;
   const float dmax = dmax_from_key(a.dmax_key[v]);
-  uint32_t zeros = 0;   // keys of digit 0 (of level 0 half the scene may be: alpha'' flushed to 0)
+  uint32_t zeros = 0;   // keys of digit 0 (half the scene may be: alpha'' flushed to 0)
   constexpr int kItems = 4;   // Gaussians per thread and round, read before any is used
   for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kItems * kBlock) {
     uint32_t k[kItems];
@@ -1006,26 +1123,25 @@ __device__ __forceinline__ void select_hist_body(const SelectArgs& a, Blk b, Sel
     for (int j = 0; j < kItems; ++j) {
       const int64_t i = i0 + j * kBlock;
       if (i >= hi) break;
-      if (a.level == 0 && a.alpha) a.alpha[v * n + i] = __uint_as_float(k[j]);
-      const bool in = a.level == 0 || (a.level == 3 ? k[j] == prefix : (k[j] >> (a.level == 1 ? 21 : 10)) == prefix);
+      const bool in = a.level == 3 ? k[j] == prefix : (k[j] >> (a.level == 1 ? 21 : 10)) == prefix;
       const uint32_t d = (k[j] >> shift) & mask;
-      if (in && d != 0u) atomicAdd(&S.h[d], 1u);
+      if (in && d != 0u) atomicAdd(&h[d], 1u);
       zeros += in && d == 0u ? 1u : 0u;
     }
   }
   zeros = wave_sum(zeros);
-  if (lane_id() == 0 && zeros) atomicAdd(&S.h[0], zeros);
+  if (lane_id() == 0 && zeros) atomicAdd(&h[0], zeros);
   __syncthreads();
   if (a.level == 3) {
-    if (threadIdx.x == 0) hist[3 * kSelBins + chunk] = S.h[0];
+    if (threadIdx.x == 0) hist[3 * kSelBins + chunk] = h[0];
     return;
   }
   for (uint32_t j = threadIdx.x; j < kSelBins; j += kBlock)
-    if (S.h[j]) atomicAdd(&hist[a.level * kSelBins + j], S.h[j]);
+    if (h[j]) atomicAdd(&hist[a.level * kSelBins + j], h[j]);
 }
 __global__ __launch_bounds__(kBlock) void k_select_hist(SelectArgs a) {
-  __shared__ SelectLds S;
-  select_hist_body(a, grid_blk(), S);
+  __shared__ uint32_t h[kSelBins];
+  select_hist_body(a, grid_blk(), h);
 }
 
 // Block v: the index of view v's last kept Gaussian among those at the threshold.
@@ -1084,8 +1200,8 @@ hipError_t launch_lod_select(const clod_scene& sc, DevView* vinfo, int V, clod_p
   h.block = kBlock;
   hipError_t e = hipSuccess;
   for (int level = 0; level < 5 && e == hipSuccess; ++level) {
-    h.kind = level < 4 ? kStSelectHist : kStSelectPick;
-    h.items = (uint32_t)(level < 4 ? kSelBlocks * V : V);
+    h.kind = level == 0 ? kStSelectFirst : level < 4 ? kStSelectHist : kStSelectPick;
+    h.items = (uint32_t)(level == 0 ? kSelFirst * ((V + kSelViews - 1) / kSelViews) : level < 4 ? kSelBlocks * V : V);
     h.a.select = SelectArgs{sc, vinfo, vinfo, V, prm, dmax_key, hist, alpha, level, 0};
     e = out.put(h);
   }
@@ -1229,6 +1345,7 @@ hipError_t launch_project_stage(const Stage& st, hipStream_t s) {
       hipLaunchKernelGGL(kern, g, blk, st.lds, s, a);
       break;
     }
+    case kStSelectFirst: hipLaunchKernelGGL(k_select_first, g, blk, 0, s, st.a.select); break;
     case kStSelectHist: hipLaunchKernelGGL(k_select_hist, g, blk, 0, s, st.a.select); break;
     case kStSelectPick: hipLaunchKernelGGL(k_select_pick, g, blk, 0, s, st.a.select); break;
     default: return hipErrorInvalidValue;

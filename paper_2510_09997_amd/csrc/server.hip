@@ -39,7 +39,7 @@ namespace clod {
 hipError_t launch_stage(const Stage& st, hipStream_t s) {
   switch (st.kind) {
     case kStViewSetup: case kStFill: case kStFrustumMax: case kStFold: case kStClassify: case kStProject:
-    case kStSelectHist: case kStSelectPick:
+    case kStSelectFirst: case kStSelectHist: case kStSelectPick:
       return launch_project_stage(st, s);
     case kStRecCount: case kStRecCompact: case kStDepthUp: case kStDepthDown: case kStRowUp: case kStRowDown:
     case kStColUp: case kStColScan: case kStColDown:
@@ -270,7 +270,8 @@ __device__ bool srv_run(int32_t kind, const Stage& st, Blk b, SrvLds& U) {
       }
       return true;
     }
-    case kStSelectHist: select_hist_body(uniform_copy(st.a.select), b, U.select); return true;
+    case kStSelectFirst: select_first_body(uniform_copy(st.a.select), b, U.select); return true;
+    case kStSelectHist: select_hist_body(uniform_copy(st.a.select), b, U.select.h[0]); return true;
     case kStSelectPick: select_pick_body(uniform_copy(st.a.select), b); return true;
     case kStRecCount: rec_count_body(uniform_copy(st.a.depth), b); return true;
     case kStRecCompact: rec_compact_body(uniform_copy(st.a.depth), b, U.rec); return true;
