@@ -542,14 +542,16 @@ __device__ __forceinline__ RowRec row_rec(const RowArgs& a, uint32_t rect, uint3
 // depth: the nearest cover tens of rows each, the others two or three, and of equal shares the first
 // set the time of the scatter.  So in large batches wave k of K starts at N f(k / K), in steps of 64,
 // with f(x) = x (1 + 3 x) / 4, a quarter of the records for the first waves and 1.75 times as many
-// for the last: 16 training views (1.5M records) 163 -> 79 us, six views of 720p to 4K (1.1M) 47 -> 36
-// us.  (x (1 + x) / 2: 107 and 36, x^2: 66 and 38 us.)  Batches whose shares are no longer than
-// kWaveMin leave the chip waves to spare, and longer last shares only cost there (a far frame of 6M
-// 25 -> 31 us, one training view 16 -> 18): equal shares.
-__device__ __forceinline__ uint64_t row_chunk(uint32_t N, const RadixGeom& G, uint32_t k) {
+// for the last: 16 training views (1.5M records of 14 tiles on average) 163 -> 79 us, six views of
+// 720p to 4K (1.1M of 9) 47 -> 36 us.  (x (1 + x) / 2: 107 and 36, x^2: 66 and 38 us.)  Where the
+// records are small their rows are even, and the longer last shares only cost (five LoD frames, 1.15M
+// of 6 tiles: 32 -> 38 us); so do they where shares are no longer than kWaveMin, which leaves the
+// chip waves to spare (a far frame of 6M 25 -> 31 us, one training view 16 -> 18): equal shares.
+__device__ __forceinline__ uint64_t row_chunk(const RowArgs& a, uint32_t N, const RadixGeom& G, uint32_t k) {
   const uint64_t K = 4u * G.nb;
   if (k >= K) return N;
-  const uint64_t at = G.kw > kWaveMin ? ((uint64_t)N * (k * (K + 3u * k)) / (4u * K * K)) & ~63ull : (uint64_t)G.kw * k;
+  const bool uneven = G.kw > kWaveMin && a.hdr[kHdrDup] >= 8ull * N;
+  const uint64_t at = uneven ? ((uint64_t)N * (k * (K + 3u * k)) / (4u * K * K)) & ~63ull : (uint64_t)G.kw * k;
   return at < N ? at : N;
 }
 
@@ -565,7 +567,7 @@ __device__ __forceinline__ void row_up_body(const RowArgs& a, Blk b, uint32_t* l
   for (uint32_t i = threadIdx.x; i < 4 * stride; i += kBlock) lds[i] = 0u;
   __syncthreads();
   const uint32_t w = threadIdx.x >> 6, lane = lane_id();
-  const uint64_t lo = row_chunk(N, G, 4 * c + w), hi = row_chunk(N, G, 4 * c + w + 1);
+  const uint64_t lo = row_chunk(a, N, G, 4 * c + w), hi = row_chunk(a, N, G, 4 * c + w + 1);
   uint32_t* cnt = lds + w * stride;
   for (uint64_t e0 = lo; e0 < hi; e0 += 256) {
     uint32_t q[4], f[4];
@@ -682,7 +684,7 @@ __device__ __forceinline__ void row_down_body(const RowArgs& a, Blk b, uint32_t*
   else if (bins == 4 * kBlock) total = row_starts<4>(a, c, G.nb, lds, sm);
   else total = row_starts<8>(a, c, G.nb, lds, sm);
   const uint32_t w = threadIdx.x >> 6;
-  const uint64_t lo = row_chunk(N, G, 4 * c + w), hi = row_chunk(N, G, 4 * c + w + 1);
+  const uint64_t lo = row_chunk(a, N, G, 4 * c + w), hi = row_chunk(a, N, G, 4 * c + w + 1);
   uint32_t* bits = lds + 4 * (bins + 1) + w * kRowBitWords;
   if (bins <= 2 * kBlock) row_scatter<9>(a, lo, hi, total, lds + w * bins, bits);
   else row_scatter<11>(a, lo, hi, total, lds + w * bins, bits);
