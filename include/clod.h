@@ -263,7 +263,10 @@ clod_status clod_adam_step(int64_t n, int32_t sh_degree, const clod_scene_grad *
                            const clod_scene_grad *v, const clod_adam *hp, void *stream);
 
 /* Synchronises `stream` and copies to host info[4] = {D (tile pairs of the last
-   clod_bin_sort), overflow flag, duplicate capacity, radix passes}. */
+   clod_bin_sort), overflow flag, duplicate capacity, radix passes of clod_bin_sort for this
+   batch: three over the depth keys and two partitions (by tile row, by column), or three and one
+   per eight bits of the tile id for batches of more than 2,048 tile rows or frames beyond 256 x 256
+   tiles; 0 for an empty scene}. */
 clod_status clod_read_info(const clod_batch *batch, int64_t *info_host, void *stream);
 
 /* Read-only views of intermediate results (for inspection and tests).  Stores the device

@@ -43,9 +43,10 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static bool finite_f(float x) { return isfinite(x) != 0; }
 
-// Radix passes of clod_bin_sort: 4 over the depth keys of the rendered records, then the
-// tile-id passes over the pairs.
-static int sort_passes(uint32_t tiles_total) { return 4 + tile_passes(tiles_total); }
+// Radix passes of clod_bin_sort: three over the depth keys of the rendered records, then the row and
+// the column partition of the row path or the tile-id passes of the general one (none for an empty
+// scene, which has nothing to sort).
+static int sort_passes(const Layout& L) { return L.VN == 0 ? 0 : 3 + (L.row_path ? 2 : tile_passes(L.tiles_total)); }
 
 int sort_blocks(int64_t cap) {
   int64_t g = (cap + kSortTile - 1) / kSortTile;
@@ -664,7 +665,7 @@ clod_status clod_read_info(const clod_batch* batch, int64_t* info_host, void* st
   info_host[0] = (int64_t)h[0];
   info_host[1] = (int64_t)h[1];
   info_host[2] = batch->dup ? clod_dup_capacity(batch->dup_bytes) : 0;
-  info_host[3] = sort_passes(cx.L.tiles_total);
+  info_host[3] = sort_passes(cx.L);
   return CLOD_OK;
 }
 
