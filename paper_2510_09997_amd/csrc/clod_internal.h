@@ -646,11 +646,10 @@ struct RadixArgs {   // one pass: upsweep, digit scan and downsweep share it
   const unsigned long long* hdr; int32_t cw, G, shift;
 };
 struct EmitReduceArgs {
-  const uint32_t* sorted_f; const float4* rec; const uint8_t* flags; int64_t count; const unsigned long long* hdr;
-  uint32_t* partE; uint32_t* tsorted;
+  const uint32_t* sorted_f; const float4* rec; const unsigned long long* hdr; uint32_t* partE; uint32_t* tsorted;
 };
 struct EmitPartialsArgs {
-  uint32_t* partE; unsigned long long* hdr; int32_t nb; int64_t cap;
+  uint32_t* partE; const unsigned long long* hdr;
 };
 struct EmitOffsetsArgs {
   const uint32_t* tsorted; const uint32_t* partE; const unsigned long long* hdr; uint32_t* eoff; uint32_t* owner;

@@ -275,86 +275,52 @@ __device__ __forceinline__ uint32_t rec_tiles(const float4* __restrict__ rec, ui
   return __float_as_uint(rec[kRecQuads * (int64_t)f + 3].w);
 }
 
-// Single block: D (summed in 64 bits) and the overflow flag (D above the capacity) to the
-// header, and, unless overflowed, the exclusive scan of the chunk totals in place.
+// Single block: the exclusive scan of the chunk totals in place (their sum D is at most the capacity:
+// the depth sort has stored D and the overflow flag, and an overflowed batch is left as it is).
 __device__ __forceinline__ void emit_partials_body(const EmitPartialsArgs& a, Blk) {
-  __shared__ unsigned long long sm[4];
+  __shared__ uint32_t sm[4];
   uint32_t* __restrict__ partE = a.partE;
-  unsigned long long* __restrict__ hdr = a.hdr;
-  const int nb = a.nb;
-  const int64_t cap = a.cap;
-  const bool over = hdr[kHdrOverflow] != 0ull;
-  const int nparts = over ? nb : (int)(((int64_t)hdr[kHdrRend] + kScanChunk - 1) / kScanChunk);
-  const uint32_t lane = lane_id();
-  const int wave = threadIdx.x >> 6;
-  unsigned long long carry = 0;
+  const unsigned long long* __restrict__ hdr = a.hdr;
+  if (hdr[kHdrOverflow] != 0ull) return;
+  const int nparts = (int)(((int64_t)hdr[kHdrRend] + kScanChunk - 1) / kScanChunk);
+  uint32_t carry = 0;
   for (int base = 0; base < nparts; base += kBlock) {
     const int j = base + threadIdx.x;
-    const unsigned long long v = j < nparts ? partE[j] : 0ull;
-    unsigned long long inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long up = __shfl_up(inc, o, 64);
-      if (lane >= (uint32_t)o) inc += up;
-    }
-    if (lane == 63) sm[wave] = inc;
-    __syncthreads();
-    unsigned long long wb = 0;
-    for (int w = 0; w < wave; ++w) wb += sm[w];
-    const unsigned long long tot = sm[0] + sm[1] + sm[2] + sm[3];
-    __syncthreads();
-    if (!over && j < nparts) partE[j] = (uint32_t)(carry + wb + inc - v);
+    const uint32_t v = j < nparts ? partE[j] : 0u;
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan(v, sm, tot);
+    if (j < nparts) partE[j] = carry + ex;
     carry += tot;
-  }
-  if (threadIdx.x == 0) {
-    hdr[kHdrDup] = carry;
-    if ((int64_t)carry > cap) hdr[kHdrOverflow] = 1ull;
   }
 }
 __global__ __launch_bounds__(kBlock) void k_emit_partials(EmitPartialsArgs a) { emit_partials_body(a, grid_blk()); }
 
-// Per chunk of the depth-sorted records: tile pairs of the chunk (saturated at 2^32 - 1,
-// which only a total far beyond any capacity reaches); the gathered counts are also stored in
-// sorted order (tsorted) for k_emit_offsets.  If R alone exceeded the capacity
-// (the only way the overflow flag can be set at this point) the records were never sorted;
-// the pair count is then summed over chunk b of all records instead, so that D is still
-// reported.
+// Per chunk of the depth-sorted records: tile pairs of the chunk; the gathered counts are also stored
+// in sorted order (tsorted) for k_emit_offsets.  Nothing is done for an overflowed batch.
 __device__ __forceinline__ void emit_reduce_body(const EmitReduceArgs& a, Blk b) {
-  __shared__ unsigned long long sm[4];
+  __shared__ uint32_t sm[4];
   const uint32_t* __restrict__ sorted_f = a.sorted_f;
   const float4* __restrict__ rec = a.rec;
-  const uint8_t* __restrict__ flags = a.flags;
-  const int64_t count = a.count;
   const unsigned long long* __restrict__ hdr = a.hdr;
   uint32_t* __restrict__ tsorted = a.tsorted;
-  const bool over = hdr[kHdrOverflow] != 0ull;
+  if (hdr[kHdrOverflow] != 0ull) return;
   const int64_t R = (int64_t)hdr[kHdrRend];
   const int64_t base = (int64_t)b.id * kScanChunk;
-  if (!over && base >= R) return;
-  unsigned long long s = 0;
-  if (!over) {
+  if (base >= R) return;
+  uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      const int64_t j = base + (int64_t)k * kBlock + threadIdx.x;
-      if (j < R) {
-        const uint32_t c = rec_tiles(rec, sorted_f[j]);
-        tsorted[j] = c;
-        s += c;
-      }
-    }
-  } else {
-    for (int k = 0; k < kScanItems; ++k) {
-      const int64_t j = base + (int64_t)k * kBlock + threadIdx.x;
-      if (j < count && (flags[j] & 4u)) s += rec_tiles(rec, (uint32_t)j);
+  for (int k = 0; k < kScanItems; ++k) {
+    const int64_t j = base + (int64_t)k * kBlock + threadIdx.x;
+    if (j < R) {
+      const uint32_t c = rec_tiles(rec, sorted_f[j]);
+      tsorted[j] = c;
+      s += c;
     }
   }
   s = wave_sum(s);
   if (lane_id() == 0) sm[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned long long c = sm[0] + sm[1] + sm[2] + sm[3];
-    a.partE[b.id] = c > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)c;
-  }
+  if (threadIdx.x == 0) a.partE[b.id] = sm[0] + sm[1] + sm[2] + sm[3];
 }
 __global__ __launch_bounds__(kBlock) void k_emit_reduce(EmitReduceArgs a) { emit_reduce_body(a, grid_blk()); }
 
@@ -644,7 +610,6 @@ hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* 
   uint32_t* const v[2] = {(uint32_t*)(dp + D.vals1), (uint32_t*)(dp + D.vals0)};
   const int nb = L.scan_blocks;
   uint32_t* partE = (uint32_t*)(w + L.scan_part);
-  const uint8_t* flags = (const uint8_t*)(w + L.flags);
   const float4* rec = (const float4*)(w + L.rec);
   Stage st{};
   st.block = kBlock;
@@ -654,9 +619,9 @@ hipError_t launch_bin_sort(const Layout& L, void* ws, const DupLayout& D, void* 
     if (e == hipSuccess) e = out.put(st);
   };
   // Emission in depth order into buffer 0, which holds the sorted tile counts until then.
-  st.a.emit_reduce = EmitReduceArgs{(const uint32_t*)v[0], rec, flags, L.VN, (const unsigned long long*)hdr, partE, k[1]};
+  st.a.emit_reduce = EmitReduceArgs{(const uint32_t*)v[0], rec, (const unsigned long long*)hdr, partE, k[1]};
   put(kStEmitReduce, nb);
-  st.a.emit_partials = EmitPartialsArgs{partE, hdr, nb, D.cap};
+  st.a.emit_partials = EmitPartialsArgs{partE, (const unsigned long long*)hdr};
   put(kStEmitPartials, 1);
   uint32_t* owner = (uint32_t*)(dp + D.owner);
   st.a.emit_offsets = EmitOffsetsArgs{(const uint32_t*)k[1], (const uint32_t*)partE, (const unsigned long long*)hdr,
