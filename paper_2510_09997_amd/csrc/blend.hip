@@ -901,10 +901,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     // forward).  Other lanes compute discarded values.
     const uint64_t lm = ballot64(__builtin_amdgcn_fmed3f(power, bc.y, 0.0f) == power) &
                         ballot64(__float_as_uint(bc.z) < last);
-    if (kCount) {
-      n_walk += 64;
-      n_live += (unsigned long long)__popcll(lm);
-    }
+    if (kCount) n_live += (unsigned long long)__popcll(lm);
     if (lm == 0ull) return;
     const float G = cexp_core(power);
     const float prod = c.y * G;
@@ -951,6 +948,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     }
     const uint64_t mask = ballot64(rel);
     const uint32_t n = (uint32_t)__builtin_popcountll(mask);
+    if (kCount) n_walk += 64ull * n;
     if (rel) {
       const uint32_t slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
       S.s0[slot] = make_float4(g0.x, g0.y, -0.5f * g1.x, -g1.y);
