@@ -76,6 +76,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss_bwd(
   const float alpha = frcp(1.0f + fexp(-op));
   const float r = fmaxf(dc, 0.0f);
   const float iden = frcp(2.f * r * r + prm.eps), i2 = 1.44269504088896341f * iden;
+  constexpr float kMaxQ = 3e38f;   // (an infinite q comes with t = 0; their product is 0, not NaN)
   float st = 0.f, stq = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;   // sums of t, t q, t k (mu - c)
   if (dL_deta) {
     for (int v = 0; v < V; ++v) {
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss_bwd(
       const float x = fmaf_(ex, ex, fmaf_(ey, ey, ez * ez)) * C.k[0];
       float t = (C.k[1] * alpha) * __builtin_amdgcn_exp2f(-(x * i2));
       t = valid ? t : 0.f;
-      const float tq = t * (x * iden), tk = t * C.k[0];
+      const float tq = t * fminf(x * iden, kMaxQ), tk = t * C.k[0];
       st += t;
       stq += tq;
       sx = fmaf_(tk, ex, sx);
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss_bwd(
         const float ex = mx - C.c[0], ey = my - C.c[1], ez = mz - C.c[2];
         const float x = fmaf_(ex, ex, fmaf_(ey, ey, ez * ez)) * C.k[0];
         const float t = (ga2 * alpha) * __builtin_amdgcn_exp2f(-(x * i2));
-        const float tq = t * (x * iden), tk = t * C.k[0];
+        const float tq = t * fminf(x * iden, kMaxQ), tk = t * C.k[0];
         st += t;
         stq += tq;
         sx = fmaf_(tk, ex, sx);
