@@ -610,10 +610,10 @@ __device__ __forceinline__ uint32_t row_starts(const RowArgs& a, uint32_t c, uin
   if (c != 0u) return total;
   const uint32_t rows = a.rows, d0 = threadIdx.x * kPer;
   const uint32_t room = a.units_max - rows;   // units of full length that fit
-  const uint32_t unit = kUnit * max(1u, (total + kUnit * room - 1u) / (kUnit * room));
+  const uint32_t unit = unit_pairs(total, room);
   uint32_t s = 0;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) s += (tot[k] + unit - 1u) / unit;
+  for (int k = 0; k < kPer; ++k) s += ceil_div(tot[k], unit);
   uint32_t units;
   uint32_t u = block_exclusive_scan(s, sm, units);
 #pragma unroll
@@ -630,8 +630,8 @@ __device__ __forceinline__ uint32_t row_starts(const RowArgs& a, uint32_t c, uin
       a.tab.start[r] = first[k];
       a.tab.ustart[r] = u;
       a.tab.pairs[r] = 0u;
-      const uint32_t nu = (tot[k] + unit - 1u) / unit;
-      for (uint32_t j = 0; j < nu; ++j) a.tab.urow[u + j] = r;
+      const uint32_t nu = ceil_div(tot[k], unit);
+      for (uint32_t j = 0; j < nu && u + j < a.units_max; ++j) a.tab.urow[u + j] = r;
       u += nu;
     }
   }
@@ -695,16 +695,17 @@ __global__ __launch_bounds__(kBlock) void k_row_down(RowArgs a) {
 }
 
 // ----------------------------------------------------------------------------------- columns
-// A unit is a run of consecutive pairs of one tile row.
+// A unit is a run of `count` consecutive pairs of one tile row.  (The loops below count from its first
+// pair: positions near 2^32 would wrap past the run's end.)
 struct Unit {
-  uint32_t row, lo, hi;
+  uint32_t row, lo, count;
   bool first;   // of its row
 };
 __device__ __forceinline__ Unit unit_of(const ColArgs& a, uint32_t u) {
   const uint32_t row = a.tab.urow[u], len = (uint32_t)a.hdr[kHdrUnit];
   const uint32_t j = u - a.tab.ustart[row], s = a.tab.start[row], e = a.tab.start[row + 1];
-  const uint32_t lo = s + j * len;
-  return Unit{row, lo, lo + len < e ? lo + len : e, j == 0u};
+  const uint32_t lo = s + j * len;   // (below e)
+  return Unit{row, lo, min(e - lo, len), j == 0u};
 }
 
 // Per unit: pairs per column (+1 at the first column, -1 past the last, summed up).
@@ -716,16 +717,16 @@ __device__ __forceinline__ void col_up_body(const ColArgs& a, Blk b) {
   cnt[threadIdx.x] = 0u;
   if (threadIdx.x == 0) cnt[kColsMax] = 0u;
   __syncthreads();
-  for (uint32_t e0 = U.lo; e0 < U.hi; e0 += 2 * kBlock) {
+  for (uint32_t o0 = 0; o0 < U.count; o0 += 2 * kBlock) {
     uint32_t x[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const uint32_t e = e0 + j * kBlock + threadIdx.x;
-      x[j] = e < U.hi ? a.in[e].y : 0u;
+      const uint32_t o = o0 + j * kBlock + threadIdx.x;
+      x[j] = o < U.count ? a.in[U.lo + o].y : 0u;
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (e0 + j * kBlock + threadIdx.x < U.hi) {
+      if (o0 + j * kBlock + threadIdx.x < U.count) {
         atomicAdd(&cnt[x[j] & 0xFFu], 1u);
         atomicAdd(&cnt[(x[j] >> 8) + 1u], 0xFFFFFFFFu);
       }
@@ -831,20 +832,20 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
   if (U.first && t < width && mine) a.ranges[tile0 + t] = make_uint2(at, at + mine);
   const uint32_t D = (uint32_t)a.hdr[kHdrDup];
   const uint64_t lt = lanemask_lt();
-  for (uint32_t e0 = U.lo; e0 < U.hi; e0 += kSubUnit) {
-    // The sub-unit's pairs: wave w the 128 from e0 + 128 w.
+  for (uint32_t o0 = 0; o0 < U.count; o0 += kSubUnit) {
+    // The sub-unit's pairs: wave w the 128 from o0 + 128 w.
     uint2 rp[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const uint32_t e = e0 + 128u * w + 64u * j + lane;
-      rp[j] = e < U.hi ? a.in[e] : make_uint2(0u, 0u);
+      const uint32_t o = o0 + 128u * w + 64u * j + lane;
+      rp[j] = o < U.count ? a.in[U.lo + o] : make_uint2(0u, 0u);
     }
     uint32_t* cnt = S.cnt[w];
     for (uint32_t i = lane; i <= kColsMax; i += 64) cnt[i] = 0u;
     wave_lds_fence();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (e0 + 128u * w + 64u * j + lane < U.hi) {
+      if (o0 + 128u * w + 64u * j + lane < U.count) {
         atomicAdd(&cnt[rp[j].y & 0xFFu], 1u);
         atomicAdd(&cnt[(rp[j].y >> 8) + 1u], 0xFFFFFFFFu);
       }
@@ -875,7 +876,7 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
     const bool staged = total <= kStagePairs;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const bool in = e0 + 128u * w + 64u * j + lane < U.hi;
+      const bool in = o0 + 128u * w + 64u * j + lane < U.count;
       const uint32_t x0 = rp[j].y & 0xFFu, len = in ? (rp[j].y >> 8) - x0 + 1u : 0u;
       const uint32_t inc = wave_scan_inc(len), off = inc - len;
       const uint32_t rel = x0 - off;

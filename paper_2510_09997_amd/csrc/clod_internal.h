@@ -48,6 +48,12 @@ constexpr uint32_t kDepthBins0 = 1u << kDepthBits0;
 constexpr uint32_t kRowBinsMax = 2048;     // tile rows of a batch in the row path
 constexpr uint32_t kColsMax = 256;         // tile columns (and rows) of a view in the row path
 constexpr uint32_t kUnit = 512;            // least row pairs per column unit
+// Row pairs per column unit so that `total` of them (any count below 2^32: no term wraps) in all the
+// rows make at most rows + room units, and kUnit where that does.
+__host__ __device__ constexpr uint32_t ceil_div(uint32_t a, uint32_t b) { return a / b + (a % b != 0u ? 1u : 0u); }
+__host__ __device__ constexpr uint32_t unit_pairs(uint32_t total, uint32_t room) {
+  return kUnit * (total > kUnit * room ? ceil_div(total, kUnit * room) : 1u);
+}
 constexpr uint32_t kOrderCopies = 32;      // copies of the length-class counters
 __host__ __device__ constexpr uint32_t radix_blocks(uint32_t bins) {
   return kHistWords / (4u * bins) < kRadixBlocksMax ? kHistWords / (4u * bins) : kRadixBlocksMax;
