@@ -211,8 +211,8 @@ clod_status clod_scene_reorder(const clod_scene *src, const clod_scene_grad *dst
    caller workspace.  The per-view constants, per-block partials and the work list live in a
    library-owned device array of CLOD_LOD_SCRATCH_BYTES per GPU (held by each GPU the library
    runs on until the process ends); the call allocates nothing.  Inputs whose workspace exceeds
-   it (about 4 bytes per Gaussian plus about 24 KiB per view, plus 128 KiB per budgeted view)
-   are rejected with CLOD_E_ARG before anything is launched.  Every call on one GPU shares that
+   it (about 4 bytes per Gaussian plus about 40 KiB per view, and 26 KiB more per view in batches
+   with a budget) are rejected with CLOD_E_ARG before anything is launched.  Every call on one GPU shares that
    array and leaves its contents behind (nothing in it needs to start cleared): calls that
    overlap on one GPU (other streams or threads) race and must be serialised by the caller. */
 #define CLOD_LOD_SCRATCH_BYTES (64u << 20)

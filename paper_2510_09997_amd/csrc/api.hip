@@ -71,7 +71,7 @@ DupLayout dup_layout(int64_t cap) {
 
 // Sums over a batch's views, and its largest view in tiles.
 struct HostTotals {
-  uint32_t tiles = 0, loss_blocks = 0, widest = 0, tallest = 0;
+  uint32_t tiles = 0, loss_blocks = 0, ssim_regions = 0, widest = 0, tallest = 0;
   int64_t pixels = 0, rows = 0;
 };
 
@@ -93,6 +93,7 @@ static clod_status host_views(int32_t V, const clod_view* vh, HostView* hv, Host
     tb += (uint64_t)h.tiles_x * h.tiles_y;
     pb += (uint64_t)c.width * c.height;
     lb += h.loss_blocks;
+    t.ssim_regions += (uint32_t)(((c.width + kSsimRegionW - 1) / kSsimRegionW) * ((c.height + kSsimRegionH - 1) / kSsimRegionH));
     t.rows += h.tiles_y;
     if ((uint32_t)h.tiles_x > t.widest) t.widest = (uint32_t)h.tiles_x;
     if ((uint32_t)h.tiles_y > t.tallest) t.tallest = (uint32_t)h.tiles_y;
@@ -113,6 +114,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.V = V;
   L.VN = n * (int64_t)V;
   L.tiles_total = tiles_total;
+  L.ssim_regions = t.ssim_regions;
   L.pixels_total = pixels_total;
   L.scan_blocks = (int32_t)((L.VN + kScanChunk - 1) / kScanChunk);
   L.rec_groups = (uint32_t)((L.VN + (int64_t)kRecChunk * kRecGroup - 1) / ((int64_t)kRecChunk * kRecGroup));
@@ -122,8 +124,9 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
     L.row_bins = kBlock;
     while (L.row_bins < L.rows) L.row_bins *= 2;
     L.cols = (t.widest + 63u) / 64u * 64u;
-    L.units_max = kHistWords / L.cols;
   }
+  const uint32_t hist = L.VN > 0 ? hist_words(L.VN, L.rows, L.cols, L.row_path ? t.tallest : 0u) : 0u;
+  if (L.row_path) L.units_max = hist / L.cols;
   size_t o = 0;
   L.hdr = o; o = align256(o + kHdrWords * 8);
   L.vinfo = o; o = align256(o + (size_t)V * sizeof(DevView));
@@ -132,7 +135,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.gdmax = o; o = align256(o + (size_t)V * 4);
   L.loss_acc = o; o = align256(o + (size_t)V * 4);
   L.ssim_acc = o; o = align256(o + (size_t)V * 4);
-  L.loss_part = o; o = align256(o + ((size_t)tiles_total * 6 + (size_t)pixels_total * 3 / kLossChunk + V) * 4);
+  L.loss_part = o; o = align256(o + ((size_t)L.ssim_regions * 6 + (size_t)pixels_total * 3 / kLossChunk + V) * 4);
   L.kpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
   L.cpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4 * 4);
   L.gpart = o; o = align256(o + (size_t)kMaxProjBlocks * V * 4);
@@ -147,10 +150,10 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.order = o; o = align256(o + (size_t)tiles_total * 4);
   L.tord = o; o = align256(o + ((size_t)kTileOrderWords + (size_t)kOrderCopies * kTileBuckets) * 4);
   L.pair_part = o; o = align256(o + (size_t)tiles_total * 3 * 8);
-  L.sort_hist = o; o = align256(o + (L.VN > 0 ? (size_t)kHistWords * 4 : 0));
+  L.sort_hist = o; o = align256(o + (size_t)hist * 4);
   L.sort_stat = o; o = align256(o + (size_t)L.scan_blocks * sizeof(DepthStat));
   L.sort_gcount = o; o = align256(o + (size_t)L.rec_groups * kLineWords * 4);
-  L.sort_gsum = o; o = align256(o + (L.VN > 0 ? (size_t)kDepthCounterWords * 4 : 0));
+  L.sort_gsum = o; o = align256(o + (L.VN > 0 ? sum_words(L.VN, L.row_bins) * 4 : 0));
   L.row_tab = o; o = align256(o + (L.row_path ? (4 * ((size_t)L.rows + 1) + L.units_max) * 4 : 0));
   L.tcount = o; o = align256(o + (L.row_path ? (size_t)tiles_total * 4 : 0));
   L.gscreen = o; o = align256(o + (size_t)L.VN * kGscreen * 4);
@@ -226,9 +229,6 @@ static clod_status prepare(const clod_batch* b, bool need_full_ws, Ctx& cx) {
   bool any_budget = false;
   for (int v = 0; v < b->n_views; ++v) any_budget = any_budget || b->views_host[v].budget > 0;
   cx.L = make_layout(n, b->n_views, totals, any_budget);
-  for (int v = 0; v < b->n_views; ++v)
-    cx.L.ssim_regions += (uint32_t)(((cx.hv[v].width + kSsimRegionW - 1) / kSsimRegionW) *
-                                    ((cx.hv[v].height + kSsimRegionH - 1) / kSsimRegionH));
   // The per-view area and the projection work list precede the per-(view, Gaussian) planes.
   const size_t need = need_full_ws ? cx.L.total : cx.L.flags;
   if (b->ws_bytes < need) return fail(CLOD_E_ARG, "ws_bytes %zu < required %zu", b->ws_bytes, need);

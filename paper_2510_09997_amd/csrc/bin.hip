@@ -117,18 +117,6 @@ __device__ __forceinline__ void wave_expand(uint32_t off, uint32_t len, uint32_t
 }
 
 // ------------------------------------------------------------------------------ radix geometry
-// N elements in wave chunks of kw (a multiple of 64), four consecutive chunks per block, at most
-// radix_blocks(bins) blocks (the histogram holds four rows of `bins` counts per block).
-constexpr uint32_t kWaveMin = 256;   // least elements per wave: below it the prefix reads cost more
-struct RadixGeom {
-  uint32_t kw, nb;
-};
-__device__ __forceinline__ RadixGeom radix_geom(uint64_t N, uint32_t bins) {
-  const uint64_t most = radix_blocks(bins);
-  uint64_t kw = (N + most * 256u - 1) / (most * 256u) * 64u;
-  if (kw < kWaveMin) kw = kWaveMin;
-  return RadixGeom{(uint32_t)kw, (uint32_t)((N + 4 * kw - 1) / (4 * kw))};
-}
 // Chunk of a block: consecutive chunks lie on one XCD (blocks go round-robin to the eight XCDs).
 // A block without one gets an index of nb or more.
 __device__ __forceinline__ uint32_t xcd_chunk(uint32_t b, uint32_t nb) {
@@ -264,7 +252,7 @@ __device__ __forceinline__ uint32_t rendered_mask(const uint8_t* __restrict__ fl
 __device__ __forceinline__ void rec_count_body(const DepthArgs& a, Blk b) {
   __shared__ uint32_t sm[4];
   for (int64_t q = (int64_t)b.id * kBlock + threadIdx.x; q < a.range_words; q += (int64_t)b.n * kBlock) a.ranges[q] = 0u;
-  zero_words(a.gnext, kGroups * kDepthBins0, b);
+  zero_words(a.gnext, a.sums * kDepthBins0, b);
   const int64_t j0 = (int64_t)b.id * kRecChunk + 16 * (int64_t)threadIdx.x;
   const uint32_t r = wave_sum((uint32_t)__popc(rendered_mask(a.flags, a.VN, j0)));
   if (lane_id() == 0) sm[threadIdx.x >> 6] = r;
@@ -491,7 +479,7 @@ __device__ __forceinline__ void depth_down_body(const DepthArgs& a, Blk b, Radix
   __shared__ uint32_t sm[4];
   const DepthState D = depth_state(a);
   if (D.over) return;
-  if (a.gnext) zero_words(a.gnext, kGroups * (a.pass == 2 ? a.row_bins : 1u << depth_bits(a.pass + 1, D.nbits)), b);
+  if (a.gnext) zero_words(a.gnext, a.sums * (a.pass == 2 ? a.row_bins : 1u << depth_bits(a.pass + 1, D.nbits)), b);
   const uint32_t bins = 1u << D.bits, N = D.N;
   const RadixGeom G = radix_geom(N, bins);
   const uint32_t c = xcd_chunk(b.id, G.nb);

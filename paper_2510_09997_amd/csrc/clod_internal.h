@@ -39,7 +39,7 @@ constexpr int kMaxSortBlocks = 1024;
 // Depth sort and row / column partitions (bin.hip): blocks per radix pass, blocks per group sum,
 // words of the wave count rows, digits of the first depth pass and of the widest partition.
 constexpr uint32_t kRadixBlocksMax = 1024;
-constexpr uint32_t kGroup = 32, kGroups = kRadixBlocksMax / kGroup;
+constexpr uint32_t kGroup = 32;
 constexpr uint32_t kHistWords = 1u << 21;
 constexpr uint32_t kRecChunk = 16 * kBlock;  // flags per block of the compaction, chunks per group sum
 constexpr uint32_t kRecGroup = 64, kLineWords = 32;
@@ -57,6 +57,39 @@ __host__ __device__ constexpr uint32_t unit_pairs(uint32_t total, uint32_t room)
 constexpr uint32_t kOrderCopies = 32;      // copies of the length-class counters
 __host__ __device__ constexpr uint32_t radix_blocks(uint32_t bins) {
   return kHistWords / (4u * bins) < kRadixBlocksMax ? kHistWords / (4u * bins) : kRadixBlocksMax;
+}
+constexpr uint32_t kWaveMin = 256;   // least elements per wave: below it the prefix reads cost more
+// N elements in wave chunks of kw (a multiple of 64), four consecutive chunks per block, at most
+// radix_blocks(bins) blocks (the histogram holds four rows of `bins` counts per block).
+struct RadixGeom {
+  uint32_t kw, nb;
+};
+__host__ __device__ constexpr RadixGeom radix_geom(uint64_t N, uint32_t bins) {
+  const uint64_t most = radix_blocks(bins);
+  uint64_t kw = (N + most * 256u - 1) / (most * 256u) * 64u;
+  if (kw < kWaveMin) kw = kWaveMin;
+  return RadixGeom{(uint32_t)kw, (uint32_t)((N + 4 * kw - 1) / (4 * kw))};
+}
+// Blocks that a radix pass over `most` elements, or fewer, can need.
+constexpr uint32_t pass_blocks(int64_t most) {
+  const int64_t b = (most + 4 * kWaveMin - 1) / (4 * kWaveMin);
+  return b < (int64_t)kRadixBlocksMax ? (uint32_t)b : kRadixBlocksMax;
+}
+// Words of counts that a batch of VN (view, Gaussian) records can need: four rows of counts per block
+// of a radix pass, and kUnit-pair column units of `cols` counts for a pair per record and tile row of
+// the tallest view, in units besides the ones that end the `rows` rows.  At most kHistWords, where the
+// blocks are capped and the units grow; sized to it for every batch the two tables took 8.9 MB, more
+// than all else together below some 200,000 records.
+constexpr uint32_t hist_words(int64_t VN, uint32_t rows, uint32_t cols, uint32_t tallest) {
+  const uint64_t radix = 4ull * kRowBinsMax * pass_blocks(VN);
+  const uint64_t units = ((uint64_t)((VN * tallest + kUnit - 1) / kUnit) + rows) * cols;
+  const uint64_t w = radix > units ? radix : units;
+  return w < kHistWords ? (uint32_t)w : kHistWords;
+}
+// Groups of blocks of a pass over VN records, and the words of their sums (three depth passes, rows).
+constexpr uint32_t sum_groups(int64_t VN) { return (pass_blocks(VN) + kGroup - 1) / kGroup; }
+constexpr size_t sum_words(int64_t VN, uint32_t row_bins) {
+  return (size_t)sum_groups(VN) * (kDepthBins0 + 2 * kRowBinsMax + row_bins);
 }
 constexpr int kMaxProjBlocks = 2048;      // per-block partial reductions of the per-Gaussian passes
 constexpr int kGscreen = 9;                // du, dv, dA, dB, dC, dalpha'', dr, dg, db (interleaved per record)
@@ -80,13 +113,12 @@ struct DevView {
 };
 
 // Radix select of the budgeted mask: bins per level, chunks of a view, and per view three levels of
-// bins and the chunk counts (the workspace keeps kSelBytes for them).
+// bins and the chunk counts.
 constexpr uint32_t kSelBins = 2048;
 constexpr int kSelBlocks = 512;
 constexpr int kSelViews = 4, kSelFirst = 768;   // level 0: views of a block, parts of the scene
 constexpr uint32_t kSelWords = 3 * kSelBins + kSelBlocks;
-constexpr size_t kSelBytes = 128 * 256 * 4;
-static_assert(kSelWords * 4 <= kSelBytes, "select bins");
+constexpr size_t kSelBytes = 4 * (size_t)kSelWords;
 
 // Workspace header words (uint64): pairs, overflow flag, rendered records; of the depth sort the
 // subtrahend of the keys and their bit length; row pairs per column unit and column units.
@@ -98,8 +130,6 @@ struct DepthStat {
   unsigned long long pairs;
   uint32_t kmax, reserved;
 };
-
-constexpr uint32_t kDepthCounterWords = kGroups * (kDepthBins0 + 3 * kRowBinsMax);
 
 // Per tile row of the batch (one more entry closes the ranges): first tile, first row pair, first
 // column unit; tile pairs of the row; and the row of every column unit.
@@ -635,7 +665,7 @@ struct DepthArgs {   // the passes of the depth sort share it
   uint32_t* gnext;      // group sums of the pass after this one, cleared here
   DepthStat* stat; uint32_t* part; uint32_t* gcount; const uint2* in; uint2* out; uint32_t* kout; uint32_t* vout; int64_t cap;
   uint32_t* tord; uint32_t* ranges; int64_t range_words;
-  uint32_t chunks, groups, tord_words, row_bins; int32_t pass, pad;
+  uint32_t chunks, groups, tord_words, row_bins; int32_t pass; uint32_t sums;   // sums: groups of blocks
 };
 struct RowArgs {
   const DevView* views; int32_t V; uint32_t rows; int64_t n; unsigned long long* hdr; const uint32_t* rect;

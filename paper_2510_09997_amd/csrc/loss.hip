@@ -149,7 +149,7 @@ hipError_t launch_loss(const Layout& L, void* ws, int64_t n, const float* rgb, c
   float* acc = (float*)(w + L.loss_acc);
   float* sacc = (float*)(w + L.ssim_acc);
   float* spart = (float*)(w + L.loss_part);                   // [regions][3] (SSIM, L1) partials
-  float* lpart = spart + 6 * (int64_t)L.tiles_total;          // [loss blocks] L1 partials
+  float* lpart = spart + 6 * (int64_t)L.ssim_regions;         // [loss blocks] L1 partials
   const DevView* views = (const DevView*)(w + L.vinfo);
   if (lambda_dssim > 0.f) {   // the L1 part in the same pass
     hipError_t e = launch_ssim(L, ws, rgb, target, lambda_dssim, s_max, spart, dL_drgb, s);

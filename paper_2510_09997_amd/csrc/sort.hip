@@ -495,12 +495,11 @@ int sorted_buffer(const Layout& L) { return L.row_path || (tile_passes(L.tiles_t
 // binning, so that a binning finds them clear.
 static void depth_counters(const Layout& L, char* w, uint32_t* (&gsum)[4]) {
   gsum[0] = (uint32_t*)(w + L.sort_gsum);
-  for (int k = 1; k < 4; ++k) gsum[k] = gsum[0] + kGroups * (kDepthBins0 + (uint32_t)(k - 1) * kRowBinsMax);
+  for (int k = 1; k < 4; ++k) gsum[k] = gsum[0] + sum_groups(L.VN) * (kDepthBins0 + (uint32_t)(k - 1) * kRowBinsMax);
 }
 // Blocks that the records of a batch can need in a pass (their number is known on the device only).
 static uint32_t record_blocks(const Layout& L, const DupLayout& D) {
-  const int64_t most = L.VN < D.cap ? L.VN : D.cap, b = (most + 4 * kWaveMin - 1) / (4 * kWaveMin);
-  return b < (int64_t)kRadixBlocksMax ? (uint32_t)b : kRadixBlocksMax;
+  return pass_blocks(L.VN < D.cap ? L.VN : D.cap);
 }
 
 static hipError_t depth_sort(const Layout& L, char* w, const DupLayout& D, char* dp, const Sink& out) {
@@ -525,6 +524,7 @@ static hipError_t depth_sort(const Layout& L, char* w, const DupLayout& D, char*
   a.ranges = (uint32_t*)(w + L.ranges);
   a.range_words = L.row_path ? 0 : 2 * (int64_t)L.tiles_total;
   a.row_bins = L.row_path ? L.row_bins : 0u;
+  a.sums = sum_groups(L.VN);
   uint2* const buf[2] = {(uint2*)(dp + D.keys0), (uint2*)(dp + D.keys1)};
   hipError_t e = hipSuccess;
   auto put = [&](int32_t kind, uint32_t items) {
