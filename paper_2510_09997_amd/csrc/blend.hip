@@ -230,7 +230,6 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
     const uint32_t row = lane >> 4;
     struct Set {
       float4 a; float2 c; float2 b;   // (u, v, -A/2, -B), (-C/2, alpha''), (cut, list position)
-      float k[4];                     // the row's channel of the four entries
     };
     const float* colour = row == 0u ? &s1[0].z : row == 1u ? &s1[0].w : &s2[0].x;
     auto load = [&](const uint32_t k, Set& q) {
@@ -238,10 +237,14 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       q.a = s0[fr];
       q.c = *reinterpret_cast<const float2*>(&s1[fr].x);
       q.b = *reinterpret_cast<const float2*>(&s2[fr].y);
-#pragma unroll
-      for (uint32_t e = 0; e < 4; ++e) q.k[e] = colour[4u * (k + e)];
     };
     auto group = [&](const uint32_t k, const Set& q) {
+      // The row's channel of the four entries: requested here, there before the opacities are.  (In
+      // the two sets they took eight registers more, and the kernel spilled: 382 us for the five-frame
+      // batch of 3M at seven waves per SIMD, now 371.)
+      float col[4];
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) col[e] = colour[4u * (k + e)];
       const float dx = q.a.x - pcx, dy = q.a.y - pcy;
       const float power = fmaf_(q.a.z * dx, dx, fmaf_(q.c.x * dy, dy, (q.a.w * dx) * dy));
       const uint32_t left = n - k;   // slots at or past n hold stale entries
@@ -265,7 +268,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float w = al4[e] * Tn;
-        sum = fmaf_(q.k[e], w, sum);
+        sum = fmaf_(col[e], w, sum);
         Tn = Tn * (1.0f - al4[e]);
       }
       if ((ballot64(Tn < kTmin) & ~dm) == 0ull && finite) {
@@ -285,7 +288,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
         const uint64_t take = ballot64(al4[e] > 0.0f) & ~dm, ends = ballot64(T * (1.0f - al4[e]) < kTmin) & take;
         if (__builtin_amdgcn_inverse_ballot_w64(take & ~ends)) {
           const float w = al4[e] * T;
-          cr = fmaf_(q.k[e], w, cr);
+          cr = fmaf_(col[e], w, cr);
           T = T * (1.0f - al4[e]);
         }
         last = __builtin_amdgcn_inverse_ballot_w64(take & ~ends & rows) ? count : last;
@@ -641,10 +644,10 @@ __device__ __forceinline__ uint32_t blend_items(const BlendArgs& a) {
   return long_grid(long_tiles(a.tord, a.long_max)) + xcd_grid(a.tiles_total);
 }
 
-// Per-batch launch: one workgroup per tile (four per long tile).  Seven waves per SIMD (the 4x4
-// walk alone would take the kernel to 76 registers and six: 2 to 4 % on frames without long tiles).
+// Per-batch launch: one workgroup per tile (four per long tile).  Seven waves per SIMD, 72 registers
+// (six cost 2 to 4 % on frames without long tiles); the counting instance needs 78, so six.
 template <bool kCount>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_blend_fwd(BlendArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kCount ? 6 : 7))) void k_blend_fwd(BlendArgs a) {
   __shared__ TileLds S;
   blend_item<kCount>(a, blockIdx.x, S);
 }
