@@ -272,6 +272,9 @@ __global__ __launch_bounds__(kBlock) void k_frustum_max(FrustumArgs a) {
   frustum_max_body(a, grid_blk(), words_dyn);
 }
 
+// log2(e) q at which the contract's exponential of -q becomes 0 (q = 86).
+constexpr float kZeroExp = 124.0717f;
+
 // Factors of Eq. (2) for the loops below, beside the camera in LDS (every block fills its own table).
 __device__ __forceinline__ CamLds classify_cam(const DevView& Vw, unsigned long long dk) {
   CamLds L = cam_lds(Vw);
@@ -281,18 +284,29 @@ __device__ __forceinline__ CamLds classify_cam(const DevView& Vw, unsigned long 
   L.k[2] = Vw.s_v;
   return L;
 }
+// A view without a budget whose threshold is 0 keeps every alpha'' above 0.
+__device__ __forceinline__ bool zero_threshold(const DevView& Vw) { return Vw.budget <= 0 && Vw.tau_sv == 0.0f; }
 // Counting: (s_v / d_max)^2 (NaN: no estimate), log2 of the mask's threshold, and the squared
-// distance below which a Gaussian cannot hold the frustum maximum.
-__device__ __forceinline__ CamLds count_cam(const DevView& Vw, unsigned long long dk, float eps) {
+// distance below which a Gaussian cannot hold the frustum maximum.  zeros: some view of the batch has
+// a threshold of 0 (see lod_item).
+__device__ __forceinline__ CamLds count_cam(const DevView& Vw, unsigned long long dk, float eps, bool zeros) {
   CamLds L = cam_lds(Vw);
   const float dmax = dmax_from_key(dk), r = Vw.s_v / dmax, kv = r * r;
   // The mask keeps alpha'' above tau s_v, or above (or at) the value of the budget's smallest key.
   const float thr = Vw.budget > 0 ? __uint_as_float((uint32_t)(Vw.mkey >> 32)) : Vw.tau_sv;
-  const bool ok = in_exponents<60>(kv) && in_exponents<100>(thr) && eps > 1e-20f;
-  L.k[0] = ok ? kv : __builtin_nanf("");
-  L.k[1] = __builtin_amdgcn_logf(thr);
+  const bool zero = zero_threshold(Vw), all = Vw.budget > 0 && Vw.mkey == 0ull;   // all: the budget is the whole scene
+  const bool ok = in_exponents<100>(kv) && eps > 1e-36f && (zero || (thr >= 0x1p-100f && !zeros));
+  L.k[0] = all ? 0.0f : ok ? kv : __builtin_nanf("");
+  L.k[1] = all ? -__builtin_inff() : zero ? -kZeroExp : __builtin_amdgcn_logf(thr);
   L.k[2] = dk ? (dmax * 0.999999f) * dmax : __builtin_inff();
   return L;
+}
+// Whether some view has a threshold of 0 (every thread of the block takes part; s_v is 1 or more).
+__device__ __forceinline__ bool any_zero_threshold(const DevView* views, int V, float tau) {
+  if (tau > 0.0f) return false;
+  bool z = false;
+  for (int v = threadIdx.x; v < V; v += kBlock) z = z || zero_threshold(views[v]);
+  return __builtin_amdgcn_readfirstlane(__syncthreads_or(z ? 1 : 0)) != 0;
 }
 
 // Whether Gaussian i at distance d, in the frustum, holds the frustum maximum: its index competes
@@ -468,13 +482,23 @@ __global__ __launch_bounds__(kBlock) void k_classify(ClassifyArgs a) {
 // Mask: alpha'' > threshold is log2(alpha) - q log2(e) > log2(threshold), where the left side needs
 // no root, quotient or exponential per view.  alpha'' of the contract differs from the exact value
 // by a factor within 2^(5e-6 q + 1e-6) (q's roundings, E's 2 ulp, the last product), and the
-// estimate's by less than that (hardware log2 and reciprocal, five products), both far inside the
-// margin below; NaN and any case the factors cannot express (count_cam) stay open.
+// estimate's by less than that (hardware log2 and reciprocal, five products; a product that underflows
+// is off by 2^-149 / eps at most), both far inside the margin below; NaN and any case the factors
+// cannot express (count_cam) stay open.
+//
+// A threshold of 0 keeps alpha'' > 0, which ends where the contract's exponential does, at log2(e) q =
+// kZeroExp, for every alpha above 2^-20 (the product is then at least 2^-145).  In a batch with such
+// views la is 0, or NaN for the fainter Gaussians, and the views' threshold is 2^-kZeroExp; a budget
+// of the whole scene keeps everything (kv = 0).  Other views of such a batch get no estimate.  16 views of
+// 6M Gaussians with tau = 0 took 697 us in full and 1,008 us with every mask left open, now 358 us;
+// with budgets of the whole scene 960, 1,075 and now 432 us.
 struct LodItem {
   float la, iden;   // log2(alpha), log2(e) / (2 max(sigma_d, 0)^2 + eps)
 };
-__device__ __forceinline__ LodItem lod_item(float opac, float decay, float eps) {
-  return LodItem{__builtin_amdgcn_logf(sigmoid_c(opac)), 1.44269504088896341f * __builtin_amdgcn_rcpf(decay_den(decay, eps))};
+__device__ __forceinline__ LodItem lod_item(float opac, float decay, float eps, bool zeros) {
+  const float la = __builtin_amdgcn_logf(sigmoid_c(opac));
+  return LodItem{!zeros ? la : la > -20.0f ? 0.0f : __builtin_nanf(""),
+                 1.44269504088896341f * __builtin_amdgcn_rcpf(decay_den(decay, eps))};
 }
 // (Lane masks of the wave.)
 __device__ __forceinline__ void mask_estimate(const LodItem& I, const CamLds& L, float d2, uint64_t& kept, uint64_t& dropped) {
@@ -532,11 +556,12 @@ __device__ __forceinline__ void count_body(const ClassifyArgs& a, Blk b, uint32_
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(words + kCamWords * V);
   uint32_t* imin = words + (kCamWords + 2) * V;
   uint32_t* rend = imin + V;
+  const bool zeros = any_zero_threshold(views, V, prm.tau);
   for (int j = threadIdx.x; j < V; j += kBlock) {
     cnt[j] = 0ull;
     imin[j] = 0xFFFFFFFFu;
     rend[j] = 0u;
-    cam[j] = count_cam(views[j], dmax_key[j], prm.eps);
+    cam[j] = count_cam(views[j], dmax_key[j], prm.eps, zeros);
   }
   if (threadIdx.x == 0) sbase = 0;
   __syncthreads();
@@ -554,7 +579,7 @@ __device__ __forceinline__ void count_body(const ClassifyArgs& a, Blk b, uint32_
       it[k] = LodItem{sc.opacity[i], sc.decay[i]};
     }
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) it[k] = lod_item(it[k].la, it[k].iden, prm.eps);
+    for (int k = 0; k < kItems; ++k) it[k] = lod_item(it[k].la, it[k].iden, prm.eps, zeros);
     uint64_t vm[kItems];   // lanes with a Gaussian
 #pragma unroll
     for (int k = 0; k < kItems; ++k) vm[k] = ballot64(b0 + k * kBlock + threadIdx.x < hi);
@@ -605,7 +630,7 @@ __device__ __forceinline__ void count_body(const ClassifyArgs& a, Blk b, uint32_
           const float d2 = cam_distance2(C, px, py, pz, ex, ey, ez);
           if (__builtin_amdgcn_inverse_ballot_w64(F)) dmax_tie(&imin[v], __builtin_sqrtf(d2), dmax_key[v], i);
           uint64_t kept, dropped;
-          mask_estimate(lod_item(sc.opacity[i], sc.decay[i], prm.eps), C, d2, kept, dropped);
+          mask_estimate(lod_item(sc.opacity[i], sc.decay[i], prm.eps, zeros), C, d2, kept, dropped);
           const uint64_t M = (kept | (ballot64(mask_exact(sc, Vw, dmax_key[v], d2, prm.eps, i)) & ~dropped)) & valid;
           uint64_t in, out;
           geo_estimate(Vw, geo_item(sc, i), prm.dilation, x, y, z, in, out);
@@ -691,9 +716,10 @@ __device__ __forceinline__ void count_rest_body(const ProjectArgs& a, Blk b, uin
   CamLds* cam = reinterpret_cast<CamLds*>(sdyn);
   uint32_t* soff = sdyn + kCamWords * V;
   uint32_t* scnt = soff + kSegWords;
+  const bool zeros = any_zero_threshold(views, V, prm.tau);
   for (int j = threadIdx.x; j < V; j += kBlock) {
     scnt[j] = 0u;
-    cam[j] = count_cam(views[j], a.dmax_key[j], prm.eps);
+    cam[j] = count_cam(views[j], a.dmax_key[j], prm.eps, zeros);
   }
   const uint32_t L = scan_segments(a.lcount, G, soff);
   const int64_t per = (n + G - 1) / G;
@@ -702,7 +728,7 @@ __device__ __forceinline__ void count_rest_body(const ProjectArgs& a, Blk b, uin
     const uint64_t valid = ballot64(e0 + lane_id() < L);
     const int64_t i = list_entry(a.list, soff, per, e0, e);
     const float mx = sc.mean[i], my = sc.mean[n + i], mz = sc.mean[2 * n + i];
-    const LodItem it = lod_item(sc.opacity[i], sc.decay[i], prm.eps);
+    const LodItem it = lod_item(sc.opacity[i], sc.decay[i], prm.eps, zeros);
     const float s2 = geo_item(sc, i);
     const float s0 = cexp(sc.log_scale[i]), s1 = cexp(sc.log_scale[n + i]), s2c = cexp(sc.log_scale[2 * n + i]);
     float Rm[9], S[9], w_, x_, y_, z_, rn;
