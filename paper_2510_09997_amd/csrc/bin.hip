@@ -917,7 +917,7 @@ __device__ __forceinline__ void col_order(const ColArgs& a, uint32_t blk, uint32
     uint32_t start = 0;
     for (uint32_t c = t + 1; c < (uint32_t)kTileBuckets; ++c) start += all[c];
     cur[t] = cnt[t] ? start + atomicAdd(&a.tord[kTileBuckets + t], cnt[t]) : 0u;
-    if (t == 0 && blk == 0) a.tord[kTileLongWord] = long_tile_count(all);
+    if (t == 0 && blk == 0) store_long_tiles(all, a.tord);
   }
   __syncthreads();
   for (uint32_t i = t0 + t; i < tiles && i < t0 + kTileOrderChunk; i += kBlock) {

@@ -5,7 +5,7 @@
 // are staged in LDS (one per lane or thread, a coalesced gather of the records) and read back
 // as LDS broadcasts; entries that provably cannot reach a quadrant are dropped for it (see
 // quadrant_mask).  Blocks take tiles longest list first (the order clod_bin_sort computes),
-// so the long tiles, not stragglers, start the launch.  Long lists (long_tile_count) are blended with
+// so the long tiles, not stragglers, start the launch.  Long lists (store_long_tiles) are blended with
 // 4x4-pixel blocks per wave (four workgroups per tile); a stage before the blend marks per entry the
 // blocks it may reach, and each block's wave walks only those entries.
 #include "clod_internal.h"
@@ -37,10 +37,10 @@ __host__ __device__ inline uint32_t long_grid(uint32_t long_tiles) {
   return (4 * long_tiles + 4 * kXcds - 1) / (4 * kXcds) * (4 * kXcds);
 }
 
-// The long tiles of this blend: the first tord[kTileLongWord] positions of the tile order
-// (written by the tile ordering stage), within the bound the launch was sized for.
-__device__ __forceinline__ uint32_t long_tiles(const uint32_t* tord, uint32_t bound) {
-  const uint32_t nl = tord[kTileLongWord];
+// The long tiles of this blend: the first *nlong positions of the tile order (written by the tile
+// ordering stage), within the bound the launch was sized for.
+__device__ __forceinline__ uint32_t long_tiles(const uint32_t* nlong, uint32_t bound) {
+  const uint32_t nl = *nlong;
   return nl < bound ? nl : bound;
 }
 
@@ -138,7 +138,7 @@ __device__ __forceinline__ uint32_t quadrant_mask1(float u, float v, float A, fl
   return (ddx * ddx + ddy * ddy <= rc * rc && ellipse_reaches<kB>(u, v, A, B, C, cut, x0, y0)) ? 1u : 0u;
 }
 
-// Long tiles (long_tile_count) are blended with 4x4-pixel blocks per wave: a wave walks only the
+// Long tiles (store_long_tiles) are blended with 4x4-pixel blocks per wave: a wave walks only the
 // entries that may reach its block, and sixteen waves share the tile instead of four.  The tile
 // order puts them first (longest first): they are taken by the leading workgroups of the launch.
 // They get their block tests from k_long_mask and their waves walk compacted lists (where the bit
@@ -181,7 +181,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   if (a.hdr[kHdrOverflow]) return;
   if (pos >= tiles_total) return;
   // The long tiles are taken as 4x4 blocks.
-  if ((kB == 8) != (pos >= long_tiles(a.tord, a.long_max))) return;
+  if ((kB == 8) != (pos >= long_tiles(a.nlong, a.long_max))) return;
   const int tile_i = (int)order[pos];
   const int v = view_of_tile(views, V, (uint32_t)tile_i);
   const DevView& Vw = views[v];
@@ -315,7 +315,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   // at list position j: staged in this wave's LDS slice, culled against the quadrant, then
   // walked.  The entries of a premasked long tile arrive already compacted to those that may reach
   // the 4x4 block (relc); elsewhere the batch is 64 consecutive entries and is culled here.
-  const bool pre = kB == 4 && pos < long_tiles(a.tord, a.pre_max);
+  const bool pre = kB == 4 && pos < long_tiles(a.nlong, a.pre_max);
   // next() runs between the staging and the walk: it requests the next batch's records, into the
   // same registers.
   auto batch = [&](const uint32_t j, const float4& g0, const float4& g1, const float4& g2,
@@ -562,7 +562,7 @@ __device__ __forceinline__ void long_mask_body(const LongMaskArgs& a, Blk b) {
   __shared__ uint32_t first[kBlock + 1], start[kBlock], len[kBlock], tile[kBlock], sm[4];
   __shared__ float ox[kBlock], oy[kBlock];
   if (a.hdr[kHdrOverflow]) return;
-  const uint32_t nl = long_tiles(a.tord, a.pre_max);
+  const uint32_t nl = long_tiles(a.nlong, a.pre_max);
   const uint32_t lane = lane_id(), t = threadIdx.x;
   const uint32_t gw = b.id * (kBlock / 64u) + (t >> 6), GW = b.n * (kBlock / 64u);
   for (uint32_t p0 = 0; p0 < nl; p0 += kBlock) {
@@ -628,7 +628,7 @@ __device__ __forceinline__ void long_item(uint32_t b, uint32_t& pos, uint32_t& s
 // sized for the most long tiles the pair capacity allows) map past the last tile and exit.
 template <bool kCount>
 __device__ __forceinline__ void blend_item(const BlendArgs& a, uint32_t b, TileLds& S) {
-  const uint32_t lb = long_grid(long_tiles(a.tord, a.long_max));
+  const uint32_t lb = long_grid(long_tiles(a.nlong, a.long_max));
   if (b < lb) {
     uint32_t pos, sub;
     long_item(b, pos, sub);
@@ -641,7 +641,7 @@ __device__ __forceinline__ void blend_item(const BlendArgs& a, uint32_t b, TileL
 // Items a blend stage needs once the tile order is known (the resident kernel sizes its
 // claims by it; a per-stage launch covers the bound instead).
 __device__ __forceinline__ uint32_t blend_items(const BlendArgs& a) {
-  return long_grid(long_tiles(a.tord, a.long_max)) + xcd_grid(a.tiles_total);
+  return long_grid(long_tiles(a.nlong, a.long_max)) + xcd_grid(a.tiles_total);
 }
 
 // Per-batch launch: one workgroup per tile (four per long tile).  Seven waves per SIMD, 72 registers
@@ -677,11 +677,12 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
     hipError_t e = launch_fill_u32((uint32_t*)part, 0u, 6 * (int64_t)L.tiles_total, out);
     if (e != hipSuccess) return e;
   }
-  const uint32_t long_max = long_tile_bound(bb.cap, L.tiles_total);
-  // Their bit planes (16 planes of pw words) must fit the arrays the tile-id sort left free, else
-  // each wave tests the entries itself.
+  // The long tiles' bit planes (16 planes of pw words) must fit the arrays the tile-id sort left free,
+  // else each wave tests the entries itself.
   const uint32_t pw = (uint32_t)((bb.cap + 63) / 64 + (int64_t)L.tiles_total + 1);
   const bool planes_fit = (size_t)16 * pw * sizeof(unsigned long long) <= bb.spare_bytes;
+  const uint32_t long_max = long_tile_bound(bb.cap, L.tiles_total, planes_fit);
+  const uint32_t* nlong = (const uint32_t*)(w + L.tord) + (planes_fit ? kTileLongWord : kTileLongBareWord);
   const uint32_t pre_max = planes_fit ? long_max : 0u;
   if (pre_max > 0) {
     Stage m{};
@@ -689,7 +690,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
     m.items = kLongMaskBlocks;
     m.block = kBlock;
     m.a.long_mask = LongMaskArgs{(const DevView*)(w + L.vinfo), L.V, (const uint2*)(w + L.ranges),
-                                 (const uint32_t*)(w + L.order), (const uint32_t*)(w + L.tord), bb.svals,
+                                 (const uint32_t*)(w + L.order), nlong, bb.svals,
                                  (const float4*)(w + L.rec), L.VN, (const unsigned long long*)(w + L.hdr),
                                  bb.spare, pw, pre_max};
     const hipError_t e = out.put(m);
@@ -702,7 +703,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
   st.a.blend = BlendArgs{(const DevView*)(w + L.vinfo), L.V, L.tiles_total, L.VN, (const float4*)(w + L.rec),
                          (const uint2*)(w + L.ranges), bb.svals, (const unsigned long long*)(w + L.hdr), prm.bg[0],
                          prm.bg[1], prm.bg[2], rgb, T, last, part, (const uint32_t*)(w + L.order),
-                         (const uint32_t*)(w + L.tord), long_max, part ? 1 : 0, bb.spare, pw, pre_max};
+                         nlong, long_max, part ? 1 : 0, bb.spare, pw, pre_max};
   hipError_t e = out.put(st);
   if (e == hipSuccess && part) {
     Stage r{};

@@ -18,20 +18,25 @@ constexpr int kRecQuads = 4;
 constexpr int kRecBytes = kRecQuads * 16;
 constexpr int kScanItems = 16;             // items per thread in the emission's chunks
 constexpr int kScanChunk = kBlock * kScanItems;
-// Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the number of long tiles
-// (the leading positions of the order), which the blend takes as sixteen 4x4-pixel blocks.  A tile
-// is long from 8,192 entries, or from 2,048 in a batch with at most kSparseTiles tiles that are not
-// empty: there the launch lasts as long as its longest chain of entries, and the chip has room for
+// Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the numbers of long tiles
+// (the leading positions of the order), which the blend takes as sixteen 4x4-pixel blocks: by the
+// rule for blends that get the blocks' masks, and for blends that do not.  A tile
+// is long from 8,192 entries, or, with masks, from 2,048 in a batch with at most kSparseTiles tiles that
+// are not empty: there the launch lasts as long as its longest chain of entries, and the chip has room for
 // the waves (far frame of 6M, 318 tiles: 614 us with the line at 8,192, 375 at 4,096, 384 to 290 at
 // 2,048; 2M Gaussians at half the distance: 360, 275 and 185 us), while in a full frame the shorter
 // lists are cheaper as four quadrants (one 1080p view of 3M: 150 us with the line at 8,192 and 212 at
-// 1,024; six views of 3M: 657 and, at 2,048, 790).
+// 1,024; six views of 3M: 657 and, at 2,048, 790).  Without masks (the resident server, and where the
+// planes find no room) sixteen waves gather and test every entry of a long tile instead of four, and
+// 8,192 is the line in sparse batches too: the server's blend of one view of 3M takes 301 us with it at
+// 8,192, 356 at 4,096 and 429 at 2,048 (640 x 480, 1,184 tiles), 568, 669 and 818 us (1280 x 720, 1,709
+// tiles), 963, 1,004 and 1,046 us for the far frame of 6M.
 constexpr int kEmitTile = 2048;            // tile pairs per output chunk of the emission
 constexpr int kTileBuckets = 33;
 constexpr int kLongBucket = 14, kLongBucketSparse = 12;
 constexpr uint32_t kSparseTiles = 2048;
-constexpr int kTileLongWord = 2 * kTileBuckets;
-constexpr int kTileOrderWords = 2 * kTileBuckets + 1;
+constexpr int kTileLongWord = 2 * kTileBuckets, kTileLongBareWord = kTileLongWord + 1;   // with, without masks
+constexpr int kTileOrderWords = 2 * kTileBuckets + 2;
 constexpr int kTileOrderChunk = 1024;       // tiles per block in the ordering kernels
 constexpr int kSortItems = 8;              // keys per thread per radix tile
 constexpr int kSortTile = kBlock * kSortItems;   // 2048 keys per radix tile
@@ -516,16 +521,20 @@ __device__ __forceinline__ void block_chunk(int64_t n, Blk b, int64_t& lo, int64
 }
 __device__ __forceinline__ void block_chunk(int64_t n, int64_t& lo, int64_t& hi) { block_chunk(n, grid_blk(), lo, hi); }
 
-// The long tiles, from the number of tiles per length class.
-__device__ __forceinline__ uint32_t long_tile_count(const uint32_t* classes) {
-  uint32_t filled = 0, n = 0;
-  for (int c = 1; c < kTileBuckets; ++c) filled += classes[c];
-  for (int c = filled <= kSparseTiles ? kLongBucketSparse : kLongBucket; c < kTileBuckets; ++c) n += classes[c];
-  return n;
+// The numbers of long tiles, from the number of tiles per length class, to the words of the tile order.
+__device__ __forceinline__ void store_long_tiles(const uint32_t* classes, uint32_t* tord) {
+  uint32_t filled = 0, bare = 0, sparse = 0;
+  for (int c = 1; c < kTileBuckets; ++c) {
+    filled += classes[c];
+    sparse += c >= kLongBucketSparse ? classes[c] : 0u;
+    bare += c >= kLongBucket ? classes[c] : 0u;
+  }
+  tord[kTileLongWord] = filled <= kSparseTiles ? sparse : bare;
+  tord[kTileLongBareWord] = bare;
 }
 // A bound on them for `cap` pairs in `tiles` tiles.
-inline uint32_t long_tile_bound(int64_t cap, uint32_t tiles) {
-  int64_t n = cap >> (kLongBucketSparse - 1);
+inline uint32_t long_tile_bound(int64_t cap, uint32_t tiles, bool masks) {
+  int64_t n = masks ? cap >> (kLongBucketSparse - 1) : 0;
   if (n > (int64_t)kSparseTiles) n = (int64_t)kSparseTiles;
   if (n < cap >> (kLongBucket - 1)) n = cap >> (kLongBucket - 1);
   return n < (int64_t)tiles ? (uint32_t)n : tiles;
@@ -704,7 +713,7 @@ struct TileOrderArgs {
 struct BlendArgs {
   const DevView* views; int32_t V; uint32_t tiles_total; int64_t VN; const float4* rec; const uint2* ranges;
   const uint32_t* svals; const unsigned long long* hdr; float bg0, bg1, bg2; float* rgb; float* T; uint32_t* last;
-  unsigned long long* pair_part; const uint32_t* order; const uint32_t* tord;
+  unsigned long long* pair_part; const uint32_t* order; const uint32_t* nlong;   // nlong: the number of long tiles
   uint32_t long_max;      // most long tiles the launch covers (the pair capacity's bound)
   int32_t count;
   // Long tiles (the first pre_max of them): per 4x4 block b of the tile, one bit per list
@@ -713,7 +722,7 @@ struct BlendArgs {
   const unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };
 struct LongMaskArgs {
-  const DevView* views; int32_t V; const uint2* ranges; const uint32_t* order; const uint32_t* tord;
+  const DevView* views; int32_t V; const uint2* ranges; const uint32_t* order; const uint32_t* nlong;
   const uint32_t* svals; const float4* rec; int64_t VN; const unsigned long long* hdr;
   unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };

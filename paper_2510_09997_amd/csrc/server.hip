@@ -310,9 +310,9 @@ __device__ bool srv_run(int32_t kind, const Stage& st, Blk b, SrvLds& U) {
 __device__ uint32_t open_items(const SrvJob& job, uint32_t k, int32_t kind) {
   if (kind == kStBlend) {
     const BlendArgs& a = job.st[k].a.blend;
-    const uint32_t* tord =
-        reinterpret_cast<const uint32_t*>(ld_agent(reinterpret_cast<const uint64_t*>(&a.tord)));
-    const uint32_t nl = ld_agent(tord + kTileLongWord), lmax = ld_agent(&a.long_max);
+    const uint32_t* nlong =
+        reinterpret_cast<const uint32_t*>(ld_agent(reinterpret_cast<const uint64_t*>(&a.nlong)));
+    const uint32_t nl = ld_agent(nlong), lmax = ld_agent(&a.long_max);
     return long_grid(nl < lmax ? nl : lmax) + xcd_grid(ld_agent(&a.tiles_total));
   }
   return ld_agent(&job.st[k].items);

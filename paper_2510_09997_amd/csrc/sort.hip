@@ -719,7 +719,7 @@ __device__ __forceinline__ void tile_scatter_body(const TileOrderArgs& a, Blk bl
     uint32_t start = 0;
     for (uint32_t c = b + 1; c < (uint32_t)kTileBuckets; ++c) start += tord[c];
     cur[b] = cnt[b] ? start + atomicAdd(&tord[kTileBuckets + b], cnt[b]) : 0u;
-    if (b == 0 && blk.id == 0) tord[kTileLongWord] = long_tile_count(tord);
+    if (b == 0 && blk.id == 0) store_long_tiles(tord, tord);
   }
   __syncthreads();
   for (uint32_t t = t0 + threadIdx.x; t < tiles && t < t0 + kTileOrderChunk; t += kBlock) {
