@@ -4,7 +4,7 @@
 // (w & 1, w >> 1) and lane l its pixel (l & 7, l >> 3).  Entries of the tile's sorted list
 // are staged in LDS (one per lane or thread, a coalesced gather of the records) and read back
 // as LDS broadcasts; entries that provably cannot reach a quadrant are dropped for it (see
-// quadrant_mask).  Blocks take tiles longest list first (the order clod_bin_sort computes),
+// block_reached).  Blocks take tiles longest list first (the order clod_bin_sort computes),
 // so the long tiles, not stragglers, start the launch.  Long lists (store_long_tiles) are blended with
 // 4x4-pixel blocks per wave (four workgroups per tile); a stage before the blend marks per entry the
 // blocks it may reach, and each block's wave walks only those entries.
@@ -95,7 +95,8 @@ __device__ __forceinline__ bool ellipse_reaches(float u, float v, float A, float
   return box_qmin(A, B, C, X0, X1, Y0, Y1) < 2.5f * -cut;
 }
 
-// Conservative per-quadrant cull of a staged entry.  A pixel centre p farther than
+// Conservative cull of a staged entry for the kB x kB pixel block with corner (x0, y0) (an 8x8
+// quadrant, a 4x4 block of a long tile): 1 if the entry may touch it.  A pixel centre p farther than
 // sqrt(2.4 |cut|) rad / 3 + 0.5 from the 2D mean has exact quadratic form
 // d^T Q d > 2.4 |cut| (rad >= 3 sqrt(lambda_max)), i.e. exact power < -1.2 |cut|.  The binary32
 // power differs from the exact one by a factor common to the conic (the rounding of det,
@@ -104,28 +105,8 @@ __device__ __forceinline__ bool ellipse_reaches(float u, float v, float A, float
 // skipped.  (The radius uses the hardware square root: its relative error of a few 2^-24
 // is far inside that slack.)  Culled pairs are therefore exactly pairs the pixel loop would have skipped.
 // Entries with a worse conditioned conic are never culled spatially.
-__device__ __forceinline__ uint32_t quadrant_mask(float u, float v, float A, float B, float C, float rad,
-                                                  float cut, float x0, float y0) {
-  if (cut > 0.0f) return 0u;
-  const float ac = A * C;
-  const float det = ac - B * B;
-  if (!(det > 2e-5f * ac) || !(rad < 1e6f)) return 0xFu;
-  const float rc = __builtin_amdgcn_sqrtf(2.4f * -cut) * rad * (1.0f / 3.0f) + 0.5f;
-  const float rc2 = rc * rc;
-  uint32_t m = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float qx = x0 + (float)((q & 1) * 8), qy = y0 + (float)((q >> 1) * 8);
-    const float ddx = fmaxf(0.0f, fmaxf(qx + 0.5f - u, u - (qx + 7.5f)));
-    const float ddy = fmaxf(0.0f, fmaxf(qy + 0.5f - v, v - (qy + 7.5f)));
-    if (ddx * ddx + ddy * ddy <= rc2 && ellipse_reaches(u, v, A, B, C, cut, qx, qy)) m |= 1u << q;
-  }
-  return m;
-}
-
-// The same test for one kB x kB pixel block with corner (x0, y0): 1 if the entry may touch it.
 template <int kB>
-__device__ __forceinline__ uint32_t quadrant_mask1(float u, float v, float A, float B, float C, float rad,
+__device__ __forceinline__ uint32_t block_reached(float u, float v, float A, float B, float C, float rad,
                                                    float cut, float x0, float y0) {
   if (!(cut <= 0.0f)) return 0u;   // never live (a NaN cut included: no power reaches it)
   const float ac = A * C;
@@ -331,7 +312,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
       }
     } else if (j < rg.y) {
       cut = entry_cut(g0.z);
-      rel = (quadrant_mask1<kB>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, fqx, fqy)) != 0u;
+      rel = (block_reached<kB>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, fqx, fqy)) != 0u;
     }
     uint64_t mask = ballot64(rel);
     // The entries that may reach the quadrant (block) are staged compacted, in list order
@@ -376,7 +357,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
     auto pair = [&](const float4& a, const float4& c, const float4& bc) {
       const float dx = a.x - pcx, dy = a.y - pcy;
       const float power = fmaf_(a.z * dx, dx, fmaf_(c.x * dy, dy, (a.w * dx) * dy));
-      // cut <= power <= 0 as one test: a staged entry has cut <= 0 (quadrant_mask1 culls the
+      // cut <= power <= 0 as one test: a staged entry has cut <= 0 (block_reached culls the
       // others), so the median of (power, cut, 0) is power exactly then; a NaN power (the
       // padding entry) compares unequal.
       const uint64_t lm = ballot64(__builtin_amdgcn_fmed3f(power, bc.y, 0.0f) == power) & ~dm;
@@ -598,7 +579,7 @@ __device__ __forceinline__ void long_mask_body(const LongMaskArgs& a, Blk b) {
         const float cut = entry_cut(g0.z);
 #pragma unroll
         for (int q = 0; q < 16; ++q)
-          m |= quadrant_mask1<4>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, ox[lo] + (float)(q % 4 * 4),
+          m |= block_reached<4>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, ox[lo] + (float)(q % 4 * 4),
                                  oy[lo] + (float)(q / 4 * 4)) << q;
       }
       unsigned long long mine = 0ull;
@@ -948,7 +929,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     float cut = 0.0f;
     if (d < m) {
       cut = entry_cut(g0.z);
-      rel = quadrant_mask1<8>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, fqx, fqy) != 0u;
+      rel = block_reached<8>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, fqx, fqy) != 0u;
     }
     const uint64_t mask = ballot64(rel);
     const uint32_t n = (uint32_t)__builtin_popcountll(mask);

@@ -40,21 +40,10 @@ __device__ __forceinline__ uint32_t chunk_offsets(uint32_t* loff, uint32_t* sm, 
   return total;
 }
 
-// Largest k with loff[k] <= o (loff[0] = 0 <= o); with o below the chunk total this is the
-// item that output o belongs to (items with no outputs share their successor's offset).
-__device__ __forceinline__ int owner_of(const uint32_t* loff, uint32_t o) {
-  int lo = 0, hi = kScanChunk - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (loff[mid] <= o) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // ---------------------------------------------------------------------------- radix sort
-// (General path and scene order.)  Reduce-then-scan LSD radix sort of (uint32 key, uint32 value) pairs with 8-bit digits; the
-// element count is header word `cw`.  Block b of G owns the contiguous chunk
-// [b*C, (b+1)*C) (C a multiple of the 2048-key tile), so the stable order across blocks is the
+// (General path and scene order.)  Reduce-then-scan LSD radix sort of (uint32 key, uint32 value)
+// pairs with 8-bit digits; the element count is header word `cw`.  Block b of G owns the contiguous
+// chunk [b*C, (b+1)*C) (C a multiple of the 2048-key tile), so the stable order across blocks is the
 // block order.
 
 __device__ __forceinline__ void sort_chunk(int64_t N, int G, int b, int64_t& lo, int64_t& hi) {
@@ -64,17 +53,6 @@ __device__ __forceinline__ void sort_chunk(int64_t N, int G, int b, int64_t& lo,
   hi = lo + per * kSortTile;
   if (lo > N) lo = N;
   if (hi > N) hi = N;
-}
-
-// Lanes of this wave holding the same 8-bit digit (restricted to `active`).
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t active) {
-  uint64_t m = active;
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint64_t bal = ballot64((d >> b) & 1u);
-    m &= ((d >> b) & 1u) ? bal : ~bal;
-  }
-  return m;
 }
 
 // Digit counts per 16-lane group of each wave (16 copies, rows padded to 257 words): lanes
@@ -194,7 +172,7 @@ __device__ __forceinline__ void radix_downsweep_body(const RadixArgs& a, Blk b, 
       const uint32_t d = valid ? (k8[j] >> shift) & 255u : 256u;
       d8[j] = d;
       const uint64_t active = ballot64(valid);
-      const uint64_t m = match_digit(d & 255u, active);
+      const uint64_t m = match_bits<8>(d & 255u, active);
       if (valid) {
         const uint32_t before = wcnt[wave][d];
         r8[j] = before + (uint32_t)__popcll(m & lt);
