@@ -121,8 +121,7 @@ static Layout make_layout(int64_t n, int32_t V, const HostTotals& t, bool any_bu
   L.row_path = L.VN > 0 && t.rows <= (int64_t)kRowBinsMax && t.widest <= kColsMax && t.tallest <= kColsMax;
   if (L.row_path) {
     L.rows = (uint32_t)t.rows;
-    L.row_bins = kBlock;
-    while (L.row_bins < L.rows) L.row_bins *= 2;
+    L.row_bins = row_bins_of(L.rows);
     L.cols = (t.widest + 63u) / 64u * 64u;
   }
   const uint32_t hist = L.VN > 0 ? hist_words(L.VN, L.rows, L.cols, L.row_path ? t.tallest : 0u) : 0u;

@@ -526,6 +526,12 @@ __device__ __forceinline__ RowRec row_rec(const RowArgs& a, uint32_t rect, uint3
   return RowRec{a.views[v].row_base + y0, y1 - y0 + 1u, rect & 0xFFFFu};
 }
 
+// Records per wave of the row kernels.  (3,000 records of 68 rows each were twelve waves' work: 111 us
+// for k_row_down, now 32; 200,000 of 13 rows 71 us, now 30.)
+__device__ __forceinline__ RadixGeom row_geom(const RowArgs& a, uint32_t N) {
+  return radix_geom(N, a.bins, a.hdr[kHdrDup] >= (uint64_t)kWideTiles * N ? kWaveMinWide : kWaveMin);
+}
+
 // First record of wave k of the row kernels.  The work is a record's rows, and the records come by
 // depth: the nearest cover tens of rows each, the others two or three, and of equal shares the first
 // set the time of the scatter.  So in large batches wave k of K starts at N f(k / K), in steps of 64,
@@ -548,7 +554,7 @@ __device__ __forceinline__ uint64_t row_chunk(const RowArgs& a, uint32_t N, cons
 __device__ __forceinline__ void row_up_body(const RowArgs& a, Blk b, uint32_t* lds) {
   if (a.hdr[kHdrOverflow]) return;
   const uint32_t N = (uint32_t)a.hdr[kHdrRend], bins = a.bins;
-  const RadixGeom G = radix_geom(N, bins);
+  const RadixGeom G = row_geom(a, N);
   const uint32_t c = xcd_chunk(b.id, G.nb);
   if (c >= G.nb) return;
   const uint32_t stride = bins + 1u;
@@ -665,7 +671,7 @@ __device__ __forceinline__ void row_down_body(const RowArgs& a, Blk b, uint32_t*
   __shared__ uint32_t sm[4];
   if (a.hdr[kHdrOverflow]) return;
   const uint32_t N = (uint32_t)a.hdr[kHdrRend], bins = a.bins;
-  const RadixGeom G = radix_geom(N, bins);
+  const RadixGeom G = row_geom(a, N);
   const uint32_t c = xcd_chunk(b.id, G.nb > 0u ? G.nb : 1u);
   if (c >= G.nb && c != 0u) return;
   uint32_t total;
@@ -794,8 +800,12 @@ __global__ __launch_bounds__(kBlock) void k_col_scan(ColArgs a) { col_scan_body(
 // Sub-unit of 512 row pairs: each wave owns 128 of them, counts its columns, and places its tile
 // pairs (record, column) in LDS ordered by column; the block then stores each column's run to its
 // list, so that a store instruction covers a few runs instead of 64 separate words.  A sub-unit
-// of more than kStagePairs tile pairs (wide rectangles) is stored from the ranks directly.
-constexpr uint32_t kSubUnit = 512, kStagePairs = 4096;
+// of more than kStagePairs tile pairs (wide rectangles) is taken in parts that fit, down to
+// kLeastPart row pairs (which always do); the next sub-units start with parts of that size and
+// go back to larger ones where a part is less than half full.  (Stored from the ranks directly, word
+// by word, 3,000 Gaussians over the whole of a 1080p frame took 338 us instead of 185, and 200,000
+// of 209 tiles each 366 instead of 217.)
+constexpr uint32_t kSubUnit = 512, kStagePairs = 4096, kLeastPart = kStagePairs / kColsMax;
 struct ColLds {
   uint32_t base[kColsMax];              // next output position per column
   uint32_t lstart[kColsMax];            // first place in the stage per column
@@ -822,20 +832,19 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
   if (U.first && t < width && mine) a.ranges[tile0 + t] = make_uint2(at, at + mine);
   const uint32_t D = (uint32_t)a.hdr[kHdrDup];
   const uint64_t lt = lanemask_lt();
-  for (uint32_t o0 = 0; o0 < U.count; o0 += kSubUnit) {
-    // The sub-unit's pairs: wave w the 128 from o0 + 128 w.
+  uint32_t part = kSubUnit;
+  for (uint32_t o0 = 0; o0 < U.count;) {
+    // The part's pairs: wave w the part / 4 from o0 + part / 4 w.
+    const uint32_t wo = o0 + part / 4u * w, wn = min(part / 4u, U.count > wo ? U.count - wo : 0u);
     uint2 rp[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t o = o0 + 128u * w + 64u * j + lane;
-      rp[j] = o < U.count ? a.in[U.lo + o] : make_uint2(0u, 0u);
-    }
+    for (int j = 0; j < 2; ++j) rp[j] = 64u * j + lane < wn ? a.in[U.lo + wo + 64u * j + lane] : make_uint2(0u, 0u);
     uint32_t* cnt = S.cnt[w];
     for (uint32_t i = lane; i <= kColsMax; i += 64) cnt[i] = 0u;
     wave_lds_fence();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (o0 + 128u * w + 64u * j + lane < U.count) {
+      if (64u * j + lane < wn) {
         atomicAdd(&cnt[rp[j].y & 0xFFu], 1u);
         atomicAdd(&cnt[(rp[j].y >> 8) + 1u], 0xFFFFFFFFu);
       }
@@ -856,6 +865,10 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
     }
     uint32_t total;
     uint32_t place = block_exclusive_scan(run, sm, total);
+    if (total > kStagePairs && part > kLeastPart) {   // (the block scan ends with a barrier)
+      while (part > kLeastPart && total > kStagePairs) { part /= 2u; total /= 2u; }
+      continue;
+    }
     S.lstart[t] = place;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -863,10 +876,9 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
       place += c4[q];
     }
     __syncthreads();
-    const bool staged = total <= kStagePairs;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const bool in = o0 + 128u * w + 64u * j + lane < U.count;
+      const bool in = 64u * j + lane < wn;
       const uint32_t x0 = rp[j].y & 0xFFu, len = in ? (rp[j].y >> 8) - x0 + 1u : 0u;
       const uint32_t inc = wave_scan_inc(len), off = inc - len;
       const uint32_t rel = x0 - off;
@@ -874,26 +886,21 @@ __device__ __forceinline__ void col_down_unit(const ColArgs& a, uint32_t u, ColL
         const uint32_t col = (uint32_t)__shfl((int)rel, o, 64) + p;   // (of lanes with an output)
         const uint32_t f = (uint32_t)__shfl((int)rp[j].x, o, 64);
         const uint32_t q = wave_rank<8>(cnt, col, ok, lt);
-        if (ok) {
-          if (staged) {
-            S.sf[q] = f;
-            S.scol[q] = (uint8_t)col;
-          } else {
-            const uint32_t g = S.base[col] + (q - S.lstart[col]);
-            if (g < D) { a.kout[g] = tile0 + col; a.vout[g] = f; }
-          }
+        if (ok && q < kStagePairs) {
+          S.sf[q] = f;
+          S.scol[q] = (uint8_t)col;
         }
       });
     }
     __syncthreads();
-    if (staged) {
-      for (uint32_t q = t; q < total; q += kBlock) {
-        const uint32_t col = S.scol[q], g = S.base[col] + (q - S.lstart[col]);
-        if (g < D) { a.kout[g] = tile0 + col; a.vout[g] = S.sf[q]; }
-      }
+    for (uint32_t q = t; q < total; q += kBlock) {
+      const uint32_t col = S.scol[q], g = S.base[col] + (q - S.lstart[col]);
+      if (g < D) { a.kout[g] = tile0 + col; a.vout[g] = S.sf[q]; }
     }
     __syncthreads();
     S.base[t] += run;
+    o0 += part;
+    if (part < kSubUnit && total < kStagePairs / 2u) part *= 2u;
   }
 }
 

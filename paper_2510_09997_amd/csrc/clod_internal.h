@@ -63,36 +63,46 @@ constexpr uint32_t kOrderCopies = 32;      // copies of the length-class counter
 __host__ __device__ constexpr uint32_t radix_blocks(uint32_t bins) {
   return kHistWords / (4u * bins) < kRadixBlocksMax ? kHistWords / (4u * bins) : kRadixBlocksMax;
 }
-constexpr uint32_t kWaveMin = 256;   // least elements per wave: below it the prefix reads cost more
+// Least elements per wave: below kWaveMin the prefix reads cost more, but for the row kernels where
+// records cover kWideTiles tiles and more on average, so that a wave makes thousands of pairs.
+constexpr uint32_t kWaveMin = 256, kWaveMinWide = 64, kWideTiles = 64;
 // N elements in wave chunks of kw (a multiple of 64), four consecutive chunks per block, at most
 // radix_blocks(bins) blocks (the histogram holds four rows of `bins` counts per block).
 struct RadixGeom {
   uint32_t kw, nb;
 };
-__host__ __device__ constexpr RadixGeom radix_geom(uint64_t N, uint32_t bins) {
+__host__ __device__ constexpr RadixGeom radix_geom(uint64_t N, uint32_t bins, uint32_t least = kWaveMin) {
   const uint64_t most = radix_blocks(bins);
   uint64_t kw = (N + most * 256u - 1) / (most * 256u) * 64u;
-  if (kw < kWaveMin) kw = kWaveMin;
+  if (kw < least) kw = least;
   return RadixGeom{(uint32_t)kw, (uint32_t)((N + 4 * kw - 1) / (4 * kw))};
 }
 // Blocks that a radix pass over `most` elements, or fewer, can need.
-constexpr uint32_t pass_blocks(int64_t most) {
-  const int64_t b = (most + 4 * kWaveMin - 1) / (4 * kWaveMin);
+constexpr uint32_t pass_blocks(int64_t most, uint32_t least = kWaveMin) {
+  const int64_t b = (most + 4 * least - 1) / (4 * least);
   return b < (int64_t)kRadixBlocksMax ? (uint32_t)b : kRadixBlocksMax;
 }
+// Digits of the row kernels (a multiple of a block's threads) for `rows` tile rows.
+constexpr uint32_t row_bins_of(uint32_t rows) {
+  uint32_t b = kBlock;
+  while (b < rows) b *= 2;
+  return b;
+}
 // Words of counts that a batch of VN (view, Gaussian) records can need: four rows of counts per block
-// of a radix pass, and kUnit-pair column units of `cols` counts for a pair per record and tile row of
+// of a depth pass and of the row kernels, and kUnit-pair column units of `cols` counts for a pair per record and tile row of
 // the tallest view, in units besides the ones that end the `rows` rows.  At most kHistWords, where the
 // blocks are capped and the units grow; sized to it for every batch the two tables took 8.9 MB, more
 // than all else together below some 200,000 records.
 constexpr uint32_t hist_words(int64_t VN, uint32_t rows, uint32_t cols, uint32_t tallest) {
-  const uint64_t radix = 4ull * kRowBinsMax * pass_blocks(VN);
+  const uint64_t depth = 4ull * kRowBinsMax * pass_blocks(VN);
+  const uint64_t row = 4ull * row_bins_of(rows) * pass_blocks(VN, kWaveMinWide);
   const uint64_t units = ((uint64_t)((VN * tallest + kUnit - 1) / kUnit) + rows) * cols;
-  const uint64_t w = radix > units ? radix : units;
+  uint64_t w = depth > row ? depth : row;
+  if (units > w) w = units;
   return w < kHistWords ? (uint32_t)w : kHistWords;
 }
 // Groups of blocks of a pass over VN records, and the words of their sums (three depth passes, rows).
-constexpr uint32_t sum_groups(int64_t VN) { return (pass_blocks(VN) + kGroup - 1) / kGroup; }
+constexpr uint32_t sum_groups(int64_t VN) { return (pass_blocks(VN, kWaveMinWide) + kGroup - 1) / kGroup; }
 constexpr size_t sum_words(int64_t VN, uint32_t row_bins) {
   return (size_t)sum_groups(VN) * (kDepthBins0 + 2 * kRowBinsMax + row_bins);
 }

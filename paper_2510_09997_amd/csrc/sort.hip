@@ -476,8 +476,8 @@ static void depth_counters(const Layout& L, char* w, uint32_t* (&gsum)[4]) {
   for (int k = 1; k < 4; ++k) gsum[k] = gsum[0] + sum_groups(L.VN) * (kDepthBins0 + (uint32_t)(k - 1) * kRowBinsMax);
 }
 // Blocks that the records of a batch can need in a pass (their number is known on the device only).
-static uint32_t record_blocks(const Layout& L, const DupLayout& D) {
-  return pass_blocks(L.VN < D.cap ? L.VN : D.cap);
+static uint32_t record_blocks(const Layout& L, const DupLayout& D, uint32_t least) {
+  return pass_blocks(L.VN < D.cap ? L.VN : D.cap, least);
 }
 
 static hipError_t depth_sort(const Layout& L, char* w, const DupLayout& D, char* dp, const Sink& out) {
@@ -523,7 +523,7 @@ static hipError_t depth_sort(const Layout& L, char* w, const DupLayout& D, char*
     a.in = buf[p & 1];
     a.out = buf[(p + 1) & 1];   // the third pass, from buffer 0, writes kout and vout instead
     if (p == 2) { a.kout = (uint32_t*)(dp + D.keys1); a.vout = (uint32_t*)(dp + D.vals1); }
-    const uint32_t items = (record_blocks(L, D) + 7u) / 8u * 8u;   // chunks are spread over the eight XCDs
+    const uint32_t items = (record_blocks(L, D, kWaveMin) + 7u) / 8u * 8u;   // chunks are spread over the eight XCDs
     put(kStDepthUp, items);
     put(kStDepthDown, items);
   }
@@ -554,7 +554,7 @@ static hipError_t row_partition(const Layout& L, char* w, const DupLayout& D, ch
                      (const uint32_t*)(dp + D.vals1), rp, hist, gsum[3], tab, L.row_bins, L.units_max, L.tiles_total,
                      1.0f / (float)L.n};
   st.lds = row_lds_words(L.row_bins) * 4u;
-  const int64_t rb = (record_blocks(L, D) + 7u) / 8u * 8u;
+  const int64_t rb = (record_blocks(L, D, kWaveMinWide) + 7u) / 8u * 8u;
   put(kStRowUp, rb);
   put(kStRowDown, rb);
   st.lds = 0;

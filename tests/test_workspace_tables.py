@@ -26,6 +26,12 @@ BODY = r"""
               if ((uint64_t)G.kw * 4 * G.nb < (uint64_t)N || G.kw % 64 != 0) bad |= 16;
             }
           if (tallest == 0) continue;
+          // The row kernels' shares where records cover many tiles.
+          for (int64_t N : {(int64_t)1, VN / 3, VN}) {
+            const RadixGeom G = radix_geom((uint64_t)N, row_bins_of(rows), kWaveMinWide);
+            if ((uint64_t)G.nb * 4 * row_bins_of(rows) > words || G.nb > pass_blocks(N < 1 ? 1 : N, kWaveMinWide)) bad |= 512;
+            if ((G.nb + kGroup - 1) / kGroup > sum_groups(VN)) bad |= 1024;
+          }
           const uint32_t units_max = words / cols;
           if (units_max <= rows) { bad |= 32; continue; }
           // Row pairs: at most one per record and row of the tallest view.
