@@ -37,10 +37,10 @@ __host__ __device__ inline uint32_t long_grid(uint32_t long_tiles) {
   return (4 * long_tiles + 4 * kXcds - 1) / (4 * kXcds) * (4 * kXcds);
 }
 
-// The long tiles of this blend: the first *nlong positions of the tile order (written by the tile
-// ordering stage), within the bound the launch was sized for.
-__device__ __forceinline__ uint32_t long_tiles(const uint32_t* nlong, uint32_t bound) {
-  const uint32_t nl = *nlong;
+// The long (or masked) tiles of this blend: the first *count positions of the tile order (written by
+// the tile ordering stage), within the bound the launch was sized for.
+__device__ __forceinline__ uint32_t long_tiles(const uint32_t* count, uint32_t bound) {
+  const uint32_t nl = *count;
   return nl < bound ? nl : bound;
 }
 
@@ -123,7 +123,8 @@ __device__ __forceinline__ uint32_t block_reached(float u, float v, float A, flo
 // entries that may reach its block, and sixteen waves share the tile instead of four.  The tile
 // order puts them first (longest first): they are taken by the leading workgroups of the launch.
 // They get their block tests from k_long_mask and their waves walk compacted lists (where the bit
-// planes find no room, and in the resident server, the waves test the entries themselves).
+// planes find no room, in the resident server, and for all but the longest in full batches, the
+// waves test the entries themselves).
 
 // Forward blend.  Each wave owns one 8x8 quadrant of a tile (lane l: pixel (l & 7, l >> 3))
 // and runs on its own: it takes 64 entries of the tile's sorted list at a time (one entry per
@@ -296,7 +297,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& a, uint32_t pos, Til
   // at list position j: staged in this wave's LDS slice, culled against the quadrant, then
   // walked.  The entries of a premasked long tile arrive already compacted to those that may reach
   // the 4x4 block (relc); elsewhere the batch is 64 consecutive entries and is culled here.
-  const bool pre = kB == 4 && pos < long_tiles(a.nlong, a.pre_max);
+  const bool pre = kB == 4 && pos < long_tiles(a.npre, a.pre_max);
   // next() runs between the staging and the walk: it requests the next batch's records, into the
   // same registers.
   auto batch = [&](const uint32_t j, const float4& g0, const float4& g1, const float4& g2,
@@ -543,7 +544,7 @@ __device__ __forceinline__ void long_mask_body(const LongMaskArgs& a, Blk b) {
   __shared__ uint32_t first[kBlock + 1], start[kBlock], len[kBlock], tile[kBlock], sm[4];
   __shared__ float ox[kBlock], oy[kBlock];
   if (a.hdr[kHdrOverflow]) return;
-  const uint32_t nl = long_tiles(a.nlong, a.pre_max);
+  const uint32_t nl = long_tiles(a.npre, a.pre_max);
   const uint32_t lane = lane_id(), t = threadIdx.x;
   const uint32_t gw = b.id * (kBlock / 64u) + (t >> 6), GW = b.n * (kBlock / 64u);
   for (uint32_t p0 = 0; p0 < nl; p0 += kBlock) {
@@ -663,7 +664,8 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
   const uint32_t pw = (uint32_t)((bb.cap + 63) / 64 + (int64_t)L.tiles_total + 1);
   const bool planes_fit = (size_t)16 * pw * sizeof(unsigned long long) <= bb.spare_bytes;
   const uint32_t long_max = long_tile_bound(bb.cap, L.tiles_total, planes_fit);
-  const uint32_t* nlong = (const uint32_t*)(w + L.tord) + (planes_fit ? kTileLongWord : kTileLongBareWord);
+  const uint32_t* tord = (const uint32_t*)(w + L.tord);
+  const uint32_t* nlong = tord + (planes_fit ? kTileLongWord : kTileLongBareWord);
   const uint32_t pre_max = planes_fit ? long_max : 0u;
   if (pre_max > 0) {
     Stage m{};
@@ -671,7 +673,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
     m.items = kLongMaskBlocks;
     m.block = kBlock;
     m.a.long_mask = LongMaskArgs{(const DevView*)(w + L.vinfo), L.V, (const uint2*)(w + L.ranges),
-                                 (const uint32_t*)(w + L.order), nlong, bb.svals,
+                                 (const uint32_t*)(w + L.order), tord + kTileMaskedWord, bb.svals,
                                  (const float4*)(w + L.rec), L.VN, (const unsigned long long*)(w + L.hdr),
                                  bb.spare, pw, pre_max};
     const hipError_t e = out.put(m);
@@ -684,7 +686,7 @@ hipError_t launch_blend_fwd(const Layout& L, void* ws, const BlendBufs& bb, clod
   st.a.blend = BlendArgs{(const DevView*)(w + L.vinfo), L.V, L.tiles_total, L.VN, (const float4*)(w + L.rec),
                          (const uint2*)(w + L.ranges), bb.svals, (const unsigned long long*)(w + L.hdr), prm.bg[0],
                          prm.bg[1], prm.bg[2], rgb, T, last, part, (const uint32_t*)(w + L.order),
-                         nlong, long_max, part ? 1 : 0, bb.spare, pw, pre_max};
+                         nlong, tord + kTileMaskedWord, long_max, part ? 1 : 0, bb.spare, pw, pre_max};
   hipError_t e = out.put(st);
   if (e == hipSuccess && part) {
     Stage r{};

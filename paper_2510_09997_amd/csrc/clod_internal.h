@@ -20,7 +20,8 @@ constexpr int kScanItems = 16;             // items per thread in the emission's
 constexpr int kScanChunk = kBlock * kScanItems;
 // Tile ordering by list length: 33 bucket counts + 33 bucket cursors + the numbers of long tiles
 // (the leading positions of the order), which the blend takes as sixteen 4x4-pixel blocks: by the
-// rule for blends that get the blocks' masks, and for blends that do not.  A tile
+// rule for blends that get the blocks' masks, and for blends that do not; and the number of masked
+// tiles among the former.  A tile
 // is long from 8,192 entries, or, with masks, from 2,048 in a batch with at most kSparseTiles tiles that
 // are not empty: there the launch lasts as long as its longest chain of entries, and the chip has room for
 // the waves (far frame of 6M, 318 tiles: 614 us with the line at 8,192, 375 at 4,096, 384 to 290 at
@@ -31,12 +32,19 @@ constexpr int kScanChunk = kBlock * kScanItems;
 // 8,192 is the line in sparse batches too: the server's blend of one view of 3M takes 301 us with it at
 // 8,192, 356 at 4,096 and 429 at 2,048 (640 x 480, 1,184 tiles), 568, 669 and 818 us (1280 x 720, 1,709
 // tiles), 963, 1,004 and 1,046 us for the far frame of 6M.
+// Masks are made for whole lists, however early the pixels end.  They pay where lists are long because
+// the view is far and the splats are small and faint, which leaves most tiles empty; in a batch of more
+// than kMaskTiles filled tiles only lists of 32,768 entries and more get them.  Blend with its masks, us, with
+// masks from 8,192 and from 32,768: 200,000 Gaussians of 209 tiles (8,160 filled) 707 and 460, a million
+// of 32 (8,027) 566 and 285, four views of 6M (8,065) 1,063 and 996; but twelve far views of 6M (2,701)
+// 2,019 and 4,442, six of 3M (2,985) 831 and 1,111.
 constexpr int kEmitTile = 2048;            // tile pairs per output chunk of the emission
 constexpr int kTileBuckets = 33;
-constexpr int kLongBucket = 14, kLongBucketSparse = 12;
-constexpr uint32_t kSparseTiles = 2048;
+constexpr int kLongBucket = 14, kLongBucketSparse = 12, kMaskBucketFull = 16;
+constexpr uint32_t kSparseTiles = 2048, kMaskTiles = 4096;
 constexpr int kTileLongWord = 2 * kTileBuckets, kTileLongBareWord = kTileLongWord + 1;   // with, without masks
-constexpr int kTileOrderWords = 2 * kTileBuckets + 2;
+constexpr int kTileMaskedWord = kTileLongWord + 2;
+constexpr int kTileOrderWords = 2 * kTileBuckets + 3;
 constexpr int kTileOrderChunk = 1024;       // tiles per block in the ordering kernels
 constexpr int kSortItems = 8;              // keys per thread per radix tile
 constexpr int kSortTile = kBlock * kSortItems;   // 2048 keys per radix tile
@@ -533,14 +541,16 @@ __device__ __forceinline__ void block_chunk(int64_t n, int64_t& lo, int64_t& hi)
 
 // The numbers of long tiles, from the number of tiles per length class, to the words of the tile order.
 __device__ __forceinline__ void store_long_tiles(const uint32_t* classes, uint32_t* tord) {
-  uint32_t filled = 0, bare = 0, sparse = 0;
+  uint32_t filled = 0, bare = 0, sparse = 0, longest = 0;
   for (int c = 1; c < kTileBuckets; ++c) {
     filled += classes[c];
     sparse += c >= kLongBucketSparse ? classes[c] : 0u;
     bare += c >= kLongBucket ? classes[c] : 0u;
+    longest += c >= kMaskBucketFull ? classes[c] : 0u;
   }
   tord[kTileLongWord] = filled <= kSparseTiles ? sparse : bare;
   tord[kTileLongBareWord] = bare;
+  tord[kTileMaskedWord] = filled <= kSparseTiles ? sparse : filled <= kMaskTiles ? bare : longest;
 }
 // A bound on them for `cap` pairs in `tiles` tiles.
 inline uint32_t long_tile_bound(int64_t cap, uint32_t tiles, bool masks) {
@@ -723,7 +733,8 @@ struct TileOrderArgs {
 struct BlendArgs {
   const DevView* views; int32_t V; uint32_t tiles_total; int64_t VN; const float4* rec; const uint2* ranges;
   const uint32_t* svals; const unsigned long long* hdr; float bg0, bg1, bg2; float* rgb; float* T; uint32_t* last;
-  unsigned long long* pair_part; const uint32_t* order; const uint32_t* nlong;   // nlong: the number of long tiles
+  unsigned long long* pair_part; const uint32_t* order;
+  const uint32_t* nlong; const uint32_t* npre;   // numbers of long tiles, of masked ones
   uint32_t long_max;      // most long tiles the launch covers (the pair capacity's bound)
   int32_t count;
   // Long tiles (the first pre_max of them): per 4x4 block b of the tile, one bit per list
@@ -732,7 +743,7 @@ struct BlendArgs {
   const unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };
 struct LongMaskArgs {
-  const DevView* views; int32_t V; const uint2* ranges; const uint32_t* order; const uint32_t* nlong;
+  const DevView* views; int32_t V; const uint2* ranges; const uint32_t* order; const uint32_t* npre;
   const uint32_t* svals; const float4* rec; int64_t VN; const unsigned long long* hdr;
   unsigned long long* lplane; uint32_t pw; uint32_t pre_max;
 };
