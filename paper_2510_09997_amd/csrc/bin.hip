@@ -282,6 +282,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 __device__ __forceinline__ void rec_compact_body(const DepthArgs& a, Blk b, RecLds& S) {
   __shared__ uint32_t sm[4];
   __shared__ unsigned long long sd[4];
+  __shared__ float sq[4];
   const uint32_t t = threadIdx.x, w = t >> 6, lane = lane_id();
   const int64_t j0 = (int64_t)b.id * kRecChunk + 16 * (int64_t)t;
   uint32_t m = rendered_mask(a.flags, a.VN, j0);
@@ -301,6 +302,7 @@ __device__ __forceinline__ void rec_compact_body(const DepthArgs& a, Blk b, RecL
   const uint32_t base = (uint32_t)a.hdr[kHdrKeyBase];
   unsigned long long pairs = 0;
   uint32_t kmax = 0;
+  float squares = 0.f;
   for (uint32_t q0 = t; q0 < total; q0 += 4 * kBlock) {
     uint32_t f[4];
     float4 q3[4];
@@ -317,7 +319,9 @@ __device__ __forceinline__ void rec_compact_body(const DepthArgs& a, Blk b, RecL
       if (q < total) {
         const uint32_t k = __float_as_uint(q3[j].x) - base;
         kmax = k > kmax ? k : kmax;
-        pairs += __float_as_uint(q3[j].w);
+        const uint32_t tiles = __float_as_uint(q3[j].w);
+        pairs += tiles;
+        squares = fmaf_((float)tiles, (float)tiles, squares);
         if ((int64_t)out0 + q < a.cap) a.out[(size_t)out0 + q] = make_uint2(k, f[j]);
       }
     }
@@ -326,9 +330,12 @@ __device__ __forceinline__ void rec_compact_body(const DepthArgs& a, Blk b, RecL
   // chunk (7,800 of them for 16 views of 2M Gaussians) took 170 us instead of the time given above.
   pairs = wave_sum(pairs);
   kmax = wave_max(kmax);
-  if (lane == 0) { sd[w] = pairs; sm[w] = kmax; }
+  squares = wave_sum(squares);
+  if (lane == 0) { sd[w] = pairs; sm[w] = kmax; sq[w] = squares; }
   __syncthreads();
-  if (t == 0) a.stat[b.id] = DepthStat{sd[0] + sd[1] + sd[2] + sd[3], max(max(sm[0], sm[1]), max(sm[2], sm[3])), 0u};
+  if (t == 0)
+    a.stat[b.id] = DepthStat{sd[0] + sd[1] + sd[2] + sd[3], max(max(sm[0], sm[1]), max(sm[2], sm[3])),
+                             sq[0] + sq[1] + sq[2] + sq[3]};
 }
 __global__ __launch_bounds__(kBlock) void k_rec_compact(DepthArgs a) {
   __shared__ RecLds S;
@@ -361,6 +368,7 @@ struct DepthState {
 __device__ __forceinline__ DepthState depth_first(const DepthArgs& a, Blk b) {
   __shared__ unsigned long long sd[4];
   __shared__ uint32_t sk[4];
+  __shared__ float sq[4];
   const uint32_t t = threadIdx.x, lane = lane_id();
   uint32_t R = 0;
   for (uint32_t g = lane; g < a.groups; g += 64) R += a.gcount[g * kLineWords];
@@ -368,6 +376,7 @@ __device__ __forceinline__ DepthState depth_first(const DepthArgs& a, Blk b) {
   if (b.id == 0u) {
     unsigned long long D = 0;
     uint32_t kmax = 0;
+    float squares = 0.f;
     for (uint32_t q0 = t; q0 < a.chunks; q0 += 4 * kBlock) {
       DepthStat q[4];
 #pragma unroll
@@ -375,18 +384,21 @@ __device__ __forceinline__ DepthState depth_first(const DepthArgs& a, Blk b) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         D += q0 + j * kBlock < a.chunks ? q[j].pairs : 0ull;
+        squares += q0 + j * kBlock < a.chunks ? q[j].squares : 0.f;
         kmax = q[j].kmax > kmax ? q[j].kmax : kmax;
       }
     }
     D = wave_sum(D);
     kmax = wave_max(kmax);
-    if (lane == 0) { sd[t >> 6] = D; sk[t >> 6] = kmax; }
+    squares = wave_sum(squares);
+    if (lane == 0) { sd[t >> 6] = D; sk[t >> 6] = kmax; sq[t >> 6] = squares; }
     __syncthreads();
     if (t == 0) {
       D = sd[0] + sd[1] + sd[2] + sd[3];
       a.hdr[kHdrDup] = D;
       a.hdr[kHdrOverflow] = (int64_t)D > a.cap ? 1ull : 0ull;   // else R <= D <= cap: a record has a pair
       a.hdr[kHdrRend] = R;
+      a.hdr[kHdrSquares] = (unsigned long long)((sq[0] + sq[1]) + (sq[2] + sq[3]));   // (R 2^40 at most)
       a.hdr[kHdrKeyBits] = (unsigned long long)bit_length(max(max(sk[0], sk[1]), max(sk[2], sk[3])));
     }
     zero_words(a.tord, a.tord_words, Blk{0u, 1u});

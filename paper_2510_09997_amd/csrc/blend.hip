@@ -747,7 +747,30 @@ struct BwdLds {
                                    // the rows' writes nor the columns' reads meet in a bank
   float gl[3][64];                 // the pixels' colour gradients
 };
-static_assert(4 * sizeof(BwdLds) <= 160 * 1024 / 5, "five workgroups per CU");
+// Records that cover many tiles are added to from every quadrant under them, and the additions to one
+// address come one after the other: where the pairs' records are large on average, the four waves of a
+// tile walk the list in common windows of 256 entries instead and add their sums (reduced over the
+// wave entry by entry) up in LDS first, a quarter of the additions to memory.  The size is that of a
+// pair's record: sum of squared tiles over sum of tiles.  Backward of one view, us, by that size, waves
+// on their own and merged: 24 tiles (250,000 Gaussians) 163 and 192, 51 tiles (250,000) 432 and 571, 87
+// tiles (64,000) 236 and 277, 102 tiles (64,000, 256 x 256) 198 and 227; 132 tiles (64,000) 220 and
+// 171, 245 tiles (16,000) 213 and 139, 498 tiles (250,000) 368 and 244, 1,836 tiles (4,000) 836 and 320.
+// Between 100 and 300 either may win by a little.
+struct MergedLds {
+  float4 s0[kBlock], s1[kBlock], s2[kBlock];   // (u, v, -A/2, -B), (-C/2, alpha'', r, g), (b, cut, -, record)
+  float acc[kBlock * kGscreen];                // [entry][9]: odd stride, conflict-free
+  unsigned long long qmask[4][4];              // [staging wave][quadrant]: entries that may reach it
+  uint32_t smax[4];
+};
+union BwdBlockLds {
+  BwdLds wave[4];
+  MergedLds merged;
+};
+static_assert(sizeof(BwdBlockLds) <= 160 * 1024 / 5, "five workgroups per CU");
+constexpr unsigned long long kMergeTiles = 112;
+__device__ __forceinline__ bool merge_tiles(const unsigned long long* hdr) {
+  return hdr[kHdrSquares] >= kMergeTiles * hdr[kHdrDup];
+}
 template <bool kCount>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_blend_bwd(
     const DevView* __restrict__ views, int V, uint32_t tiles_total, int64_t VN,
@@ -757,9 +780,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     const uint32_t* __restrict__ lastin, const float* __restrict__ dL_drgb,
     float* __restrict__ gscreen, const uint32_t* __restrict__ order,
     unsigned long long* __restrict__ pair_part) {
-  __shared__ BwdLds lds[4];
+  __shared__ BwdBlockLds lds;
   const int quad = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // the wave's quadrant
-  BwdLds& S = lds[quad];
+  BwdLds& S = lds.wave[quad];
   const uint32_t opos = xcd_tile_pos(blockIdx.x);
   if (opos >= tiles_total) return;
   const int tile_i = (int)order[opos];
@@ -796,12 +819,112 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) { const uint32_t q = __shfl_xor(m, o, 64); m = q > m ? q : m; }
   m = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+  unsigned long long n_walk = 0, n_live = 0, n_contrib = 0;   // wave-uniform (kCount)
+  if (merge_tiles(hdr)) {
+    MergedLds& M = lds.merged;
+    if (lane == 0) M.smax[quad] = m;
+    __syncthreads();
+    m = max(max(M.smax[0], M.smax[1]), max(M.smax[2], M.smax[3]));
+    if (m > rg.y - rg.x) m = rg.y - rg.x;
+    const float tx0 = (float)(tx * kTile + Vw.vx), ty0 = (float)(ty * kTile + Vw.vy);
+    const uint32_t t = threadIdx.x;
+    for (uint32_t hi = m; hi > 0u;) {   // list positions [lo, hi) of this window
+      const uint32_t lo = hi > (uint32_t)kBlock ? hi - kBlock : 0u;
+      const uint32_t cnt = hi - lo;
+      __syncthreads();
+      uint32_t qm = 0;
+      if (t < cnt) {
+        uint32_t f = svals[rg.x + lo + t];
+        if ((int64_t)f >= VN) f = 0u;   // defensive: the sort only emits indices < V*n
+        const float4 g0 = rec[kRecQuads * (int64_t)f], g1 = rec[kRecQuads * (int64_t)f + 1], g2 = rec[kRecQuads * (int64_t)f + 2];
+        const float cut = entry_cut(g0.z);
+        M.s0[t] = make_float4(g0.x, g0.y, -0.5f * g1.x, -g1.y);
+        M.s1[t] = make_float4(-0.5f * g1.z, g0.z, g2.x, g2.y);
+        M.s2[t] = make_float4(g2.z, cut, 0.0f, __uint_as_float(f));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          qm |= block_reached<8>(g0.x, g0.y, g1.x, g1.y, g1.z, g0.w, cut, tx0 + (float)((q & 1) * 8), ty0 + (float)((q >> 1) * 8)) << q;
+      }
+#pragma unroll
+      for (int q = 0; q < kGscreen; ++q) M.acc[q * kBlock + t] = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t b = ballot64((qm >> q) & 1u);
+        if (lane == 0) M.qmask[quad][q] = b;
+      }
+      __syncthreads();
+      for (int c = 3; c >= 0; --c) {
+        const unsigned long long mv = M.qmask[c][quad];
+        uint64_t mk = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mv >> 32)) << 32) |
+                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mv);
+        if (kCount) n_walk += 64ull * (unsigned)__popcll(mk);
+        while (mk != 0ull) {
+          const int e = 63 - __builtin_clzll(mk);
+          mk &= ~(1ull << e);
+          const int k = c * 64 + e;
+          const float4 a = M.s0[k], c4 = M.s1[k], bc = M.s2[k];
+          const float dx = a.x - pcx, dy = a.y - pcy;
+          const float power = fmaf_(a.z * dx, dx, fmaf_(c4.x * dy, dy, (a.w * dx) * dy));
+          const uint64_t lm = ballot64(__builtin_amdgcn_fmed3f(power, bc.y, 0.0f) == power) & ballot64(lo + (uint32_t)k < last);
+          if (kCount) n_live += (unsigned long long)__popcll(lm);
+          if (lm == 0ull) continue;
+          const float G = cexp_core(power);
+          const float prod = c4.y * G;
+          const float al = fminf(0.99f, prod);
+          const uint64_t cm = ballot64(al >= kSkip) & lm;
+          if (kCount) n_contrib += (unsigned long long)__popcll(cm);
+          if (cm == 0ull) continue;
+          const uint64_t gm = ballot64(prod <= 0.99f) & cm;
+          const float oma = 1.0f - al;
+          const float r0 = __builtin_amdgcn_rcpf(oma);
+          const float Tk = T * fmaf_(fmaf_(-oma, r0, 1.0f), r0, r0);
+          const float gc = fmaf_(g0c, c4.z, fmaf_(g1c, c4.w, g2c * bc.x));
+          const float dLda = Tk * (gc - gR);
+          const float h = __builtin_amdgcn_inverse_ballot_w64(gm) ? dLda * G : 0.f;
+          const float w = __builtin_amdgcn_inverse_ballot_w64(cm) ? al * Tk : 0.f;
+          const float hx = h * dx, hy = h * dy;
+          const float v8[8] = {hx, hy, hx * dx, hx * dy, hy * dy, h, g0c * w, g1c * w};
+          float u = row_sum8(v8);         // lane 8 g + e: sum g over the rows; then over the columns
+          u += dpp_read<0x141, 0xF>(u);   // row_half_mirror
+          u += dpp_read<0x4E, 0xF>(u);    // quad_perm (2, 3, 0, 1)
+          u += dpp_read<0xB1, 0xF>(u);    // quad_perm (1, 0, 3, 2)
+          const float b = wave_total63(g2c * w);
+          if ((lane & 7u) == 0u || lane == 63u) atomicAdd(&M.acc[k * kGscreen + (lane == 63u ? 8 : (int)(lane >> 3))], lane == 63u ? b : u);
+          if (__builtin_amdgcn_inverse_ballot_w64(cm)) {
+            gR = fmaf_(al, gc, oma * gR);
+            T = Tk;
+          }
+        }
+      }
+      __syncthreads();
+      // Consecutive threads take consecutive floats of an entry's nine; the partials from the sums as below.
+      for (uint32_t it = t; it < cnt * kGscreen; it += kBlock) {
+        const uint32_t k = it / kGscreen, q = it - k * kGscreen;
+        float val = M.acc[it];
+        if (q < 5u) {
+          const float4 a = M.s0[k];
+          const float4 c4 = M.s1[k];
+          const float m0 = M.acc[k * kGscreen], m1 = M.acc[k * kGscreen + 1];
+          val = q == 0u ? c4.y * fmaf_(2.f * a.z, m0, a.w * m1)
+              : q == 1u ? c4.y * fmaf_(2.f * c4.x, m1, a.w * m0)
+              : c4.y * (q == 3u ? -val : -0.5f * val);
+        }
+        if (val != 0.0f) atomicAdd(gscreen + (int64_t)__float_as_uint(M.s2[k].w) * kGscreen + q, val);
+      }
+      hi = lo;
+    }
+    if (kCount && lane == 0) {
+      atomicAdd(pair_part + 3 * (int64_t)tile_i, n_walk);
+      atomicAdd(pair_part + 3 * (int64_t)tile_i + 1, n_live);
+      atomicAdd(pair_part + 3 * (int64_t)tile_i + 2, n_contrib);
+    }
+    return;
+  }
   if (m > rg.y - rg.x) m = rg.y - rg.x;   // (a last of this list never is)
   if (m == 0u) return;
   S.gl[0][lane] = g0c;
   S.gl[1][lane] = g1c;
   S.gl[2][lane] = g2c;
-  unsigned long long n_walk = 0, n_live = 0, n_contrib = 0;   // wave-uniform (kCount)
   auto lds_fence = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

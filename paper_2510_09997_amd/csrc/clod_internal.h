@@ -144,14 +144,16 @@ constexpr uint32_t kSelWords = 3 * kSelBins + kSelBlocks;
 constexpr size_t kSelBytes = 4 * (size_t)kSelWords;
 
 // Workspace header words (uint64): pairs, overflow flag, rendered records; of the depth sort the
-// subtrahend of the keys and their bit length; row pairs per column unit and column units.
+// subtrahend of the keys and their bit length; row pairs per column unit and column units; sum of the
+// records' squared tile counts.
 enum : int { kHdrDup = 0, kHdrOverflow = 1, kHdrRend = 2, kHdrKeyBase = 3, kHdrKeyBits = 4, kHdrUnit = 5,
-             kHdrUnits = 6, kHdrWords = 8 };
+             kHdrUnits = 6, kHdrSquares = 7, kHdrWords = 8 };
 
-// Per chunk of the compaction: tile pairs and largest depth key.
+// Per chunk of the compaction: tile pairs, largest depth key, sum of the squared tile counts.
 struct DepthStat {
   unsigned long long pairs;
-  uint32_t kmax, reserved;
+  uint32_t kmax;
+  float squares;
 };
 
 // Per tile row of the batch (one more entry closes the ranges): first tile, first row pair, first
@@ -620,6 +622,19 @@ __device__ __forceinline__ float row_sum8(const float (&v)[8]) {
   const bool hi8 = (__lane_id() & 8u) != 0u;
   const float keep = hi8 ? s1 : s0, send = hi8 ? s0 : s1;
   return keep + dpp_read<0x128, 0xF>(send);              // row_ror:8
+}
+
+// Sum over the 64 lanes of a wave with DPP lane moves fused into the adds: quad swaps give quad
+// sums, the half-row and row mirrors row (16-lane) sums, and the two row broadcasts fold rows 0-2
+// into row 3.  The total is in lane 63.  Every lane of the wave must be active.
+__device__ __forceinline__ float wave_total63(float v) {
+  v += dpp_read<0xB1, 0xF>(v);    // quad_perm (1, 0, 3, 2)
+  v += dpp_read<0x4E, 0xF>(v);    // quad_perm (2, 3, 0, 1)
+  v += dpp_read<0x141, 0xF>(v);   // row_half_mirror
+  v += dpp_read<0x140, 0xF>(v);   // row_mirror
+  v += dpp_read<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_read<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
 }
 
 // Weight of Eq. (5): w_s = (1 - 0.5 s_v / max(s_v))^2.

@@ -19,19 +19,6 @@ namespace clod {
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
-// Sum over the 64 lanes of a wave with DPP lane moves fused into the adds: quad swaps give quad
-// sums, the half-row and row mirrors row (16-lane) sums, and the two row broadcasts fold rows 0-2
-// into row 3.  The total is in lane 63.  Every lane of the wave must be active.
-__device__ __forceinline__ float wave_total63(float v) {
-  v += dpp_read<0xB1, 0xF>(v);    // quad_perm (1, 0, 3, 2)
-  v += dpp_read<0x4E, 0xF>(v);    // quad_perm (2, 3, 0, 1)
-  v += dpp_read<0x141, 0xF>(v);   // row_half_mirror
-  v += dpp_read<0x140, 0xF>(v);   // row_mirror
-  v += dpp_read<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-  v += dpp_read<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 // Eq. (2): alpha'' = alpha exp(-q), q = d^2 k / den with k = (s_v / d_max)^2 and den the decay's
 // denominator.  With t = dL/dalpha'' alpha'': dL/dlogit = t (1 - alpha), dL/dden = t q / den,
 // dL/dmu = -2 t k (mu - c) / den, dL/dd_max = 2 t q / d_max.  Every term is linear in dL/dalpha'',
