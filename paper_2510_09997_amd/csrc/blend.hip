@@ -755,7 +755,13 @@ struct BwdLds {
 // on their own and merged: 24 tiles (250,000 Gaussians) 163 and 192, 51 tiles (250,000) 432 and 571, 87
 // tiles (64,000) 236 and 277, 102 tiles (64,000, 256 x 256) 198 and 227; 132 tiles (64,000) 220 and
 // 171, 245 tiles (16,000) 213 and 139, 498 tiles (250,000) 368 and 244, 1,836 tiles (4,000) 836 and 320.
-// Between 100 and 300 either may win by a little.
+// Between 100 and 300 either may win by a little.  That mean alone also takes in batches of many small
+// records and a few splats beside a camera, which waves on their own walk faster: their flushes seldom
+// meet.  So, besides, either the records are large throughout (24 tiles on average), or two pairs drawn
+// at random belong to one record once in 8,192 times (sum t^2 against D^2): 16 views of 2M, 656,000
+// records of 17 tiles, mean 302, once in 38,000, 2,018 and 2,167 us; one view of 1M, 66,000 records of 16
+// tiles, mean 157, once in 6,700, 370 and 325; 16 views, 458,000 records of 22 tiles, 2,203 and 2,245;
+// one view of 250,000, 79,560 records of 79 tiles, mean 305, once in 21,000, 425 and 331.
 struct MergedLds {
   float4 s0[kBlock], s1[kBlock], s2[kBlock];   // (u, v, -A/2, -B), (-C/2, alpha'', r, g), (b, cut, -, record)
   float acc[kBlock * kGscreen];                // [entry][9]: odd stride, conflict-free
@@ -767,9 +773,11 @@ union BwdBlockLds {
   MergedLds merged;
 };
 static_assert(sizeof(BwdBlockLds) <= 160 * 1024 / 5, "five workgroups per CU");
-constexpr unsigned long long kMergeTiles = 112;
+constexpr unsigned long long kMergeTiles = 112, kMergeMean = 24;
+constexpr int kMergeMeetLog = 13;
 __device__ __forceinline__ bool merge_tiles(const unsigned long long* hdr) {
-  return hdr[kHdrSquares] >= kMergeTiles * hdr[kHdrDup];
+  const unsigned long long D = hdr[kHdrDup], squares = hdr[kHdrSquares];   // D <= 2^32 - 2: no product wraps
+  return squares >= kMergeTiles * D && (D >= kMergeMean * hdr[kHdrRend] || squares >= (D >> kMergeMeetLog) * D);
 }
 template <bool kCount>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_blend_bwd(
