@@ -143,9 +143,11 @@ clod_status clod_project(const clod_scene *scene, const clod_batch *batch, int64
    the stable order of the keys (tile_base[view] + tile) << 32 | bits(depth) emitted per
    rendered Gaussian in index order and per covered tile in row-major order -- i.e. ordered by
    (view, tile, depth, Gaussian index) -- and per-tile [start, end) ranges of the sorted list.
-   Built as a radix sort of the rendered records by depth followed by a stable radix sort of
-   the pairs, emitted in that depth order, by tile id.  If more pairs exist than the duplicate buffer holds, nothing is written beyond
-   it, the overflow is recorded in ws and later calls on this batch are no-ops; with
+   Built as a radix sort of the rendered records by depth and, in that order, two stable
+   partitions: of each record's tile rows by row, then of each row's tiles by column.  Batches of
+   more than 2,048 tile rows or with a frame beyond 256 x 256 tiles emit all pairs in depth order
+   instead and radix-sort them by tile id.  If more pairs exist than the duplicate buffer holds,
+   nothing is written beyond it, the overflow is recorded in ws and later calls on this batch are no-ops; with
    n_dup_host != NULL the call synchronises `stream`, stores the pair count D (also on
    overflow) and returns CLOD_E_CAPACITY on overflow (enlarge batch->dup and call again; the
    clod_project results stay valid). */
@@ -232,8 +234,8 @@ clod_status clod_lod_count_noalloc(const clod_scene *scene, int32_t n_views, con
    Writes loss_dev (device float [n_views]), dL_drgb (the gradient of L_v with respect to the
    view's rgb; sign(0) = 0) and dL_deta_dev (device float [n_views], nullable) = w_s lambda_reg
    dL_reg/deta.  lambda_dssim in [0, 1]; when it is > 0, ssim_scratch is a device buffer of at
-   least 36 bytes per pixel of the batch (room for per-pixel SSIM derivatives; its contents are
-   unspecified afterwards); with 0 it may be NULL and L_render = L1. */
+   least 36 bytes per pixel of the batch (required and checked; the derivatives stay on the chip
+   and nothing is read or written there); with 0 it may be NULL and L_render = L1. */
 clod_status clod_loss(const clod_batch *batch, const float *rgb, const float *target,
                       float s_max, float lambda_reg, float lambda_dssim, float *ssim_scratch,
                       size_t ssim_scratch_bytes, float *loss_dev, float *dL_drgb,

@@ -369,10 +369,12 @@ __device__ __forceinline__ float sigmoid_c(float o) { return 1.0f / (1.0f + cexp
 
 // Correctly rounded square root and quotient in fewer instructions than the general ones, for
 // arguments whose intermediates stay normal (the caller checks: x in [2^-80, 2^80]; |a|, |b| in
-// [2^-60, 2^60] or a = 0).  The root is the Newton step on the hardware reciprocal root with a
-// final residual; the quotient takes rb = 1 / b correctly rounded and corrects a * rb by two
-// residuals, the second of which rounds correctly (Markstein: the first quotient is then within an
-// ulp and rb is the rounded reciprocal).  Both are bit-identical to sqrtf and a / b there.
+// [2^-60, 2^60] or a = 0).  The root is one coupled step g ~ sqrt(x), h ~ 1 / (2 sqrt(x)) from the
+// hardware reciprocal root with a final residual (P. Markstein, "Software division and square root
+// using Goldschmidt's algorithms", RNC 6, 2004); the quotient takes rb = 1 / b correctly rounded and
+// corrects a * rb by two residuals, the second of which rounds correctly (P. Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000 processor", IBM J. Res. Dev. 34(1), 1990: the
+// first quotient is then within an ulp).  Both are bit-identical to sqrtf and a / b there.
 __device__ __forceinline__ float sqrt_normal(float x) {
   const float y = __builtin_amdgcn_rsqf(x);
   float g = x * y, h = 0.5f * y;
