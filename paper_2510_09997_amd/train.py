@@ -38,7 +38,7 @@ class MultiViewTrainer:
         self.deta = torch.empty(len(views), device=dev, dtype=torch.float32)
         self.grads = {k: torch.zeros_like(v) for k, v in scene.t.items()}
         self.hdr = torch.empty(16, dtype=torch.uint8, pin_memory=True)
-        # Per-pixel SSIM derivatives (36 B per pixel), only when the D-SSIM term is on.
+        # The loss checks for 36 B per pixel when the D-SSIM term is on (nothing is stored there).
         self.ssim_scratch = torch.empty(9 * b.pixels, device=dev, dtype=torch.float32) if self.lambda_dssim > 0 else None
         self.graph = None
         if dup_capacity is None:
